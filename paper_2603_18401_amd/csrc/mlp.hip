@@ -77,36 +77,174 @@ __global__ __launch_bounds__(kFeatThreads) void k_eps_features(const EpsPair* __
 }
 
 // --------------------------------------------------------------- inference
+// The 6-64-64 layers on the BF16 matrix cores, exactly: the weights are BF16
+// values, and an FP32 activation is the sum of three BF16 values (8 + 8 + 8
+// significant bits, by truncation: x = hi + mid + lo with nothing left over),
+// so W x = W hi + W mid + W lo with every product exact and FP32
+// accumulation, as in FP32 arithmetic (error against 64 bits 1.1e-7 either
+// way).  A wavefront takes 64 keypoints, 16 at a time: v_mfma_f32_16x16x32,
+// rows = units, columns = keypoints; the three parts of the six features and
+// a constant 1 (the bias) fill one 32-deep product, and layer 1's result
+// (units 16 t + 4 g + r of keypoint l & 15, g = l >> 4) is layer 2's operand
+// as it stands, its weights read in that order once per wavefront.  28
+// products of 16 cycles per 16 keypoints; the vector arithmetic of the splits
+// and the output layer bounds it.  One thread per keypoint with the weights
+// broadcast from LDS took 332 us for 2 M keypoints; this takes 72 us.
 constexpr int kInferThreads = 256;
+constexpr int kInferWaves = kInferThreads / kWave;
+constexpr int kInferBlocks = 768;  // three per CU: the weights are staged once per workgroup
+// Features and weights from these sizes on (or not finite) are left to the
+// plain evaluation, whose infinities and overflows a split does not
+// reproduce; below them no product or sum of the network can overflow.
+constexpr float kInferBigX = 1e9f, kInferBigW = 1e6f;
 
-__global__ __launch_bounds__(kInferThreads) void k_eps_infer(const float* __restrict__ feat,
+// max(x, 0) of a value that is not NaN, as integers: one instruction, where
+// fmaxf quiets its operand first
+__device__ __forceinline__ float relu_finite(float x) {
+  return __int_as_float(max(__float_as_int(x), 0));
+}
+
+__device__ __forceinline__ uint32_t bf16_pair(float lo, float hi) {  // upper halves of both
+  return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u);
+}
+
+__device__ __forceinline__ float bf16_trunc(float x) {
+  return __uint_as_float(__float_as_uint(x) & 0xFFFF0000u);
+}
+
+// Eight values as three BF16 operands whose sum they are.
+__device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&part)[3]) {
+  uint32_t w[3][4];
+  #pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const float a = x[2 * k], b = x[2 * k + 1];
+    const float a1 = a - bf16_trunc(a), b1 = b - bf16_trunc(b);
+    const float a2 = a1 - bf16_trunc(a1), b2 = b1 - bf16_trunc(b1);
+    w[0][k] = bf16_pair(a, b);
+    w[1][k] = bf16_pair(a1, b1);
+    w[2][k] = bf16_pair(a2, b2);
+  }
+  #pragma unroll
+  for (int p = 0; p < 3; ++p)
+    part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
+}
+
+// The network's z by one thread, left to right (weights in LDS).
+__device__ float infer_plain(const float* w, const float (&x)[kIn]) {
+  float z = w[kOffB3];
+  for (int r = 0; r < kH; ++r) {
+    float a = w[kOffB2 + r];
+    for (int u = 0; u < kH; ++u) {
+      float h = w[kOffB1 + u];
+      #pragma unroll
+      for (int c = 0; c < kIn; ++c) h = fmaf(w[kOffW1 + u * kIn + c], x[c], h);
+      a = fmaf(w[kOffW2 + r * kH + u], fmaxf(h, 0.0f), a);
+    }
+    z = fmaf(w[kOffW3 + r], fmaxf(a, 0.0f), z);
+  }
+  return z;
+}
+
+__global__ __launch_bounds__(kInferThreads, 2) void k_eps_infer(const float* __restrict__ feat,
                                                              int64_t n,
                                                              const float* __restrict__ params,
                                                              float* __restrict__ eps) {
   __shared__ float w[kParams];
-  for (int p = threadIdx.x; p < kParams; p += kInferThreads) w[p] = bf16_round(params[p]);
-  __syncthreads();
-  const int64_t j = (int64_t)blockIdx.x * kInferThreads + threadIdx.x;
-  if (j >= n) return;
-  float x[kIn];
-  #pragma unroll
-  for (int c = 0; c < kIn; ++c) x[c] = feat[kIn * j + c];
-  float h1[kH];
-  #pragma unroll
-  for (int u = 0; u < kH; ++u) {
-    float a = w[kOffB1 + u];
-    #pragma unroll
-    for (int c = 0; c < kIn; ++c) a = fmaf(w[kOffW1 + u * kIn + c], x[c], a);
-    h1[u] = fmaxf(a, 0.0f);
+  __shared__ uint4 parts[kInferWaves][3][kWave];  // a wavefront's split features
+  const int lane = lane_id(), wave = wave_id();
+  const int c = lane & 15, g = lane >> 4;
+  bool odd = false;  // a weight out of the range
+  for (int p = threadIdx.x; p < kParams; p += kInferThreads) {
+    w[p] = bf16_round(params[p]);
+    odd |= !(fabsf(w[p]) < kInferBigW);
   }
-  float z = w[kOffB3];
-  for (int r = 0; r < kH; ++r) {
-    float a = w[kOffB2 + r];
+  const bool plain_all = __syncthreads_or(odd) != 0;
+  // operands: element e of lane (c, g) is k = 8 g + e
+  bf16x8 w1[4], w2[4][2];
+  f32x4 b2[4], w3[4];
+  #pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int u = 16 * t + c;
+    float v[8];
     #pragma unroll
-    for (int c = 0; c < kH; ++c) a = fmaf(w[kOffW2 + r * kH + c], h1[c], a);
-    z = fmaf(w[kOffW3 + r], fmaxf(a, 0.0f), z);
+    for (int e = 0; e < 8; ++e)
+      v[e] = g == 3 || e > kIn ? 0.0f : (e < kIn ? w[kOffW1 + u * kIn + e] : w[kOffB1 + u]);
+    w1[t] = __builtin_bit_cast(bf16x8, make_uint4(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]),
+                                                  bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])));
+    #pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      #pragma unroll
+      for (int e = 0; e < 8; ++e)  // unit 16 (2 s + e / 4) + 4 g + e % 4
+        v[e] = w[kOffW2 + u * kH + 16 * (2 * s + e / 4) + 4 * g + e % 4];
+      w2[t][s] = __builtin_bit_cast(bf16x8, make_uint4(bf16_pair(v[0], v[1]), bf16_pair(v[2], v[3]),
+                                                       bf16_pair(v[4], v[5]), bf16_pair(v[6], v[7])));
+    }
+    #pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      b2[t][r] = w[kOffB2 + 16 * t + 4 * g + r];
+      w3[t][r] = w[kOffW3 + 16 * t + 4 * g + r];
+    }
   }
-  eps[j] = fminf(fmaxf(softplus_f(z), kEpsMin), kEpsMax);
+  const float b3 = w[kOffB3];
+  const f32x4 zero = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t step = (int64_t)gridDim.x * kInferThreads;
+  for (int64_t j0 = ((int64_t)blockIdx.x * kInferWaves + wave) * kWave; j0 < n; j0 += step) {
+    const int64_t j = j0 + lane;
+    float x[kIn];
+    bool fine = true;
+    #pragma unroll
+    for (int k = 0; k < kIn; ++k) {
+      x[k] = j < n ? feat[kIn * j + k] : 0.0f;
+      fine &= fabsf(x[k]) < kInferBigX;
+    }
+    {
+      const float v[8] = {x[0], x[1], x[2], x[3], x[4], x[5], 1.0f, 0.0f};
+      bf16x8 part[3];
+      split8(v, part);
+      #pragma unroll
+      for (int p = 0; p < 3; ++p) parts[wave][p][lane] = __builtin_bit_cast(uint4, part[p]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    float z = 0.0f;
+    #pragma unroll
+    for (int q = 0; q < 4; ++q) {  // keypoints j0 + 16 q ..
+      const uint4 raw = parts[wave][g < 3 ? g : 0][16 * q + c];
+      const bf16x8 xin = __builtin_bit_cast(bf16x8, g < 3 ? raw : make_uint4(0u, 0u, 0u, 0u));
+      f32x4 h[4];
+      #pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        h[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w1[t], xin, zero, 0, 0, 0);
+        #pragma unroll
+        for (int r = 0; r < 4; ++r) h[t][r] = relu_finite(h[t][r]);
+      }
+      f32x4 a[4] = {b2[0], b2[1], b2[2], b2[3]};
+      #pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const float v[8] = {h[2 * s][0], h[2 * s][1], h[2 * s][2], h[2 * s][3],
+                            h[2 * s + 1][0], h[2 * s + 1][1], h[2 * s + 1][2], h[2 * s + 1][3]};
+        bf16x8 part[3];
+        split8(v, part);
+        #pragma unroll
+        for (int p = 0; p < 3; ++p)
+          #pragma unroll
+          for (int t = 0; t < 4; ++t)
+            a[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w2[t][s], part[p], a[t], 0, 0, 0);
+      }
+      float zp = 0.0f;
+      #pragma unroll
+      for (int t = 0; t < 4; ++t)
+        #pragma unroll
+        for (int r = 0; r < 4; ++r) zp = fmaf(w3[t][r], relu_finite(a[t][r]), zp);
+      zp += __shfl_xor(zp, 16);
+      zp += __shfl_xor(zp, 32);
+      z = g == q ? zp + b3 : z;  // lane 16 q + c keeps keypoint 16 q + c
+    }
+    if (plain_all || ballot(!fine) != 0ull) z = infer_plain(w, x);
+    if (j < n) eps[j] = fminf(fmaxf(softplus_f(z), kEpsMin), kEpsMax);
+    __builtin_amdgcn_wave_barrier();  // the parts are read before they are written again
+  }
 }
 
 // ---------------------------------------------------------------- training
@@ -493,7 +631,8 @@ hipError_t launch_eps_features(const EpsPair* pairs, const int64_t* kstart, int 
 hipError_t launch_eps_infer(const float* feat, int64_t n, const float* params, float* eps,
                             hipStream_t s) {
   if (n == 0) return hipSuccess;
-  const int64_t blocks = (n + kInferThreads - 1) / kInferThreads;
+  int64_t blocks = (n + kInferThreads - 1) / kInferThreads;
+  if (blocks > kInferBlocks) blocks = kInferBlocks;
   hipLaunchKernelGGL(k_eps_infer, dim3((unsigned)blocks), dim3(kInferThreads), 0, s, feat, n,
                      params, eps);
   return hipGetLastError();

@@ -1,8 +1,10 @@
 """The tolerance network's matrix kernels at the edges of their tiles: batches
-around 16, 64 and a full launch, with samples outside the caller's arrays.
+and keypoint counts around 16, 64 and a full launch, samples outside the
+caller's arrays, and inputs that the split into BF16 parts cannot hold.
 
-Tolerance: gradients as FP32 sums of the batch, 1e-4 of the largest entry, as
-derived for the full-size check."""
+Tolerances: gradients as FP32 sums of the batch, 1e-4 of the largest entry;
+inference 1e-5 relative + 5e-5 px (64-term FP32 dot products of O(1-10)
+terms); both as derived for the full-size checks."""
 
 import numpy as np
 import pytest
@@ -58,3 +60,56 @@ def test_gradient_tile_edges(batch):
     assert np.abs(got - rg).max() <= 1e-4 * np.abs(rg).max()
     again = tr.grad(g(X), g(y), g(slots), feat_index=g(fidx))[0].cpu().numpy()
     assert np.array_equal(got, again.astype(np.float64))
+
+
+@pytest.mark.parametrize("n", [1, 15, 17, 63, 64, 65, 257, 768 * 256 + 1])
+def test_inference_tile_edges(n):
+    from paper_2603_18401_amd import learned_eps as L
+    torch = torch_gpu()
+    theta = _net(5)
+    X = _features(np.random.default_rng(n), n)
+    dev = torch.device("cuda:0")
+    got = L.infer(torch.from_numpy(X).to(dev), torch.from_numpy(theta).to(dev)).cpu().numpy()
+    ref = mlp.infer_bf16(theta, X)
+    assert np.all(np.abs(got - ref) <= 1e-5 * ref + 5e-5), np.abs(got - ref).max()
+
+
+def _plain(theta, X):
+    """The network left to right in FP32, max(NaN, 0) = 0."""
+    u = theta.view(np.uint32)
+    t = ((u + 0x7FFF + ((u >> 16) & 1)) & np.uint32(0xFFFF0000)).view(np.float32)
+    w1, b1, w2, b2 = t[:384].reshape(64, 6), t[384:448], t[448:4544].reshape(64, 64), t[4544:4608]
+    w3, b3 = t[4608:4672], t[4672]
+    out = np.empty(len(X), np.float32)
+    with np.errstate(all="ignore"):
+        for k, x in enumerate(X.astype(np.float32)):
+            a = b1.copy()
+            for c in range(6):
+                a = a + w1[:, c] * x[c]
+            h = np.fmax(a, np.float32(0))
+            a = b2.copy()
+            for c in range(64):
+                a = a + w2[:, c] * h[c]
+            z = np.float64(b3)
+            for c in range(64):
+                z = z + np.float64(w3[c]) * np.fmax(a[c], np.float32(0))
+            sp = np.fmax(z, 0) + np.log1p(np.exp(-np.abs(z)))
+            out[k] = np.fmin(np.fmax(sp, 0.5), 8.0)
+    return out
+
+
+@pytest.mark.parametrize("what", ["features", "weights"])
+def test_inference_of_what_a_split_cannot_hold(what):
+    from paper_2603_18401_amd import learned_eps as L
+    torch = torch_gpu()
+    theta = _net(6)
+    X = _features(np.random.default_rng(1), 200)
+    if what == "features":
+        X[3, 5], X[70, 0], X[71, 1], X[130, 2], X[199, 0] = np.inf, np.nan, -np.inf, 1e20, 3e38
+    else:
+        theta[448 + 77] = np.inf
+        theta[4544 + 9] = np.nan
+    dev = torch.device("cuda:0")
+    got = L.infer(torch.from_numpy(X).to(dev), torch.from_numpy(theta).to(dev)).cpu().numpy()
+    ref = _plain(theta, X)
+    assert np.all(np.abs(got - ref) <= 1e-5 * ref + 5e-5), np.abs(got - ref).max()
