@@ -20,6 +20,7 @@ and a whole batch can be recorded once and replayed as one HIP graph:
 
 import ctypes
 import os
+import struct
 
 import numpy as np
 
@@ -262,20 +263,38 @@ class PairSpec:
     """One image pair: F (3x3, row-major), image-2 size, keypoint counts."""
 
     def __init__(self, F, w2, h2, m, n):
-        self.F = np.asarray(F, dtype=np.float64).reshape(9)
+        self.F = F
         self.w2, self.h2, self.m, self.n = int(w2), int(h2), int(m), int(n)
+
+    @property
+    def F(self):
+        return self._F
+
+    @F.setter
+    def F(self, F):
+        self._F = np.ascontiguousarray(F, dtype=np.float64).reshape(9)
+
+
+# the fields of epm_pair after F
+_PAIR_TAIL = struct.Struct("=2i4q")
+assert 72 + _PAIR_TAIL.size == ctypes.sizeof(_Pair)
 
 
 def _pair_array(specs):
-    arr = (_Pair * len(specs))()
+    """The epm_pair array of a batch and its keypoint totals (N1, N2), as one
+    byte string: 0.15 ms for 512 pairs, where assigning the ctypes fields one
+    by one took 1.2 ms, a third of the batch's time on the GPU."""
+    parts = []
     q = k = 0
-    for a, s in zip(arr, specs):
-        a.F[:] = [float(v) for v in s.F]
-        a.w2, a.h2 = s.w2, s.h2
-        a.q_begin, a.m, a.k_begin, a.n = q, s.m, k, s.n
-        q += s.m
-        k += s.n
-    return arr, q, k
+    pack = _PAIR_TAIL.pack
+    for s in specs:
+        m, n = s.m, s.n
+        parts.append(s._F if type(s) is PairSpec
+                     else np.ascontiguousarray(s.F, dtype=np.float64).reshape(9))
+        parts.append(pack(s.w2, s.h2, q, m, k, n))
+        q += m
+        k += n
+    return (_Pair * len(specs)).from_buffer(bytearray(b"".join(parts))), q, k
 
 
 class Index:

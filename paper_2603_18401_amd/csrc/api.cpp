@@ -217,24 +217,19 @@ epm_status setup_pair(const epm_pair& in, PairDev& pd) {
   return EPM_OK;
 }
 
-void make_tiles(const std::vector<int64_t>& starts, int P, std::vector<SortTile>& tiles,
-                std::vector<SortSeg>& segs) {
-  tiles.clear();
+// The sort segments of `starts` and their tiles; the total of tiles.  (The
+// tile lists themselves are made on the device, from the segments.)
+int64_t make_segs(const std::vector<int64_t>& starts, int P, std::vector<SortSeg>& segs) {
   segs.resize(P);
+  int64_t tiles = 0;
   for (int p = 0; p < P; ++p) {
-    const int64_t b = starts[p], cnt = starts[p + 1] - starts[p];
-    segs[p].begin = b;
-    segs[p].count = cnt;
-    segs[p].tile_begin = (int32_t)tiles.size();
-    for (int64_t o = 0; o < cnt; o += kSortTile) {
-      SortTile t;
-      t.begin = b + o;
-      t.count = (int32_t)(cnt - o < kSortTile ? cnt - o : kSortTile);
-      t.seg = p;
-      tiles.push_back(t);
-    }
-    segs[p].tile_count = (int32_t)tiles.size() - segs[p].tile_begin;
+    segs[p].begin = starts[p];
+    segs[p].count = starts[p + 1] - starts[p];
+    segs[p].tile_begin = (int32_t)tiles;
+    segs[p].tile_count = (int32_t)tiles_of(segs[p].count);
+    tiles += segs[p].tile_count;
   }
+  return tiles;
 }
 
 }  // namespace
@@ -245,9 +240,8 @@ struct epm_index {
   std::vector<PairDev> pairs;
   std::vector<int32_t> stile_begin;  // first stabbing tile of every pair, and the total
   std::vector<int64_t> qstart, kstart;
-  std::vector<SortTile> rtiles, qtiles;
   std::vector<SortSeg> rsegs, qsegs;
-  std::vector<StabTile> stiles;
+  int64_t rtiles = 0, qtiles = 0, stiles = 0;  // tiles of the two sorts and of the stabbing pass
   std::vector<char> head;  // host image of the table region of the workspace
   char* ws = nullptr;
   Layout L;
@@ -310,8 +304,8 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   }
   idx->qstart[num_pairs] = n1;
   idx->kstart[num_pairs] = n2;
-  make_tiles(idx->kstart, num_pairs, idx->rtiles, idx->rsegs);
-  make_tiles(idx->qstart, num_pairs, idx->qtiles, idx->qsegs);
+  idx->rtiles = make_segs(idx->kstart, num_pairs, idx->rsegs);
+  idx->qtiles = make_segs(idx->qstart, num_pairs, idx->qsegs);
   for (int p = 0; p < num_pairs; ++p) {
     PairDev& pd = idx->pairs[p];
     pd.rtile_begin = idx->rsegs[p].tile_begin;
@@ -321,18 +315,11 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   }
   idx->stile_begin.resize(num_pairs + 1);
   for (int p = 0; p < num_pairs; ++p) {
-    idx->stile_begin[p] = (int32_t)idx->stiles.size();
-    for (int64_t o = 0; o < pairs[p].m; o += kTileQ) {
-      StabTile t;
-      t.begin = pairs[p].q_begin + o;
-      t.count = (int32_t)(pairs[p].m - o < kTileQ ? pairs[p].m - o : kTileQ);
-      t.pair = p;
-      idx->stiles.push_back(t);
-    }
+    idx->stile_begin[p] = (int32_t)idx->stiles;
+    idx->stiles += stab_tiles_of(pairs[p].m);
   }
-  idx->stile_begin[num_pairs] = (int32_t)idx->stiles.size();
-  idx->L = make_layout(num_pairs, n1, n2, (int64_t)idx->rtiles.size(), (int64_t)idx->qtiles.size(),
-                       (int64_t)idx->stiles.size());
+  idx->stile_begin[num_pairs] = (int32_t)idx->stiles;
+  idx->L = make_layout(num_pairs, n1, n2, idx->rtiles, idx->qtiles, idx->stiles);
   if (workspace_bytes < idx->L.total) {
     delete idx;
     return EPM_ERR_WORKSPACE;
@@ -360,9 +347,9 @@ hipError_t expand_tiles(const epm_index* idx, hipStream_t stream) {
   const Layout& L = idx->L;
   return launch_expand_tiles(idx->at<SortSeg>(L.rsegs), idx->at<SortSeg>(L.qsegs),
                              idx->at<int64_t>(L.qstart), idx->at<int32_t>(L.stile_begin), idx->P,
-                             idx->at<SortTile>(L.rtiles), (int64_t)idx->rtiles.size(),
-                             idx->at<SortTile>(L.qtiles), (int64_t)idx->qtiles.size(),
-                             idx->at<StabTile>(L.stiles), (int64_t)idx->stiles.size(), stream);
+                             idx->at<SortTile>(L.rtiles), idx->rtiles,
+                             idx->at<SortTile>(L.qtiles), idx->qtiles,
+                             idx->at<StabTile>(L.stiles), idx->stiles, stream);
 }
 
 epm_status index_upload(epm_index* idx, hipStream_t stream) {
@@ -386,14 +373,14 @@ epm_status enqueue_build(epm_index* idx, const float* kp2_xy, const float* eps2,
   const int64_t n2 = idx->N2;
   const PairDev* dpairs = idx->at<PairDev>(L.pairs);
   const int64_t* dkstart = idx->at<int64_t>(L.kstart);
-  EPM_HIP(launch_intervals(dpairs, idx->at<SortTile>(L.rtiles), (int)idx->rtiles.size(), kp2_xy,
+  EPM_HIP(launch_intervals(dpairs, idx->at<SortTile>(L.rtiles), (int)idx->rtiles, kp2_xy,
                            eps2, eps_scalar, idx->at<uint32_t>(L.rk0), idx->at<uint32_t>(L.rv0),
                            idx->at<uint32_t>(L.recC), idx->at<uint32_t>(L.recH),
                            idx->at<uint32_t>(L.hist), sort_passes(kSortBits) - 1, stream));
   bool in1 = false;
   EPM_HIP(segmented_radix_sort(idx->at<uint32_t>(L.rk0), idx->at<uint32_t>(L.rv0),
                                idx->at<uint32_t>(L.rk1), idx->at<uint32_t>(L.rv1),
-                               idx->at<SortTile>(L.rtiles), (int)idx->rtiles.size(),
+                               idx->at<SortTile>(L.rtiles), (int)idx->rtiles,
                                idx->at<SortSeg>(L.rsegs), P, max_tiles(idx->rsegs),
                                idx->at<uint32_t>(L.hist), kSortBits, &in1, stream,
                                idx->at<uint32_t>(L.digit_base), true));
@@ -438,7 +425,7 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.cols = col_indices;
   A.capacity = capacity;
   A.tiles = idx->at<StabTile>(L.stiles);
-  A.num_tiles = (int)idx->stiles.size();
+  A.num_tiles = (int)idx->stiles;
   A.staging = idx->at<int32_t>(L.staging);
   A.stats = idx->at<unsigned long long>(L.stats);
   A.long_rows = idx->at<uint32_t>(L.long_rows);
@@ -487,7 +474,7 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
     if (A.match_stats) EPM_HIP(launch_clear_stats(nullptr, stream, nullptr, A.match_stats));
     return EPM_OK;
   }
-  EPM_HIP(launch_query_keys(A.pairs, idx->at<SortTile>(L.qtiles), (int)idx->qtiles.size(),
+  EPM_HIP(launch_query_keys(A.pairs, idx->at<SortTile>(L.qtiles), (int)idx->qtiles,
                             A.kp1, idx->at<uint32_t>(L.qkey), idx->at<uint32_t>(L.qflag),
                             idx->at<uint32_t>(L.qk0), idx->at<uint32_t>(L.qv0), A.qline,
                             idx->at<uint32_t>(L.qhist), sort_passes(kQuerySortBits) - 1, A.stats,
@@ -495,7 +482,7 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   bool in1 = false;
   EPM_HIP(segmented_radix_sort(idx->at<uint32_t>(L.qk0), idx->at<uint32_t>(L.qv0),
                                idx->at<uint32_t>(L.qk1), idx->at<uint32_t>(L.qv1),
-                               idx->at<SortTile>(L.qtiles), (int)idx->qtiles.size(),
+                               idx->at<SortTile>(L.qtiles), (int)idx->qtiles,
                                idx->at<SortSeg>(L.qsegs), idx->P, max_tiles(idx->qsegs),
                                idx->at<uint32_t>(L.qhist), kQuerySortBits, &in1, stream, nullptr,
                                true));
@@ -631,7 +618,7 @@ MatchArgs match_args(epm_index* idx, const MatchCall& c) {
   A.best_dist = c.best_dist;
   A.second_dist = c.second_dist;
   A.tiles = idx->at<StabTile>(L.stiles);
-  A.num_tiles = (int)idx->stiles.size();
+  A.num_tiles = (int)idx->stiles;
   A.windows = idx->at<TileWindow>(L.windows);
   A.rinv = idx->at<uint32_t>(L.rinv);
   A.rj = idx->at<int32_t>(L.rj);
@@ -1710,7 +1697,7 @@ epm_status epm_get_query_stats(const epm_index* idx, epm_query_stats* out) {
   out->queries = idx->N1;
   if (!idx->have_stats) return EPM_OK;
   // the tile pass leaves its counters per tile: summed here
-  const size_t nt = idx->stiles.size();
+  const size_t nt = (size_t)idx->stiles;
   std::vector<unsigned long long> tc((size_t)kTileCounts * nt);
   int64_t nnz = 0;
   if (nt > 0)
@@ -1741,7 +1728,7 @@ epm_status epm_get_match_stats(const epm_index* idx, epm_match_stats* out) {
                          sizeof(unsigned long long) * kNumMatchStats, hipMemcpyDeviceToHost,
                          idx->match_stream));
   // a match fused into the tile pass leaves its BF16 counters per tile
-  const size_t nt = idx->match_from_tiles ? idx->stiles.size() : 0;
+  const size_t nt = idx->match_from_tiles ? (size_t)idx->stiles : 0;
   std::vector<unsigned long long> tc((size_t)kTileCounts * nt);
   if (nt > 0)
     EPM_HIP(hipMemcpyAsync(tc.data(), idx->at<unsigned long long>(idx->L.tile_counts),
