@@ -420,6 +420,7 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.reps = idx->at<float>(L.reps);
   A.rinv = idx->at<uint32_t>(L.rinv);
   A.counts = idx->at<uint32_t>(L.counts);
+  A.row_sums = nullptr;
   A.qrec = nullptr;
   A.row_offsets = row_offsets;
   A.cols = col_indices;
@@ -455,8 +456,9 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   return A;
 }
 
-// Query keys and their sort, the tile windows, the stabbing pass and the
-// scan of the row lengths into row_offsets (Algorithm 1, matching loop).
+// Query keys and their sort, the tile windows, the stabbing pass, and the row
+// offsets with the parked rows and the matches selected so far (Algorithm 1,
+// matching loop).
 // records_ready: the record build runs on another stream and completes this
 // event; the stream waits for it after the query sort, before the first
 // kernel that reads the records.
@@ -489,6 +491,9 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   idx->qperm = idx->at<uint32_t>(in1 ? L.qv1 : L.qv0);
   idx->have_qperm = true;
   A.qperm = idx->qperm;
+  // the sort's other key buffer is free from here on: 8 bytes per 256 queries
+  // in its 4 bytes per query
+  A.row_sums = idx->at<uint64_t>(in1 ? L.qk0 : L.qk1);
   if (records_ready) EPM_HIP(hipStreamWaitEvent(stream, records_ready, 0));
   const epm_sched& S = idx->sched;
   const bool persistent = S.stab_workgroups > 0 || S.match_workgroups > 0;
@@ -516,16 +521,13 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   if (timed) EPM_HIP(hipEventRecord(idx->ev_start, stream));
   EPM_HIP(launch_stab_tiles(A, S.stab_workgroups, mode, S.stab_chunk, stream));
   if (timed) EPM_HIP(hipEventRecord(idx->ev_stop, stream));
-  if (A.qrec)
-    EPM_HIP(launch_scan_counts(reinterpret_cast<const uint32_t*>(A.qrec), 4, n1, row_offsets,
-                               idx->at<int64_t>(L.partials), stream));
-  else
-    EPM_HIP(launch_scan_counts(A.counts, 1, n1, row_offsets, idx->at<int64_t>(L.partials), stream));
+  EPM_HIP(launch_finish_rows(A, idx->at<int64_t>(L.partials), row_offsets, stream));
   return EPM_OK;
 }
 
-// CSR fill after the scan: parked short rows, brute-force long rows, then the
-// wide-row pass (match: with its FP32 selection, see launch_wide_tiles).
+// The rows that were not parked: brute-force rows and those of tiles that the
+// fused pass leaves, then the wide-row pass (match: with its FP32 selection,
+// see launch_wide_tiles).
 // BF16 copies of the image-2 rows of the pairs with wide tiles, for a
 // matching wide-row pass (A.desc2 set): they go to the staging area, whose
 // parked rows the fill pass has copied out by then, when it holds 256 bytes
@@ -541,9 +543,24 @@ hipError_t prepare_wide_rows(epm_index* idx, StabArgs& A, hipStream_t stream) {
   return launch_round_rows(A, (int64_t)n2, idx->at<int64_t>(idx->L.pre_pairs), stream);
 }
 
+// Reads the counters that the pass over the rows left (waits for the stream):
+// the total of candidates into *nnz_host, and whether a later pass has rows to
+// write or to match.  EPM_ERR_CAPACITY when the rows did not fit.
+epm_status read_totals(const epm_index* idx, const StabArgs& A, int64_t* nnz_host, bool* more,
+                       hipStream_t stream) {
+  unsigned long long c[kNumStats];
+  EPM_HIP(hipMemcpyAsync(c, A.stats, sizeof(c), hipMemcpyDeviceToHost, stream));
+  EPM_HIP(hipStreamSynchronize(stream));
+  *nnz_host = (int64_t)c[kStatNnz];
+  // (timing events around the wide-row kernel have to be recorded)
+  *more = c[kStatLongRows] != 0 || c[kStatRest] != 0 || c[kStatWide] != 0 ||
+          (idx->ev_start && idx->timed == EPM_TIMED_WIDE);
+  return *nnz_host > A.capacity ? EPM_ERR_CAPACITY : EPM_OK;
+}
+
 epm_status enqueue_fill(epm_index* idx, StabArgs& A, hipStream_t stream, bool match = false) {
   if (idx->N1 == 0) return EPM_OK;
-  EPM_HIP(launch_fill_rows(A, stream));
+  EPM_HIP(launch_fill_long(A, stream));
   if (match) EPM_HIP(prepare_wide_rows(idx, A, stream));
   const bool timed = idx->ev_start && idx->timed == EPM_TIMED_WIDE;
   if (timed) EPM_HIP(hipEventRecord(idx->ev_start, stream));
@@ -779,11 +796,9 @@ epm_status enqueue_query_match(epm_index* idx, StabArgs& A, int64_t* row_offsets
   idx->last_offsets = row_offsets;
   idx->have_stats = true;
   if (nnz_host) {
-    int64_t nnz = 0;
-    EPM_HIP(hipMemcpyAsync(&nnz, row_offsets + n1, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-    EPM_HIP(hipStreamSynchronize(stream));
-    *nnz_host = nnz;
-    if (nnz > A.capacity) return EPM_ERR_CAPACITY;
+    bool more = false;
+    const epm_status rs = read_totals(idx, A, nnz_host, &more, stream);
+    if (rs != EPM_OK || !more) return rs;
   }
   const epm_status fs = enqueue_fill(idx, A, stream, true);
   if (fs != EPM_OK) return fs;
@@ -970,12 +985,14 @@ epm_status epm_query_candidates(epm_index* idx, const float* kp1_xy, int64_t* ro
     idx->last_offsets = row_offsets;
     idx->have_stats = true;
   }
+  if (n1 == 0) {
+    if (nnz_host) *nnz_host = 0;
+    return EPM_OK;
+  }
   if (nnz_host) {
-    int64_t nnz = 0;
-    EPM_HIP(hipMemcpyAsync(&nnz, row_offsets + n1, sizeof(int64_t), hipMemcpyDeviceToHost, stream));
-    EPM_HIP(hipStreamSynchronize(stream));
-    *nnz_host = nnz;
-    if (nnz > capacity) return EPM_ERR_CAPACITY;
+    bool more = false;
+    const epm_status rs = read_totals(idx, A, nnz_host, &more, stream);
+    if (rs != EPM_OK || !more) return rs;
   }
   return enqueue_fill(idx, A, stream);
 }

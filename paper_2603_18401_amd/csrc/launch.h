@@ -84,6 +84,7 @@ struct StabArgs {
   const float* reps;
   const uint32_t* rinv;
   uint32_t* counts;
+  uint64_t* row_sums;  // look-back words of launch_finish_rows, cleared by the window pass
   // fused selection: per query (original index) one 16-byte record {row
   // length, best index, best distance, second distance} written in one store
   // (the count is read by the scan from it, the match by the copy pass);
@@ -160,9 +161,10 @@ hipError_t launch_xcd_lpt_order(const uint32_t* cost, int num_tiles, uint32_t* b
 hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s);
 
 // Device-wide counters of a query: the lengths of its two queues (long rows
-// for the fill pass, rows left to the listed-query match).
-constexpr int kStatLongRows = 0, kStatRest = 1;
-constexpr int kNumStats = 2;
+// for the fill pass, rows left to the listed-query match), whether any tile
+// has wide rows, and the total of candidates.
+constexpr int kStatLongRows = 0, kStatRest = 1, kStatWide = 2, kStatNnz = 3;
+constexpr int kNumStats = 4;
 // Clears the kNumStats counters unless stats is NULL, the kSchedWords
 // scheduling words unless sched is NULL and the kMatchStatWords match counters
 // unless match_stats is NULL.
@@ -186,9 +188,16 @@ constexpr int kStabCount = 0, kStabF32 = 1, kStabBF16 = 2, kStabFP8 = 3;
 // BF16 and FP8 passes, 512 for the others).
 hipError_t launch_stab_tiles(const StabArgs& a, int grid, int mode, int chunk, hipStream_t s);
 constexpr int32_t kMatchDeferred = INT32_MIN;
-// Fill pass after launch_stab_tiles: copies parked rows, rebuilds the
-// brute-force long rows.
-hipError_t launch_fill_rows(const StabArgs& a, hipStream_t s);
+// After launch_stab_tiles: row offsets (offsets[n1] and stats[kStatNnz] the
+// total), the fused pass's matches and the parked rows.  a.row_sums:
+// finish_state_words(n1) words, cleared by launch_tile_windows; partials:
+// scan_partials_count(n1) words.
+int64_t finish_state_words(int64_t n1);
+hipError_t launch_finish_rows(const StabArgs& a, int64_t* partials, int64_t* offsets,
+                              hipStream_t s);
+// Rebuilds the rows that launch_finish_rows queued (brute-force queries, rows
+// of tiles that the fused pass leaves).
+hipError_t launch_fill_long(const StabArgs& a, hipStream_t s);
 // Wide-row pass over the tiles flagged in a.tile_wide.
 //   kWideFill:  writes the rows longer than kStage of normal queries (after
 //               the scan of the row lengths);

@@ -25,6 +25,7 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
+constexpr int kFinishRows = 256;  // queries per workgroup of k_finish_rows
 
 // Bitonic sort of one value per lane, ascending over the wavefront.
 __device__ __forceinline__ int32_t wave_sort64(int32_t v) {
@@ -271,6 +272,11 @@ constexpr int kWindowTiles = 4;  // tiles (one wavefront each) per workgroup
 __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs A) {
   const int lane = lane_id();
   const int t = blockIdx.x * kWindowTiles + wave_id();
+  // the look-back words of the pass over the rows (one per 256 queries, a
+  // tile holds at most 64) start from zero
+  for (int64_t k = (int64_t)blockIdx.x * (kWave * kWindowTiles) + threadIdx.x;
+       k < (A.n1 + kFinishRows - 1) / kFinishRows; k += (int64_t)gridDim.x * (kWave * kWindowTiles))
+    A.row_sums[k] = 0ull;
   if (t >= A.num_tiles) return;  // whole wavefronts
   const StabTile T = A.tiles[t];
   bool normal = false, brute = false;
@@ -950,6 +956,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
         atomicAdd(&tile_stats[3], empty);
         if (wm != 0ull) {
           A.tile_wide[tile] = 1u;
+          A.stats[kStatWide] = 1ull;
           if (A.pair_wide) atomicAdd(&A.pair_wide[T.pair], 1u);
         }
       }
@@ -1386,11 +1393,184 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
   }
 }
 
-// Fill pass, part 1: sixteen lanes per query, queries in natural order, copy
-// the parked (already sorted) short rows; short rows marked as not parked and
-// longer rows of brute-force queries are queued for part 2 (long rows of
-// normal queries go to the wide-row pass).
-constexpr int kCopyLanes = 16;
+// The pass after the tiles, in one launch: row offsets, matches and parked
+// rows.  A workgroup owns kFinishRows consecutive queries: it scans their row
+// lengths, publishes their sum, finds the sum of all earlier workgroups by
+// looking back over what those have published, and then writes its offsets,
+// the fused pass's matches (unless a later pass writes them) and the parked
+// (already sorted) short rows.  Short rows marked as not parked and longer
+// rows of brute-force queries are queued for k_fill_long; long rows of normal
+// queries belong to the wide-row pass.
+//
+// A word of row_sums is a sum with a flag in its top bits: of the workgroup
+// alone, or of it and all before it.  Nothing has to be waited for: the row
+// lengths are complete when the launch starts, so a workgroup that finds
+// nothing published after kFinishPolls looks adds up that workgroup's lengths
+// itself.  What bounds it: the latency of its three dependent steps (lengths,
+// look-back, stores), so the first 16 entries of every row are on their way
+// before the look-back; on large batches the staging reads and the CSR.  The
+// separate launches it replaces (partial sums, offsets, matches, rows) took
+// 4.7 + 5.7 + 4.7 + 9.0 us for 120000 queries; this takes 13.9.  Beyond what
+// the chip holds about twice over, the look-back walks over the workgroups
+// that run at the same time in every workgroup, and the separate launches are
+// faster again: whole calls of 84000 / 168000 / 336000 / 672000 queries
+// 145 / 215 / 352 / 652 us with this one, 155 / 222 / 353 / 635 with those.
+constexpr int kCopyLanes = 16;  // lanes per row
+constexpr int kFinishThreads = 1024;
+constexpr int kFinishWaves = kFinishRows / kWave;  // wavefronts that hold a query per lane
+constexpr int kFinishGroups = kFinishThreads / kCopyLanes;
+constexpr int kFinishPer = kFinishRows / kFinishGroups;  // rows per group of lanes
+constexpr int kFinishPolls = 256;
+constexpr int64_t kFinishOneLaunch = 262144;  // queries
+constexpr uint64_t kSumOwn = 1ull << 62, kSumAll = 2ull << 62, kSumMask = (1ull << 62) - 1ull;
+
+__device__ __forceinline__ uint32_t row_length(const StabArgs& A, int64_t i) {
+  return A.qrec ? A.qrec[i].x : A.counts[i];
+}
+
+// Sum of the row lengths before workgroup b, by its first kFinishRows threads
+// (the others take part in the barriers); every thread gets it.
+__device__ __forceinline__ int64_t look_back(const StabArgs& A, int64_t b, int64_t* s_sum,
+                                             int* s_all) {
+  const int lane = lane_id(), wave = wave_id();
+  int64_t before = 0;
+  for (int64_t top = b; top > 0; top -= kFinishRows) {
+    if (wave < kFinishWaves) {
+      const int64_t p = top - 1 - (int64_t)threadIdx.x;
+      uint64_t w = kSumAll;  // before the first workgroup
+      if (p >= 0) {
+        w = __hip_atomic_load(&A.row_sums[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        for (int k = 0; k < kFinishPolls && (w >> 62) == 0; ++k) {
+          __builtin_amdgcn_s_sleep(1);
+          w = __hip_atomic_load(&A.row_sums[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if ((w >> 62) == 0) {
+          w = kSumOwn;
+          for (int k = 0; k < kFinishRows; ++k) w += row_length(A, p * kFinishRows + k);
+        }
+      }
+      // workgroups up to the nearest one with a complete sum
+      const uint64_t all = ballot((w >> 62) == 2);
+      const int last = all != 0ull ? (int)__builtin_ctzll(all) : kWave - 1;
+      int64_t v = lane <= last ? (int64_t)(w & kSumMask) : 0;
+      #pragma unroll
+      for (int off = 1; off < kWave; off <<= 1) v += __shfl_xor(v, off);
+      if (lane == 0) {
+        s_sum[wave] = v;
+        s_all[wave] = all != 0ull;
+      }
+    }
+    __syncthreads();
+    bool done = false;
+    #pragma unroll
+    for (int k = 0; k < kFinishWaves; ++k) {
+      before += done ? 0 : s_sum[k];
+      done |= s_all[k] != 0;
+    }
+    if (done) break;
+    __syncthreads();  // the sums are read before they are written again
+  }
+  return before;
+}
+
+__global__ __launch_bounds__(kFinishThreads) void k_finish_rows(StabArgs A,
+                                                                int64_t* __restrict__ offsets) {
+  __shared__ int64_t s_off[kFinishRows], s_sum[kFinishWaves], s_back[kFinishWaves];
+  __shared__ uint32_t s_len[kFinishRows];
+  __shared__ int s_all[kFinishWaves];
+  static_assert(kCopyLanes <= kStage && kFinishPer <= 32, "first pieces; one bit per row");
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const int64_t b = blockIdx.x, i0 = b * kFinishRows, i = i0 + tid;
+  const bool mine = tid < kFinishRows && i < A.n1;  // this thread's query
+  uint4 rec = make_uint4(0u, (uint32_t)kMatchDeferred, 0u, 0u);
+  if (mine) {
+    if (A.qrec) rec = A.qrec[i];
+    else rec.x = A.counts[i];
+  }
+  // the lengths' exclusive scan
+  int64_t incl = rec.x;
+  if (wave < kFinishWaves) {
+    s_len[tid] = rec.x;
+    #pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+      const int64_t o = __shfl_up(incl, off);
+      if (lane >= off) incl += o;
+    }
+    if (lane == kWave - 1) s_sum[wave] = incl;
+  }
+  __syncthreads();
+  // the rows' first pieces; its first word tells whether a row was parked
+  const int grp = tid / kCopyLanes, sub = tid % kCopyLanes;
+  int32_t v[kFinishPer];
+  #pragma unroll
+  for (int u = 0; u < kFinishPer; ++u) {
+    const int row = u * kFinishGroups + grp;
+    const uint32_t len = s_len[row];
+    v[u] = (uint32_t)sub < len && len <= (uint32_t)kStage ? A.staging[(i0 + row) * kStage + sub] : 0;
+  }
+  int64_t total = 0;
+  #pragma unroll
+  for (int k = 0; k < kFinishWaves; ++k) {
+    incl += k < wave ? s_sum[k] : 0;
+    total += s_sum[k];
+  }
+  if (tid == 0)
+    __hip_atomic_store(&A.row_sums[b], (b == 0 ? kSumAll : kSumOwn) | (uint64_t)total, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  if (wave < kFinishWaves) s_off[tid] = incl - rec.x;
+  const int64_t before = look_back(A, b, s_back, s_all);
+  if (b == 0) __syncthreads();  // s_off is complete (look_back has a barrier otherwise)
+  if (tid == 0 && b > 0)
+    __hip_atomic_store(&A.row_sums[b], kSumAll | (uint64_t)(before + total), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  if (mine) offsets[i] = before + s_off[tid];
+  if (b == (int64_t)gridDim.x - 1 && tid == 0) {
+    offsets[A.n1] = before + total;
+    A.stats[kStatNnz] = (unsigned long long)(before + total);
+  }
+  if (mine && (int32_t)rec.y != kMatchDeferred) {
+    A.best_idx[i] = (int32_t)rec.y;
+    A.best_dist[i] = __uint_as_float(rec.z);
+    A.second_dist[i] = __uint_as_float(rec.w);
+  }
+  uint32_t parked = 0u;  // bit u: the row's pieces are copied
+  uint32_t longest = 0u;
+  #pragma unroll
+  for (int u = 0; u < kFinishPer; ++u) {
+    const int row = u * kFinishGroups + grp;
+    const uint32_t len = s_len[row];
+    const int32_t first = __shfl(v[u], 0, kCopyLanes);
+    if (len == 0) continue;
+    if (len <= (uint32_t)kStage && first != kRowNotParked) {
+      const int64_t dst = before + s_off[row] + sub;
+      if ((uint32_t)sub < len && dst < A.capacity) A.cols[dst] = v[u];
+      parked |= 1u << u;
+      longest = len > longest ? len : longest;
+    } else if (sub == 0 &&
+               (len <= (uint32_t)kStage || A.qflag[i0 + row] != kQueryNormal)) {
+      const unsigned long long slot = atomicAdd(&A.stats[kStatLongRows], 1ull);
+      A.long_rows[slot] = (uint32_t)(i0 + row);
+    }
+  }
+  for (uint32_t k0 = kCopyLanes; k0 < longest; k0 += kCopyLanes) {
+    const uint32_t k = k0 + sub;
+    #pragma unroll
+    for (int u = 0; u < kFinishPer; ++u) {
+      const int row = u * kFinishGroups + grp;
+      const bool take = ((parked >> u) & 1u) != 0u && k < s_len[row];
+      v[u] = take ? A.staging[(i0 + row) * kStage + k] : 0;
+    }
+    #pragma unroll
+    for (int u = 0; u < kFinishPer; ++u) {
+      const int row = u * kFinishGroups + grp;
+      const int64_t dst = before + s_off[row] + k;
+      if (((parked >> u) & 1u) != 0u && k < s_len[row] && dst < A.capacity) A.cols[dst] = v[u];
+    }
+  }
+}
+
+// The same over several launches, for more than kFinishOneLaunch queries: the
+// scan of the row lengths, the matches, and the rows, sixteen lanes per query.
 constexpr int kCopyQueries = kThreads / kCopyLanes;
 constexpr int kCopyUnroll = 4;  // rows per group
 __global__ __launch_bounds__(kThreads) void k_copy_rows(StabArgs A) {
@@ -1399,6 +1579,8 @@ __global__ __launch_bounds__(kThreads) void k_copy_rows(StabArgs A) {
   // kCopyUnroll consecutive rows per group of kCopyLanes, their loads in flight together
   const int64_t i0 =
       ((int64_t)blockIdx.x * kCopyQueries + (threadIdx.x / kCopyLanes)) * kCopyUnroll;
+  if (blockIdx.x == 0 && threadIdx.x == 0)
+    A.stats[kStatNnz] = (unsigned long long)A.row_offsets[A.n1];
   if (i0 >= A.n1) return;  // whole groups of kCopyLanes leave together
   // each slot's first piece is read beside the row offsets (before the row's
   // length is known); its first word tells whether the row was parked
@@ -1444,7 +1626,7 @@ __global__ __launch_bounds__(kThreads) void k_write_matches(StabArgs A) {
   A.second_dist[i] = __uint_as_float(r.w);
 }
 
-// Fill pass, part 2: rebuilds the queued long rows (grid-stride over the
+// Rebuilds the queued rows (grid-stride over the
 // queue, whose length only the device knows).
 __global__ __launch_bounds__(kThreads) void k_fill_long(StabArgs A) {
   __shared__ int32_t rowbuf[kWaves][kRowSortMax];
@@ -1632,15 +1814,9 @@ hipError_t launch_stab_tiles(const StabArgs& a, int grid, int mode, int chunk, h
   }
 }
 
-hipError_t launch_fill_rows(const StabArgs& a, hipStream_t s) {
+hipError_t launch_fill_long(const StabArgs& a, hipStream_t s) {
   if (a.n1 == 0) return hipSuccess;
   const int64_t blocks = (a.n1 + kWaves - 1) / kWaves;
-  const int64_t rows_per_block = (int64_t)kCopyQueries * kCopyUnroll;
-  const int64_t cblocks = (a.n1 + rows_per_block - 1) / rows_per_block;
-  if (a.qrec)
-    hipLaunchKernelGGL(k_write_matches, dim3((unsigned)((a.n1 + kThreads - 1) / kThreads)),
-                       dim3(kThreads), 0, s, a);
-  hipLaunchKernelGGL(k_copy_rows, dim3((unsigned)cblocks), dim3(kThreads), 0, s, a);
   // long rows are few and each is latency-bound: up to 2048 workgroups
   // (8192 wavefronts) take them from the queue
   const int64_t lblocks = blocks < 2048 ? blocks : 2048;
@@ -1667,6 +1843,32 @@ hipError_t launch_scan_counts(const uint32_t* counts, int stride, int64_t n, int
   hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(kScanThreads), 0, s, partials, nb);
   hipLaunchKernelGGL(k_scan_final, dim3((unsigned)nb), dim3(kScanThreads), 0, s, counts, stride,
                      n, partials, nb, offsets);
+  return hipGetLastError();
+}
+
+int64_t finish_state_words(int64_t n1) { return (n1 + kFinishRows - 1) / kFinishRows; }
+
+hipError_t launch_finish_rows(const StabArgs& a, int64_t* partials, int64_t* offsets,
+                              hipStream_t s) {
+  if (a.n1 == 0) return hipSuccess;
+  if (!a.row_sums || !partials || !offsets || !a.stats || !a.staging || (a.capacity > 0 && !a.cols))
+    return hipErrorInvalidValue;
+  if (a.n1 <= kFinishOneLaunch) {
+    hipLaunchKernelGGL(k_finish_rows, dim3((unsigned)finish_state_words(a.n1)),
+                       dim3(kFinishThreads), 0, s, a, offsets);
+    return hipGetLastError();
+  }
+  const hipError_t e =
+      a.qrec ? launch_scan_counts(reinterpret_cast<const uint32_t*>(a.qrec), 4, a.n1, offsets,
+                                  partials, s)
+             : launch_scan_counts(a.counts, 1, a.n1, offsets, partials, s);
+  if (e != hipSuccess) return e;
+  if (a.qrec)
+    hipLaunchKernelGGL(k_write_matches, dim3((unsigned)((a.n1 + kThreads - 1) / kThreads)),
+                       dim3(kThreads), 0, s, a);
+  const int64_t rows_per_block = (int64_t)kCopyQueries * kCopyUnroll;
+  hipLaunchKernelGGL(k_copy_rows, dim3((unsigned)((a.n1 + rows_per_block - 1) / rows_per_block)),
+                     dim3(kThreads), 0, s, a);
   return hipGetLastError();
 }
 
