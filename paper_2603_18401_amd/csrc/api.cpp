@@ -24,16 +24,26 @@ size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
 // Offsets of every device buffer inside the caller's workspace.
 struct Layout {
-  size_t pairs, qstart, kstart, rsegs, qsegs, stile_begin, head_end, rtiles, qtiles, stiles, hist,
-      qhist;
-  size_t rk0, rv0, rk1, rv1, recC, recH, rC, rH, rj, rxy, reps, rinv, class_begin;
-  size_t qkey, qflag, qk0, qv0, qk1, qv1, counts, qrec, partials, staging, stats, long_rows;
-  size_t digit_base, windows, match_stats, sched, tile_cost, order, block_tile, rest, tile_wide,
+  size_t pairs, qstart, kstart, rsegs, qsegs, stile_begin, head_end, rtiles, qtiles, stiles;
+  size_t rk0, rk1, rv1, rhist0, rhist1, recC, recH, rC, rH, rj, rxy, reps, rinv, class_begin;
+  size_t qkey, qflag, qk0, qk1, qv1, qhist0, qhist1, counts, qrec, partials, staging, stats,
+      long_rows;
+  size_t windows, match_stats, sched, tile_cost, order, block_tile, rest, tile_wide,
       pair_wide, pre_pairs, qline, tile_q, tile_counts;
   size_t total;
 };
 
-Layout make_layout(int P, int64_t n1, int64_t n2, int64_t tr, int64_t tq, int64_t ts) {
+// Tiles of a batch: elements per sort tile, tiles and rows of digit counts of
+// the record (r) and the query (q) sort, and the stabbing tiles.
+struct Tiles {
+  int rsize = kSortTileMin, qsize = kSortTileMin;
+  int64_t r = 0, q = 0, rrows = 0, qrows = 0, stab = 0;
+  // queries by all bits of their codes: tiles of larger segments
+  bool q_two_passes() const { return qsize > kSortTileMin; }
+};
+
+Layout make_layout(int P, int64_t n1, int64_t n2, const Tiles& T) {
+  const int64_t tr = T.r, tq = T.q, ts = T.stab;
   Layout L;
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -54,36 +64,41 @@ Layout make_layout(int P, int64_t n1, int64_t n2, int64_t tr, int64_t tq, int64_
   L.rtiles = take(sizeof(SortTile) * tr);
   L.qtiles = take(sizeof(SortTile) * tq);
   L.stiles = take(sizeof(StabTile) * ts);
-  // per-tile digit counts of every pass of the record (3) and of the query
-  // (2) sort: separate, so that the two sorts may run side by side
-  L.hist = take(sizeof(uint32_t) * 256 * (size_t)sort_passes(kSortBits) * (size_t)tr);
-  L.qhist = take(sizeof(uint32_t) * 256 * (size_t)sort_passes(kQuerySortBits) * (size_t)tq);
   L.rk0 = take(4 * N2);
-  L.rv0 = take(4 * N2);
   L.rk1 = take(4 * N2);
   L.rv1 = take(4 * N2);
+  const size_t rrow_bytes = sizeof(uint32_t) * kHistWords * (size_t)T.rrows;
+  L.rhist1 = take(rrow_bytes);
   L.recC = take(4 * N2);
   L.recH = take(4 * N2);
+  // the first pass's counts are dead when the second pass writes the records
+  // (at most 8 bytes per record of a segment with rows, in 28)
+  L.rhist0 = off;
   L.rC = take(4 * N2);
   L.rH = take(4 * N2);
   L.rj = take(4 * N2);
   L.rxy = take(8 * N2);
   L.reps = take(4 * N2);
   L.rinv = take(4 * N2);
+  if (off - L.rhist0 < rrow_bytes) off = L.rhist0 + align_up(rrow_bytes);
   L.class_begin = take(sizeof(int64_t) * kClassSlots * P);
   L.qkey = take(4 * N1);
   L.qflag = take(4 * N1);
   L.qk0 = take(4 * N1);
-  L.qv0 = take(4 * N1);
   L.qk1 = take(4 * N1);
   L.qv1 = take(4 * N1);
   L.counts = take(4 * N1);
   L.qrec = take(16 * N1);
   L.partials = take(sizeof(int64_t) * (size_t)scan_partials_count(n1));
-  L.staging = take(sizeof(int32_t) * kStage * N1);
+  // before the stabbing pass parks rows there, the staging area holds the
+  // digit counts of the query sort
+  const size_t qrow_bytes = sizeof(uint32_t) * kHistWords * (size_t)T.qrows;
+  const size_t staging = sizeof(int32_t) * kStage * N1;
+  L.staging = take(staging > 2 * qrow_bytes ? staging : 2 * qrow_bytes);
+  L.qhist0 = L.staging;
+  L.qhist1 = L.staging + qrow_bytes;
   L.stats = take(sizeof(unsigned long long) * kNumStats);
   L.long_rows = take(sizeof(uint32_t) * N1);
-  L.digit_base = take(sizeof(uint32_t) * 256 * P);
   L.windows = take(sizeof(TileWindow) * ts);
   L.match_stats = take(sizeof(unsigned long long) * kMatchStatWords);
   L.sched = take(sizeof(uint32_t) * kSchedWords);
@@ -101,14 +116,28 @@ Layout make_layout(int P, int64_t n1, int64_t n2, int64_t tr, int64_t tq, int64_
   return L;
 }
 
-int64_t tiles_of(int64_t count) { return (count + kSortTile - 1) / kSortTile; }
-
-int max_tiles(const std::vector<SortSeg>& segs) {
-  int m = 0;
-  for (const SortSeg& g : segs) m = g.tile_count > m ? g.tile_count : m;
-  return m;
-}
 int64_t stab_tiles_of(int64_t m) { return (m + kTileQ - 1) / kTileQ; }
+
+// The tiles of a validated batch.
+Tiles tiles_of(const epm_pair* pairs, int P) {
+  Tiles T;
+  int64_t mmax = 0, nmax = 0;
+  for (int p = 0; p < P; ++p) {
+    mmax = pairs[p].m > mmax ? pairs[p].m : mmax;
+    nmax = pairs[p].n > nmax ? pairs[p].n : nmax;
+  }
+  T.rsize = sort_tile_size(nmax);
+  T.qsize = sort_tile_size(mmax);
+  for (int p = 0; p < P; ++p) {
+    const int64_t r = (pairs[p].n + T.rsize - 1) / T.rsize, q = (pairs[p].m + T.qsize - 1) / T.qsize;
+    T.r += r;
+    T.q += q;
+    T.rrows += r > 1 ? r : 0;
+    T.qrows += q > 1 ? q : 0;
+    T.stab += stab_tiles_of(pairs[p].m);
+  }
+  return T;
+}
 
 bool validate_pairs(const epm_pair* pairs, int32_t num_pairs, int64_t* n1, int64_t* n2) {
   if (!pairs || num_pairs < 1 || num_pairs > 65535) return false;
@@ -210,6 +239,7 @@ epm_status setup_pair(const epm_pair& in, PairDev& pd) {
   pd.G22 = pd.v[0] * pd.v[0] + pd.v[1] * pd.v[1];
   pd.e12 = std::sqrt(pd.e[0] * pd.e[0] + pd.e[1] * pd.e[1]);
   pd.kappa = kKappaBuild;
+  set_key_arc(pd);
   pd.q_begin = in.q_begin;
   pd.m = in.m;
   pd.k_begin = in.k_begin;
@@ -217,19 +247,23 @@ epm_status setup_pair(const epm_pair& in, PairDev& pd) {
   return EPM_OK;
 }
 
-// The sort segments of `starts` and their tiles; the total of tiles.  (The
-// tile lists themselves are made on the device, from the segments.)
-int64_t make_segs(const std::vector<int64_t>& starts, int P, std::vector<SortSeg>& segs) {
+// The sort segments of `starts`, `size` elements per tile.  (The tile lists
+// themselves are made on the device, from the segments.)
+void make_segs(const std::vector<int64_t>& starts, int P, int size, std::vector<SortSeg>& segs) {
   segs.resize(P);
-  int64_t tiles = 0;
+  int64_t tiles = 0, rows = 0;
   for (int p = 0; p < P; ++p) {
+    const int64_t count = starts[p + 1] - starts[p];
+    const int64_t t = (count + size - 1) / size;
     segs[p].begin = starts[p];
-    segs[p].count = starts[p + 1] - starts[p];
+    segs[p].count = count;
     segs[p].tile_begin = (int32_t)tiles;
-    segs[p].tile_count = (int32_t)tiles_of(segs[p].count);
-    tiles += segs[p].tile_count;
+    segs[p].tile_count = (int32_t)t;
+    segs[p].hist_begin = (int32_t)rows;
+    segs[p].pad = 0;
+    tiles += t;
+    rows += t > 1 ? t : 0;
   }
-  return tiles;
 }
 
 }  // namespace
@@ -241,13 +275,12 @@ struct epm_index {
   std::vector<int32_t> stile_begin;  // first stabbing tile of every pair, and the total
   std::vector<int64_t> qstart, kstart;
   std::vector<SortSeg> rsegs, qsegs;
-  int64_t rtiles = 0, qtiles = 0, stiles = 0;  // tiles of the two sorts and of the stabbing pass
+  Tiles tiles;
   std::vector<char> head;  // host image of the table region of the workspace
   char* ws = nullptr;
   Layout L;
-  size_t skey_off = 0;  // sorted record keys (one of the sort buffers)
   bool have_qperm = false;
-  const uint32_t* qperm = nullptr;
+  uint32_t* qperm = nullptr;
   hipStream_t last_stream = nullptr;  // stream of the last query call
   const int64_t* last_offsets = nullptr;
   bool have_stats = false;
@@ -304,22 +337,14 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   }
   idx->qstart[num_pairs] = n1;
   idx->kstart[num_pairs] = n2;
-  idx->rtiles = make_segs(idx->kstart, num_pairs, idx->rsegs);
-  idx->qtiles = make_segs(idx->qstart, num_pairs, idx->qsegs);
-  for (int p = 0; p < num_pairs; ++p) {
-    PairDev& pd = idx->pairs[p];
-    pd.rtile_begin = idx->rsegs[p].tile_begin;
-    pd.rtile_count = idx->rsegs[p].tile_count;
-    pd.qtile_begin = idx->qsegs[p].tile_begin;
-    pd.qtile_count = idx->qsegs[p].tile_count;
-  }
+  idx->tiles = tiles_of(pairs, num_pairs);
+  make_segs(idx->kstart, num_pairs, idx->tiles.rsize, idx->rsegs);
+  make_segs(idx->qstart, num_pairs, idx->tiles.qsize, idx->qsegs);
   idx->stile_begin.resize(num_pairs + 1);
-  for (int p = 0; p < num_pairs; ++p) {
-    idx->stile_begin[p] = (int32_t)idx->stiles;
-    idx->stiles += stab_tiles_of(pairs[p].m);
-  }
-  idx->stile_begin[num_pairs] = (int32_t)idx->stiles;
-  idx->L = make_layout(num_pairs, n1, n2, idx->rtiles, idx->qtiles, idx->stiles);
+  idx->stile_begin[0] = 0;
+  for (int p = 0; p < num_pairs; ++p)
+    idx->stile_begin[p + 1] = idx->stile_begin[p] + (int32_t)stab_tiles_of(pairs[p].m);
+  idx->L = make_layout(num_pairs, n1, n2, idx->tiles);
   if (workspace_bytes < idx->L.total) {
     delete idx;
     return EPM_ERR_WORKSPACE;
@@ -345,11 +370,12 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
 // The tile lists, from the uploaded tables (after their upload on `stream`).
 hipError_t expand_tiles(const epm_index* idx, hipStream_t stream) {
   const Layout& L = idx->L;
+  const Tiles& T = idx->tiles;
   return launch_expand_tiles(idx->at<SortSeg>(L.rsegs), idx->at<SortSeg>(L.qsegs),
                              idx->at<int64_t>(L.qstart), idx->at<int32_t>(L.stile_begin), idx->P,
-                             idx->at<SortTile>(L.rtiles), idx->rtiles,
-                             idx->at<SortTile>(L.qtiles), idx->qtiles,
-                             idx->at<StabTile>(L.stiles), idx->stiles, stream);
+                             idx->at<SortTile>(L.rtiles), T.r, T.rsize,
+                             idx->at<SortTile>(L.qtiles), T.q, T.qsize,
+                             idx->at<StabTile>(L.stiles), T.stab, stream);
 }
 
 epm_status index_upload(epm_index* idx, hipStream_t stream) {
@@ -372,30 +398,36 @@ epm_status enqueue_build(epm_index* idx, const float* kp2_xy, const float* eps2,
   const int P = idx->P;
   const int64_t n2 = idx->N2;
   const PairDev* dpairs = idx->at<PairDev>(L.pairs);
-  const int64_t* dkstart = idx->at<int64_t>(L.kstart);
-  EPM_HIP(launch_intervals(dpairs, idx->at<SortTile>(L.rtiles), (int)idx->rtiles, kp2_xy,
-                           eps2, eps_scalar, idx->at<uint32_t>(L.rk0), idx->at<uint32_t>(L.rv0),
-                           idx->at<uint32_t>(L.recC), idx->at<uint32_t>(L.recH),
-                           idx->at<uint32_t>(L.hist), sort_passes(kSortBits) - 1, stream));
-  bool in1 = false;
-  EPM_HIP(segmented_radix_sort(idx->at<uint32_t>(L.rk0), idx->at<uint32_t>(L.rv0),
-                               idx->at<uint32_t>(L.rk1), idx->at<uint32_t>(L.rv1),
-                               idx->at<SortTile>(L.rtiles), (int)idx->rtiles,
-                               idx->at<SortSeg>(L.rsegs), P, max_tiles(idx->rsegs),
-                               idx->at<uint32_t>(L.hist), kSortBits, &in1, stream,
-                               idx->at<uint32_t>(L.digit_base), true));
-  const uint32_t* skey = idx->at<uint32_t>(in1 ? L.rk1 : L.rk0);
-  const uint32_t* sval = idx->at<uint32_t>(in1 ? L.rv1 : L.rv0);
-  EPM_HIP(launch_gather_records(dkstart, P, n2, sval, kp2_xy, eps2, eps_scalar,
-                                idx->at<uint32_t>(L.recC), idx->at<uint32_t>(L.recH),
-                                idx->at<uint32_t>(L.rC), idx->at<uint32_t>(L.rH),
-                                idx->at<int32_t>(L.rj), idx->at<float2>(L.rxy),
-                                idx->at<float>(L.reps), idx->at<uint32_t>(L.rinv),
-                                idx->at<uint32_t>(L.digit_base), idx->at<int64_t>(L.class_begin),
-                                stream));
-  idx->skey_off = in1 ? L.rk1 : L.rk0;
-  // with keypoints the gather wrote the class starts
-  if (n2 == 0) EPM_HIP(launch_class_bounds(dkstart, P, skey, idx->at<int64_t>(L.class_begin), stream));
+  SortCall c;
+  c.tiles = idx->at<SortTile>(L.rtiles);
+  c.num_tiles = idx->tiles.r;
+  c.rows = idx->tiles.rrows;
+  c.segs = idx->at<SortSeg>(L.rsegs);
+  c.num_segs = P;
+  c.k0 = idx->at<uint32_t>(L.rk0);
+  c.k1 = idx->at<uint32_t>(L.rk1);
+  c.v1 = idx->at<uint32_t>(L.rv1);
+  c.hist0 = idx->at<uint32_t>(L.rhist0);
+  c.hist1 = idx->at<uint32_t>(L.rhist1);
+  RecordSort r;
+  r.kp2 = kp2_xy;
+  r.eps2 = eps2;
+  r.eps_scalar = eps_scalar;
+  r.recC = idx->at<uint32_t>(L.recC);
+  r.recH = idx->at<uint32_t>(L.recH);
+  r.rC = idx->at<uint32_t>(L.rC);
+  r.rH = idx->at<uint32_t>(L.rH);
+  r.rj = idx->at<int32_t>(L.rj);
+  r.rxy = idx->at<float2>(L.rxy);
+  r.reps = idx->at<float>(L.reps);
+  r.rinv = idx->at<uint32_t>(L.rinv);
+  r.class_begin = idx->at<int64_t>(L.class_begin);
+  EPM_HIP(launch_intervals(dpairs, c, kp2_xy, eps2, eps_scalar, idx->at<uint32_t>(L.recC),
+                           idx->at<uint32_t>(L.recH), stream));
+  EPM_HIP(sort_records(c, r, stream));
+  // with keypoints the sort wrote the class starts
+  if (n2 == 0)
+    EPM_HIP(launch_class_bounds(idx->at<int64_t>(L.kstart), P, c.k0, r.class_begin, stream));
   return EPM_OK;
 }
 
@@ -412,7 +444,7 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.qflag = idx->at<uint32_t>(L.qflag);
   A.qperm = nullptr;
   A.class_begin = idx->at<int64_t>(L.class_begin);
-  A.skey = idx->at<uint32_t>(idx->skey_off);
+  A.skey = idx->at<uint32_t>(L.rk0);
   A.rC = idx->at<uint32_t>(L.rC);
   A.rH = idx->at<uint32_t>(L.rH);
   A.rj = idx->at<int32_t>(L.rj);
@@ -426,7 +458,7 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.cols = col_indices;
   A.capacity = capacity;
   A.tiles = idx->at<StabTile>(L.stiles);
-  A.num_tiles = (int)idx->stiles;
+  A.num_tiles = (int)idx->tiles.stab;
   A.staging = idx->at<int32_t>(L.staging);
   A.stats = idx->at<unsigned long long>(L.stats);
   A.long_rows = idx->at<uint32_t>(L.long_rows);
@@ -476,24 +508,28 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
     if (A.match_stats) EPM_HIP(launch_clear_stats(nullptr, stream, nullptr, A.match_stats));
     return EPM_OK;
   }
-  EPM_HIP(launch_query_keys(A.pairs, idx->at<SortTile>(L.qtiles), (int)idx->qtiles,
-                            A.kp1, idx->at<uint32_t>(L.qkey), idx->at<uint32_t>(L.qflag),
-                            idx->at<uint32_t>(L.qk0), idx->at<uint32_t>(L.qv0), A.qline,
-                            idx->at<uint32_t>(L.qhist), sort_passes(kQuerySortBits) - 1, A.stats,
-                            idx->at<uint32_t>(L.sched), A.match_stats, stream));
-  bool in1 = false;
-  EPM_HIP(segmented_radix_sort(idx->at<uint32_t>(L.qk0), idx->at<uint32_t>(L.qv0),
-                               idx->at<uint32_t>(L.qk1), idx->at<uint32_t>(L.qv1),
-                               idx->at<SortTile>(L.qtiles), (int)idx->qtiles,
-                               idx->at<SortSeg>(L.qsegs), idx->P, max_tiles(idx->qsegs),
-                               idx->at<uint32_t>(L.qhist), kQuerySortBits, &in1, stream, nullptr,
-                               true));
-  idx->qperm = idx->at<uint32_t>(in1 ? L.qv1 : L.qv0);
+  const bool two = idx->tiles.q_two_passes();
+  SortCall c;
+  c.tiles = idx->at<SortTile>(L.qtiles);
+  c.num_tiles = idx->tiles.q;
+  c.rows = idx->tiles.qrows;
+  c.segs = idx->at<SortSeg>(L.qsegs);
+  c.num_segs = idx->P;
+  c.k0 = idx->at<uint32_t>(L.qk0);
+  c.k1 = idx->at<uint32_t>(L.qk1);
+  c.v1 = idx->at<uint32_t>(L.qv1);
+  c.hist0 = idx->at<uint32_t>(L.qhist0);
+  c.hist1 = idx->at<uint32_t>(L.qhist1);
+  // one pass leaves the keys' buffer free afterwards, two passes the other
+  idx->qperm = two ? c.k0 : c.v1;
   idx->have_qperm = true;
+  EPM_HIP(launch_query_keys(A.pairs, c, two, A.kp1, idx->at<uint32_t>(L.qkey),
+                            idx->at<uint32_t>(L.qflag), A.qline, A.stats,
+                            idx->at<uint32_t>(L.sched), A.match_stats, stream));
+  EPM_HIP(sort_queries(c, two, idx->qperm, stream));
   A.qperm = idx->qperm;
-  // the sort's other key buffer is free from here on: 8 bytes per 256 queries
-  // in its 4 bytes per query
-  A.row_sums = idx->at<uint64_t>(in1 ? L.qk0 : L.qk1);
+  // 8 bytes per 256 queries in 4 bytes per query
+  A.row_sums = reinterpret_cast<uint64_t*>(two ? c.k1 : c.k0);
   if (records_ready) EPM_HIP(hipStreamWaitEvent(stream, records_ready, 0));
   const epm_sched& S = idx->sched;
   const bool persistent = S.stab_workgroups > 0 || S.match_workgroups > 0;
@@ -635,7 +671,7 @@ MatchArgs match_args(epm_index* idx, const MatchCall& c) {
   A.best_dist = c.best_dist;
   A.second_dist = c.second_dist;
   A.tiles = idx->at<StabTile>(L.stiles);
-  A.num_tiles = (int)idx->stiles;
+  A.num_tiles = (int)idx->tiles.stab;
   A.windows = idx->at<TileWindow>(L.windows);
   A.rinv = idx->at<uint32_t>(L.rinv);
   A.rj = idx->at<int32_t>(L.rj);
@@ -915,13 +951,7 @@ extern "C" {
 size_t epm_workspace_bytes(const epm_pair* pairs, int32_t num_pairs) {
   int64_t n1, n2;
   if (!validate_pairs(pairs, num_pairs, &n1, &n2)) return 0;
-  int64_t tr = 0, tq = 0, ts = 0;
-  for (int p = 0; p < num_pairs; ++p) {
-    tr += tiles_of(pairs[p].n);
-    tq += tiles_of(pairs[p].m);
-    ts += stab_tiles_of(pairs[p].m);
-  }
-  return make_layout(num_pairs, n1, n2, tr, tq, ts).total;
+  return make_layout(num_pairs, n1, n2, tiles_of(pairs, num_pairs)).total;
 }
 
 epm_status epm_build_intervals(const epm_pair* pairs, int32_t num_pairs, const float* kp2_xy,
@@ -1144,13 +1174,8 @@ epm_status epm_query_match_noalloc(const epm_pair* pairs, int32_t num_pairs, con
   if (capacity > 0 && !col_indices) return EPM_ERR_ARG;
   {
     // the size limit is a host check: nothing runs when it fails
-    int64_t tr = 0, tq = 0, ts = 0;
-    for (int p = 0; p < num_pairs; ++p) {
-      tr += tiles_of(pairs[p].n);
-      tq += tiles_of(pairs[p].m);
-      ts += stab_tiles_of(pairs[p].m);
-    }
-    if (make_layout(num_pairs, n1, n2, tr, tq, ts).total > (size_t)EPM_NOALLOC_SCRATCH_BYTES)
+    if (make_layout(num_pairs, n1, n2, tiles_of(pairs, num_pairs)).total >
+        (size_t)EPM_NOALLOC_SCRATCH_BYTES)
       return EPM_ERR_WORKSPACE;
   }
   MatchCall c;
@@ -1714,7 +1739,7 @@ epm_status epm_get_query_stats(const epm_index* idx, epm_query_stats* out) {
   out->queries = idx->N1;
   if (!idx->have_stats) return EPM_OK;
   // the tile pass leaves its counters per tile: summed here
-  const size_t nt = (size_t)idx->stiles;
+  const size_t nt = (size_t)idx->tiles.stab;
   std::vector<unsigned long long> tc((size_t)kTileCounts * nt);
   int64_t nnz = 0;
   if (nt > 0)
@@ -1745,7 +1770,7 @@ epm_status epm_get_match_stats(const epm_index* idx, epm_match_stats* out) {
                          sizeof(unsigned long long) * kNumMatchStats, hipMemcpyDeviceToHost,
                          idx->match_stream));
   // a match fused into the tile pass leaves its BF16 counters per tile
-  const size_t nt = idx->match_from_tiles ? (size_t)idx->stiles : 0;
+  const size_t nt = idx->match_from_tiles ? (size_t)idx->tiles.stab : 0;
   std::vector<unsigned long long> tc((size_t)kTileCounts * nt);
   if (nt > 0)
     EPM_HIP(hipMemcpyAsync(tc.data(), idx->at<unsigned long long>(idx->L.tile_counts),

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 namespace epm {
@@ -18,18 +19,25 @@ constexpr uint32_t kGuard = 4;
 // interval of a circle that contains the epipole (Sec. 4.4).
 constexpr uint32_t kFullHalf = 0x80000000u;
 
-// Records are sorted by (width class, top bits of the centre key).  Class c
+// Keys of a pair are angles minus the pair's cut, the middle of the gap that
+// the lines through the epipole leave beside image 2 (a far epipole sees the
+// image under a small angle); differences of keys do not notice.  The
+// position code of a key places it in the arc between (arc_off, arc_len) with
+// kCentreBits bits; keys outside the arc take the code of its nearer end.
+// The code never decreases with the key, so windows of keys are windows of
+// codes, whatever the arc is.
+//
+// Records are sorted by (width class, position code of the centre).  Class c
 // holds half-widths H with 2^(c-1) <= H < 2^c, so a query at key P only has
 // to scan class-c centres in [P - 2^c + 1, P + 2^c - 1]; class 31 holds every
 // half-width >= 2^30 and is scanned whole.
 constexpr int kClassBits = 5;
 constexpr int kNumClasses = 32;
-constexpr int kCentreBits = 19;
-constexpr int kCentreShift = 32 - kCentreBits;  // centre key >> 13
-constexpr int kSortBits = kClassBits + kCentreBits;  // 24 -> three 8-bit passes
+constexpr int kCentreBits = 17;
+constexpr int kRadixBits = 11;  // bits per pass of the sort
+constexpr int kSortBits = kClassBits + kCentreBits;  // two passes
 constexpr int kWideClass = 31;
-// Queries are sorted by the top 16 bits of their key (two 8-bit passes).
-constexpr int kQuerySortBits = 16;
+static_assert(kSortBits == 2 * kRadixBits, "the records take two passes");
 
 // Query flags.
 constexpr uint32_t kQueryNormal = 0;
@@ -52,10 +60,75 @@ struct PairDev {
   double G11, G12, G22; // Gram matrix of (u_12, v_12)
   double e12;           // |e_12|
   double kappa;         // miss bound absorbed by the record intervals
+  uint64_t arc_mul;     // position code of a key: (key - arc_off) * arc_mul >> 32
+  uint32_t cut, arc_off, arc_len, arc_pad;
   int64_t q_begin, m, k_begin, n;
-  int32_t qtile_begin, qtile_count;  // query sort tiles
-  int32_t rtile_begin, rtile_count;  // record sort tiles
 };
+
+// Angle key of a pencil line at phi: phi reduced to [0, pi), in key units.
+__host__ __device__ inline uint32_t angle_key(double phi) {
+  if (phi < 0.0) phi += M_PI;
+  if (phi >= M_PI) phi -= M_PI;
+  return (uint32_t)(uint64_t)(int64_t)nearbyint(phi * kKeyPerRad);
+}
+
+// The pair's arc of keys: those of the pencil lines that meet image 2, a
+// little wider on both sides; the whole circle when the epipole lies in the
+// image or close to it, or the pair has no pencil.  (Only the resolution of
+// the position codes depends on it.)
+__host__ __device__ inline void set_key_arc(PairDev& pd) {
+  pd.cut = pd.arc_off = pd.arc_pad = 0u;
+  pd.arc_len = 0xFFFFFFFFu;
+  pd.arc_mul = 1ull << kCentreBits;
+  if (pd.kappa < 0.0) return;
+  // d = e_w p - (e_x, e_y) is the direction from the epipole to the point p
+  // (normalised coordinates, centre 0; up to a common sign).  While the four
+  // corners lie ahead of the epipole as it looks at the centre, the lines
+  // through them are ordered by cross(d0, p) / dot(d0, d), also for an
+  // epipole at infinity.
+  const double dx0 = -pd.e[0], dy0 = -pd.e[1];
+  const double hx = pd.s * pd.cx, hy = pd.s * pd.cy;
+  const uint32_t kc = angle_key(atan2(pd.u[2], -pd.v[2]));  // the line through the centre
+  double tmin = 0.0, tmax = 0.0;
+  uint32_t kmin = kc, kmax = kc;
+  for (int k = 0; k < 4; ++k) {
+    const double x = k & 1 ? hx : -hx, y = k & 2 ? hy : -hy;
+    const double ahead = dx0 * (pd.e[2] * x + dx0) + dy0 * (pd.e[2] * y + dy0);
+    if (!(ahead > 1e-3 * (dx0 * dx0 + dy0 * dy0))) return;
+    const double t = (dx0 * y - dy0 * x) / ahead;
+    const uint32_t key = angle_key(atan2(pd.u[0] * x + pd.u[1] * y + pd.u[2],
+                                         -(pd.v[0] * x + pd.v[1] * y + pd.v[2])));
+    if (t < tmin) {
+      tmin = t;
+      kmin = key;
+    }
+    if (t > tmax) {
+      tmax = t;
+      kmax = key;
+    }
+  }
+  // from one extreme corner to the other, through the centre
+  uint32_t lo = kmin, len = kmax - kmin;
+  if (kc - kmin > len) {
+    lo = kmax;
+    len = kmin - kmax;
+  }
+  const uint64_t margin = (uint64_t)(len >> 5) + 65536u;
+  const uint64_t wide = (uint64_t)len + 2u * margin;
+  if (wide >= 0xF0000000ull) return;
+  lo -= (uint32_t)margin;
+  pd.arc_len = (uint32_t)wide;
+  pd.arc_off = (uint32_t)((0x100000000ull - wide) / 2u);
+  pd.cut = lo - pd.arc_off;
+  pd.arc_mul = ((1ull << (32 + kCentreBits)) - 1ull) / wide;
+}
+
+// Position code of a key (an angle minus the pair's cut); never decreases
+// with the key.
+__host__ __device__ inline uint32_t position_code(const PairDev& pd, uint32_t key) {
+  const uint32_t y = key < pd.arc_off ? 0u : key - pd.arc_off;
+  return y >= pd.arc_len ? (1u << kCentreBits) - 1u : (uint32_t)(((uint64_t)y * pd.arc_mul) >> 32);
+}
 
 struct SortTile {
   int64_t begin;  // global element index
@@ -63,14 +136,19 @@ struct SortTile {
   int32_t seg;
 };
 
+// A segment of the sort and its tiles.  Segments of several tiles have a row
+// of digit counts per tile from hist_begin on; one tile counts for itself.
 struct SortSeg {
   int64_t begin;
   int64_t count;
   int32_t tile_begin, tile_count;
+  int32_t hist_begin, pad;
 };
 
-constexpr int kSortTile = 512;      // elements per sort tile
-constexpr int kSortThreads = 256;
+constexpr int kSortThreads = 1024;
+constexpr int kSortTileMin = 1024, kSortTileMax = 32768;  // elements per sort tile
+constexpr int kRadix = 1 << kRadixBits;
+constexpr int kHistWords = kRadix / 2;  // a row of counts: two 16-bit counts per word
 
 constexpr int kClassSlots = kNumClasses + 1;  // class_begin entries per pair
 

@@ -23,13 +23,6 @@ namespace epm {
 
 namespace {
 
-__device__ __forceinline__ uint32_t angle_key(double phi) {
-  // phi in [0, pi) -> round(phi * 2^32 / pi) mod 2^32
-  const double k = nearbyint(phi * kKeyPerRad);
-  const uint64_t u = (uint64_t)(int64_t)k;
-  return (uint32_t)u;
-}
-
 // Conservative interval of one keypoint: centre key and half-width key.
 __device__ void circle_interval(const PairDev& pd, float xf, float yf, float ef, uint32_t& C,
                                 uint32_t& H) {
@@ -74,9 +67,7 @@ __device__ void circle_interval(const PairDev& pd, float xf, float yf, float ef,
     vy = disc - half;
   }
   // interval centre: the eigenvector of lm, (-vy, vx)
-  double psi = atan2(vx, -vy);
-  if (psi < 0.0) psi += M_PI;
-  if (psi >= M_PI) psi -= M_PI;
+  const double psi = atan2(vx, -vy);
   const double h = atan(sqrt(-lm / lp));
   const double hk = ceil(h * kKeyPerRad) + (double)kGuard;
   if (!(hk < (double)(kFullHalf - 2 * kGuard))) {
@@ -84,7 +75,7 @@ __device__ void circle_interval(const PairDev& pd, float xf, float yf, float ef,
     H = kFullHalf;
     return;
   }
-  C = angle_key(psi);
+  C = angle_key(psi) - pd.cut;
   H = (uint32_t)hk;
 }
 
@@ -181,37 +172,34 @@ __global__ __launch_bounds__(64) void k_pair_setup(PairDev* __restrict__ pairs,
     pd.G11 = pd.G12 = pd.G22 = pd.e12 = 0.0;
     pd.kappa = -1.0;
   }
+  set_key_arc(pd);
   pairs[p] = pd;
 }
 
-constexpr int kRadixDigits = 256;  // digits of one 8-bit radix pass
-
-// Per-tile digit counts of the first radix pass of the keys this workgroup
-// wrote (tile blockIdx.x), and zero counts for the next zero_passes passes:
-// the segmented sort then starts with its scatter.
-__device__ __forceinline__ void first_pass_counts(uint32_t* h, uint32_t* __restrict__ hist,
-                                                  int num_tiles, int zero_passes) {
+// The digit counts of the first radix pass of the keys this workgroup wrote
+// (its tile, in LDS), as the sort reads them.  A segment of one tile counts
+// for itself.
+__device__ __forceinline__ void first_pass_counts(const uint32_t* h, const SortSeg& sg,
+                                                  uint32_t* __restrict__ hist) {
+  if (sg.tile_count < 2) return;  // uniform
   __syncthreads();
   const int tid = threadIdx.x;
-  if (tid >= kRadixDigits) return;
-  hist[(int64_t)blockIdx.x * kRadixDigits + tid] = h[tid];
-  for (int p = 1; p <= zero_passes; ++p)
-    hist[((int64_t)p * num_tiles + blockIdx.x) * kRadixDigits + tid] = 0u;
+  hist[(int64_t)(sg.hist_begin + (int)blockIdx.x - sg.tile_begin) * kHistWords + tid] =
+      h[2 * tid] | (h[2 * tid + 1] << 16);
 }
 
-// One workgroup per record sort tile (kSortTile keypoints of one pair, one
-// per thread).
-__global__ __launch_bounds__(kSortTile) void k_intervals(
-    const PairDev* __restrict__ pairs, const SortTile* __restrict__ tiles, int num_tiles,
-    const float* __restrict__ kp2, const float* __restrict__ eps2, float eps_scalar,
-    uint32_t* __restrict__ sort_key, uint32_t* __restrict__ sort_val, uint32_t* __restrict__ recC,
-    uint32_t* __restrict__ recH, uint32_t* __restrict__ hist, int zero_passes) {
-  __shared__ uint32_t h[kRadixDigits];
-  if (threadIdx.x < kRadixDigits) h[threadIdx.x] = 0u;
+// One workgroup per record sort tile.
+__global__ __launch_bounds__(kSortThreads) void k_intervals(
+    const PairDev* __restrict__ pairs, const SortTile* __restrict__ tiles,
+    const SortSeg* __restrict__ segs, const float* __restrict__ kp2,
+    const float* __restrict__ eps2, float eps_scalar, uint32_t* __restrict__ sort_key,
+    uint32_t* __restrict__ recC, uint32_t* __restrict__ recH, uint32_t* __restrict__ hist) {
+  __shared__ uint32_t h[kRadix];
+  h[2 * threadIdx.x] = h[2 * threadIdx.x + 1] = 0u;
   __syncthreads();
   const SortTile t = tiles[blockIdx.x];
   const PairDev& pd = pairs[t.seg];
-  for (int k = threadIdx.x; k < t.count; k += kSortTile) {
+  for (int k = threadIdx.x; k < t.count; k += kSortThreads) {
     const int64_t r = t.begin + k;
     const float xf = kp2[2 * r], yf = kp2[2 * r + 1];
     const float ef = eps2 ? eps2[r] : eps_scalar;
@@ -221,29 +209,26 @@ __global__ __launch_bounds__(kSortTile) void k_intervals(
     if (ef > 0.0f && isfinite(ef) && isfinite(xf) && isfinite(yf))
       circle_interval(pd, xf, yf, ef, C, H);
     const uint32_t cls = (uint32_t)width_class(H);
-    const uint32_t key = (cls << kCentreBits) | (C >> kCentreShift);
+    const uint32_t key = (cls << kCentreBits) | position_code(pd, C);
     sort_key[r] = key;
-    sort_val[r] = (uint32_t)r;
     recC[r] = C;
     recH[r] = H;
-    atomicAdd(&h[key & (kRadixDigits - 1)], 1u);
+    atomicAdd(&h[key & (kRadix - 1)], 1u);
   }
-  first_pass_counts(h, hist, num_tiles, zero_passes);
+  first_pass_counts(h, segs[t.seg], hist);
 }
 
 // Eq. 2 and Eq. 7: the angle of each query's epipolar line in the pencil,
 // reduced mod pi (an undirected line).
-// One workgroup per query sort tile (kSortTile queries of one pair, one per
-// thread).
-__global__ __launch_bounds__(kSortTile) void k_query_keys(
-    const PairDev* __restrict__ pairs, const SortTile* __restrict__ tiles, int num_tiles,
-    const float* __restrict__ kp1, uint32_t* __restrict__ qkey, uint32_t* __restrict__ qflag,
-    uint32_t* __restrict__ sort_key, uint32_t* __restrict__ sort_val,
-    double4* __restrict__ qline, uint32_t* __restrict__ hist, int zero_passes,
-    unsigned long long* __restrict__ stats, uint32_t* __restrict__ sched,
-    unsigned long long* __restrict__ match_stats) {
-  __shared__ uint32_t h[kRadixDigits];
-  if (threadIdx.x < kRadixDigits) h[threadIdx.x] = 0u;
+// One workgroup per query sort tile.  shift: that of the sort's first pass.
+__global__ __launch_bounds__(kSortThreads) void k_query_keys(
+    const PairDev* __restrict__ pairs, const SortTile* __restrict__ tiles,
+    const SortSeg* __restrict__ segs, const float* __restrict__ kp1, uint32_t* __restrict__ qkey,
+    uint32_t* __restrict__ qflag, uint32_t* __restrict__ sort_key, double4* __restrict__ qline,
+    int shift, uint32_t* __restrict__ hist, unsigned long long* __restrict__ stats,
+    uint32_t* __restrict__ sched, unsigned long long* __restrict__ match_stats) {
+  __shared__ uint32_t h[kRadix];
+  h[2 * threadIdx.x] = h[2 * threadIdx.x + 1] = 0u;
   if (blockIdx.x == 0) {  // the query's counters start from zero
     if (stats && threadIdx.x < kNumStats) stats[threadIdx.x] = 0ull;
     if (match_stats && threadIdx.x < kMatchStatWords) match_stats[threadIdx.x] = 0ull;
@@ -253,7 +238,7 @@ __global__ __launch_bounds__(kSortTile) void k_query_keys(
   __syncthreads();
   const SortTile t = tiles[blockIdx.x];
   const PairDev& pd = pairs[t.seg];
-  for (int kk = threadIdx.x; kk < t.count; kk += kSortTile) {
+  for (int kk = threadIdx.x; kk < t.count; kk += kSortThreads) {
     const int64_t i = t.begin + kk;
     double a, b, c;
     epipolar_line(pd.F, kp1[2 * i], kp1[2 * i + 1], a, b, c);
@@ -274,54 +259,19 @@ __global__ __launch_bounds__(kSortTile) void k_query_keys(
       if (pd.kappa < 0.0 || !(fabs(nu) <= pd.kappa * nrm)) {
         flag = kQueryBrute;  // the line misses the epipole by more than absorbed
       } else {
-        double phi = atan2(mu, lam);
-        if (phi < 0.0) phi += M_PI;
-        if (phi >= M_PI) phi -= M_PI;
-        key = angle_key(phi);
+        key = angle_key(atan2(mu, lam)) - pd.cut;
       }
     }
     qkey[i] = key;
     qflag[i] = flag;
-    sort_key[i] = key >> (32 - kQuerySortBits);
-    sort_val[i] = (uint32_t)i;
+    const uint32_t sk = position_code(pd, key) << kClassBits;
+    sort_key[i] = sk;
     // the line and its norm for the tile passes (the denominator of Eq. 3)
     qline[i] = flag == kQueryEmpty ? make_double4(0.0, 0.0, 0.0, 0.0)
                                    : make_double4(a, b, c, line_norm(a, b));
-    atomicAdd(&h[(key >> (32 - kQuerySortBits)) & (kRadixDigits - 1)], 1u);
+    atomicAdd(&h[(sk >> shift) & (kRadix - 1)], 1u);
   }
-  first_pass_counts(h, hist, num_tiles, zero_passes);
-}
-
-// Sorted layout: structure-of-arrays in angle order, plus the inverse
-// permutation (record -> sorted position).
-__global__ __launch_bounds__(256) void k_gather_records(
-    const int64_t* __restrict__ kstart, int num_pairs, int64_t n2,
-    const uint32_t* __restrict__ sorted_val, const float* __restrict__ kp2,
-    const float* __restrict__ eps2, float eps_scalar, const uint32_t* __restrict__ recC,
-    const uint32_t* __restrict__ recH, uint32_t* __restrict__ rC, uint32_t* __restrict__ rH,
-    int32_t* __restrict__ rj, float2* __restrict__ rxy, float* __restrict__ reps,
-    uint32_t* __restrict__ rinv, const uint32_t* __restrict__ digit_base,
-    int64_t* __restrict__ class_begin) {
-  // blocks of neighbouring sorted positions run on one XCD (xcd_tile): the
-  // scattered reads and rinv writes of a pair's records then meet in one L2
-  const int64_t pos = (int64_t)xcd_tile((int)blockIdx.x, (int)gridDim.x) * blockDim.x + threadIdx.x;
-  if (digit_base && pos < (int64_t)num_pairs * kClassSlots) {
-    // the start of width class c of pair p: the last radix pass's digit
-    // (class, top centre bits) starts, as the sort left them
-    const int p = (int)(pos / kClassSlots), c = (int)(pos % kClassSlots);
-    class_begin[pos] = c == kNumClasses
-                           ? kstart[p + 1]
-                           : (int64_t)digit_base[(int64_t)p * 256 + (c << (kSortBits - 16 - kClassBits))];
-  }
-  if (pos >= n2) return;
-  const uint32_t r = sorted_val[pos];
-  const int p = find_pair(kstart, num_pairs, (int64_t)r);
-  rC[pos] = recC[r];
-  rH[pos] = recH[r];
-  rj[pos] = (int32_t)((int64_t)r - kstart[p]);
-  rxy[pos] = make_float2(kp2[2 * (int64_t)r], kp2[2 * (int64_t)r + 1]);
-  reps[pos] = eps2 ? eps2[r] : eps_scalar;
-  rinv[r] = (uint32_t)pos;
+  first_pass_counts(h, segs[t.seg], hist);
 }
 
 // Start of every width class inside each pair's sorted segment.
@@ -345,41 +295,23 @@ hipError_t launch_pair_setup(PairDev* pairs, const double* F, int num_pairs, hip
   return hipGetLastError();
 }
 
-hipError_t launch_intervals(const PairDev* pairs, const SortTile* tiles, int num_tiles,
-                            const float* kp2, const float* eps2, float eps_scalar,
-                            uint32_t* sort_key, uint32_t* sort_val, uint32_t* recC,
-                            uint32_t* recH, uint32_t* hist, int zero_passes, hipStream_t s) {
-  if (num_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_intervals, dim3((unsigned)num_tiles), dim3(kSortTile), 0, s, pairs,
-                     tiles, num_tiles, kp2, eps2, eps_scalar, sort_key, sort_val, recC, recH,
-                     hist, zero_passes);
+hipError_t launch_intervals(const PairDev* pairs, const SortCall& c, const float* kp2,
+                            const float* eps2, float eps_scalar, uint32_t* recC, uint32_t* recH,
+                            hipStream_t s) {
+  if (c.num_tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_intervals, dim3((unsigned)c.num_tiles), dim3(kSortThreads), 0, s, pairs,
+                     c.tiles, c.segs, kp2, eps2, eps_scalar, c.k0, recC, recH, c.hist0);
   return hipGetLastError();
 }
 
-hipError_t launch_query_keys(const PairDev* pairs, const SortTile* tiles, int num_tiles,
-                             const float* kp1, uint32_t* qkey, uint32_t* qflag,
-                             uint32_t* sort_key, uint32_t* sort_val, double4* qline,
-                             uint32_t* hist, int zero_passes, unsigned long long* stats,
-                             uint32_t* sched, unsigned long long* match_stats, hipStream_t s) {
-  if (num_tiles == 0) return launch_clear_stats(stats, s, sched, match_stats);
-  hipLaunchKernelGGL(k_query_keys, dim3((unsigned)num_tiles), dim3(kSortTile), 0, s, pairs,
-                     tiles, num_tiles, kp1, qkey, qflag, sort_key, sort_val, qline, hist,
-                     zero_passes, stats, sched, match_stats);
-  return hipGetLastError();
-}
-
-hipError_t launch_gather_records(const int64_t* kstart, int num_pairs, int64_t n2,
-                                 const uint32_t* sorted_val, const float* kp2, const float* eps2,
-                                 float eps_scalar, const uint32_t* recC, const uint32_t* recH,
-                                 uint32_t* rC, uint32_t* rH, int32_t* rj, float2* rxy,
-                                 float* reps, uint32_t* rinv, const uint32_t* digit_base,
-                                 int64_t* class_begin, hipStream_t s) {
-  if (n2 == 0) return hipSuccess;
-  const int64_t items = n2 > (int64_t)num_pairs * kClassSlots ? n2 : (int64_t)num_pairs * kClassSlots;
-  const int64_t blocks = (items + 255) / 256;
-  hipLaunchKernelGGL(k_gather_records, dim3((unsigned)blocks), dim3(256), 0, s, kstart,
-                     num_pairs, n2, sorted_val, kp2, eps2, eps_scalar, recC, recH, rC, rH, rj,
-                     rxy, reps, rinv, digit_base, class_begin);
+hipError_t launch_query_keys(const PairDev* pairs, const SortCall& c, bool two_passes,
+                             const float* kp1, uint32_t* qkey, uint32_t* qflag, double4* qline,
+                             unsigned long long* stats, uint32_t* sched,
+                             unsigned long long* match_stats, hipStream_t s) {
+  if (c.num_tiles == 0) return launch_clear_stats(stats, s, sched, match_stats);
+  hipLaunchKernelGGL(k_query_keys, dim3((unsigned)c.num_tiles), dim3(kSortThreads), 0, s, pairs,
+                     c.tiles, c.segs, kp1, qkey, qflag, c.k0, qline, two_passes ? 0 : kRadixBits,
+                     c.hist0, stats, sched, match_stats);
   return hipGetLastError();
 }
 

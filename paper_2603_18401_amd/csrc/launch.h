@@ -13,58 +13,68 @@ namespace epm {
 // without a pencil gets kappa = -1 (its queries then scan the whole pair).
 hipError_t launch_pair_setup(PairDev* pairs, const double* F, int num_pairs, hipStream_t s);
 
-// One workgroup per record sort tile; also leaves the first radix pass's
-// per-tile digit counts in hist (and zero counts for the later passes), so
-// that segmented_radix_sort(..., first_counts_ready = true) skips its count.
-hipError_t launch_intervals(const PairDev* pairs, const SortTile* tiles, int num_tiles,
-                            const float* kp2, const float* eps2, float eps_scalar,
-                            uint32_t* sort_key, uint32_t* sort_val, uint32_t* recC,
-                            uint32_t* recH, uint32_t* hist, int zero_passes, hipStream_t s);
+// ------------------------------------------------------------------ sort
+// One of the two sorts: its tiles and segments, the buffers (keys k0 in;
+// keys and indices k1, v1 between two passes) and the rows of digit counts of
+// its passes (kHistWords words per tile of a segment of several tiles).
+struct SortCall {
+  const SortTile* tiles;
+  int64_t num_tiles, rows;  // rows of counts
+  const SortSeg* segs;
+  int num_segs;
+  uint32_t *k0, *k1, *v1;
+  uint32_t *hist0, *hist1;
+};
 
-// One workgroup per query sort tile.  Also writes every query's line (a, b,
-// c, sqrt(a^2 + b^2)) to qline (zero for a query without a line), the first
-// radix pass's counts as launch_intervals does, and its first workgroup
-// clears the counters as launch_clear_stats does (each pointer may be NULL).
-hipError_t launch_query_keys(const PairDev* pairs, const SortTile* tiles, int num_tiles,
-                             const float* kp1, uint32_t* qkey, uint32_t* qflag,
-                             uint32_t* sort_key, uint32_t* sort_val, double4* qline,
-                             uint32_t* hist, int zero_passes, unsigned long long* stats,
-                             uint32_t* sched, unsigned long long* match_stats, hipStream_t s);
+// What the records' last pass reads (by keypoint) and writes (by place): the
+// sorted records, each keypoint's place, and every pair's class starts.
+struct RecordSort {
+  const float* kp2;
+  const float* eps2;  // or NULL: eps_scalar
+  float eps_scalar;
+  const uint32_t *recC, *recH;
+  uint32_t *rC, *rH;
+  int32_t* rj;
+  float2* rxy;
+  float* reps;
+  uint32_t* rinv;
+  int64_t* class_begin;
+};
 
-hipError_t launch_gather_records(const int64_t* kstart, int num_pairs, int64_t n2,
-                                 const uint32_t* sorted_val, const float* kp2, const float* eps2,
-                                 float eps_scalar, const uint32_t* recC, const uint32_t* recH,
-                                 uint32_t* rC, uint32_t* rH, int32_t* rj, float2* rxy,
-                                 float* reps, uint32_t* rinv, const uint32_t* digit_base,
-                                 int64_t* class_begin, hipStream_t s);
-// digit_base non-NULL: the gather also writes class_begin from the digit
-// starts of the last sort pass (digit = class << 3 | top three centre bits).
+int sort_tile_size(int64_t largest_segment);
+
+// The sort tiles of the records (tr, rsize elements each) and the queries
+// (tq, qsize) and the stabbing tiles (ts), filled from the per-pair segments,
+// the query slice starts and each pair's first stabbing tile (num_pairs + 1
+// entries).
+hipError_t launch_expand_tiles(const SortSeg* rsegs, const SortSeg* qsegs, const int64_t* qstart,
+                               const int32_t* stile_begin, int num_pairs, SortTile* rtiles,
+                               int64_t tr, int rsize, SortTile* qtiles, int64_t tq, int qsize,
+                               StabTile* stiles, int64_t ts, hipStream_t s);
+
+// Interval records and their sort keys (c.k0), with the first pass's counts.
+hipError_t launch_intervals(const PairDev* pairs, const SortCall& c, const float* kp2,
+                            const float* eps2, float eps_scalar, uint32_t* recC, uint32_t* recH,
+                            hipStream_t s);
+
+// Query keys, flags and sort keys (c.k0), with the first pass's counts; also
+// every query's line (a, b, c, sqrt(a^2 + b^2)) in qline (zero for a query
+// without a line), and the counters cleared as launch_clear_stats does (each
+// pointer may be NULL).
+hipError_t launch_query_keys(const PairDev* pairs, const SortCall& c, bool two_passes,
+                             const float* kp1, uint32_t* qkey, uint32_t* qflag, double4* qline,
+                             unsigned long long* stats, uint32_t* sched,
+                             unsigned long long* match_stats, hipStream_t s);
+
+// The records in the order of their keys, stable; c.k0 holds the sorted keys
+// afterwards.
+hipError_t sort_records(const SortCall& c, const RecordSort& r, hipStream_t s);
+// perm: the queries of every pair by the upper kRadixBits bits of their
+// position codes, or by all of them (two_passes; perm may then be c.k0).
+hipError_t sort_queries(const SortCall& c, bool two_passes, uint32_t* perm, hipStream_t s);
 
 hipError_t launch_class_bounds(const int64_t* kstart, int num_pairs, const uint32_t* skey,
                                int64_t* class_begin, hipStream_t s);
-
-// Stable LSD radix sort of (key, value) u32 pairs inside every segment, over
-// the low `bits` bits of the keys, 8 bits per pass.  Ping-pongs between
-// (k0, v0) and (k1, v1); returns through *sorted_in_1 whether the result
-// ended in (k1, v1).
-// last_digit_base (optional, [num_segs][256]): global start of every digit
-// value of the last pass inside each segment.
-// hist: [sort_passes(bits)][num_tiles][256] words; max_seg_tiles: the most
-// tiles of one segment (up to 64 a pass is a single launch).
-int sort_passes(int bits);
-// The sort tiles of the records (tr) and the queries (tq) and the stabbing
-// tiles (ts), filled from the per-pair segments, the query slice starts and
-// each pair's first stabbing tile (num_pairs + 1 entries).
-hipError_t launch_expand_tiles(const SortSeg* rsegs, const SortSeg* qsegs, const int64_t* qstart,
-                               const int32_t* stile_begin, int num_pairs, SortTile* rtiles,
-                               int64_t tr, SortTile* qtiles, int64_t tq, StabTile* stiles,
-                               int64_t ts, hipStream_t s);
-hipError_t segmented_radix_sort(uint32_t* k0, uint32_t* v0, uint32_t* k1, uint32_t* v1,
-                                const SortTile* tiles, int num_tiles, const SortSeg* segs,
-                                int num_segs, int max_seg_tiles, uint32_t* hist, int bits,
-                                bool* sorted_in_1, hipStream_t s,
-                                uint32_t* last_digit_base = nullptr,
-                                bool first_counts_ready = false);
 
 struct StabArgs {
   const PairDev* pairs;
@@ -74,7 +84,7 @@ struct StabArgs {
   const float* kp1;
   const uint32_t* qkey;
   const uint32_t* qflag;
-  const uint32_t* qperm;
+  uint32_t* qperm;  // the queries by angle; the window pass orders it within its workgroups
   const int64_t* class_begin;
   const uint32_t* skey;
   const uint32_t* rC;
