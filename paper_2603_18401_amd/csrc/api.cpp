@@ -110,13 +110,19 @@ Layout make_layout(int P, int64_t n1, int64_t n2, const Tiles& T) {
   L.pair_wide = take(sizeof(uint32_t) * P);
   L.pre_pairs = take(sizeof(int64_t) * (2 * (size_t)P + 2));
   L.qline = take(sizeof(double4) * N1);
-  L.tile_q = take(sizeof(TileQuery) * kTileQ * (size_t)ts);
+  // the tiles' queries take the place of what only the sort of the records
+  // needed, where they fit
+  const size_t tile_q_bytes = sizeof(TileQuery) * kTileQ * (size_t)ts;
+  L.tile_q = tile_q_bytes <= L.rhist0 - L.rk1 ? L.rk1 : take(tile_q_bytes);
   L.tile_counts = take(sizeof(unsigned long long) * kTileCounts * (size_t)ts);
   L.total = off;
   return L;
 }
 
-int64_t stab_tiles_of(int64_t m) { return (m + kTileQ - 1) / kTileQ; }
+int64_t stab_tiles_of(const epm_pair& e) {
+  const int tq = tile_queries(e.m, e.n);
+  return (e.m + tq - 1) / tq;
+}
 
 // The tiles of a validated batch.
 Tiles tiles_of(const epm_pair* pairs, int P) {
@@ -134,7 +140,7 @@ Tiles tiles_of(const epm_pair* pairs, int P) {
     T.q += q;
     T.rrows += r > 1 ? r : 0;
     T.qrows += q > 1 ? q : 0;
-    T.stab += stab_tiles_of(pairs[p].m);
+    T.stab += stab_tiles_of(pairs[p]);
   }
   return T;
 }
@@ -343,7 +349,7 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   idx->stile_begin.resize(num_pairs + 1);
   idx->stile_begin[0] = 0;
   for (int p = 0; p < num_pairs; ++p)
-    idx->stile_begin[p + 1] = idx->stile_begin[p] + (int32_t)stab_tiles_of(pairs[p].m);
+    idx->stile_begin[p + 1] = idx->stile_begin[p] + (int32_t)stab_tiles_of(pairs[p]);
   idx->L = make_layout(num_pairs, n1, n2, idx->tiles);
   if (workspace_bytes < idx->L.total) {
     delete idx;

@@ -156,7 +156,7 @@ constexpr int kClassSlots = kNumClasses + 1;  // class_begin entries per pair
 // ascending j order by a direct scan of the pair.
 constexpr int kRowSortMax = 2048;
 
-// Stabbing tiles: kTileQ consecutive angle-sorted queries of one pair share
+// Stabbing tiles: up to kTileQ consecutive angle-sorted queries of one pair share
 // one window search per width class; the window's records are staged in LDS
 // a round at a time (256, 512 or 1024 records, a tile shape chosen per index;
 // kChunk by default).  Rows of up to kStage candidates are parked in a staging
@@ -187,12 +187,24 @@ struct StabTile {
 };
 
 // One query of a stabbing tile as the window pass leaves it for the tile
-// pass: the epipolar line (a, b, c), sqrt(a^2 + b^2), the query's index, flag
-// and key (slots past the tile's count: empty, index 0).
+// pass: the epipolar line (a, b, c), the query's index, flag and key (slots
+// past the tile's count: empty, index 0).
 struct TileQuery {
-  double a, b, c, n;
-  int64_t i;
-  uint32_t flag, key;
+  double a, b, c;
+  uint32_t i, flag, key, pad;
 };
+
+// Queries per tile of a pair with m queries and n records.  A tile's window
+// holds the records between its first and last query, n / m per query, beside
+// those within the tolerance, and windows of more than 1024 records are left
+// to slower passes; so a pair with many records per query takes fewer queries
+// per tile, such that they hold up to 512.  (512 uneven pairs, of whose
+// queries 2 % have more than 8 records each: 3265 us with 64 everywhere --
+// 267 us of it rebuilding and matching the rows of such windows, 280 us a few
+// very long tiles of the wide-row pass -- and 3025 us with this rule; 3060
+// with up to 384.)
+__host__ __device__ inline int tile_queries(int64_t m, int64_t n) {
+  return n <= 8 * m ? kTileQ : n <= 16 * m ? kTileQ / 2 : n <= 32 * m ? kTileQ / 4 : kTileQ / 8;
+}
 
 }  // namespace epm

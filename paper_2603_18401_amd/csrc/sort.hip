@@ -95,11 +95,12 @@ __global__ __launch_bounds__(256) void k_expand_tiles(
       if ((int64_t)stile_begin[mid] <= t) lo = mid;
       else hi = mid - 1;
     }
-    const int64_t o = (t - stile_begin[lo]) * kTileQ;
     const int64_t m = qstart[lo + 1] - qstart[lo];
+    const int tq_size = tile_queries(m, rsegs[lo].count);
+    const int64_t o = (t - stile_begin[lo]) * tq_size;
     StabTile st;
     st.begin = qstart[lo] + o;
-    st.count = (int32_t)(m - o < kTileQ ? m - o : kTileQ);
+    st.count = (int32_t)(m - o < tq_size ? m - o : tq_size);
     st.pair = lo;
     stiles[t] = st;
   }

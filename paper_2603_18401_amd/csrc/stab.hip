@@ -329,10 +329,10 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
   bool normal = false, brute = false;
   uint32_t key = 0;
   TileQuery tq;
-  tq.a = tq.b = tq.c = tq.n = 0.0;
+  tq.a = tq.b = tq.c = 0.0;
   tq.i = 0;
   tq.flag = kQueryEmpty;
-  tq.key = 0;
+  tq.key = tq.pad = 0;
   if (lane < T.count) {
     const int64_t i = s_i[slot];
     if ((uint32_t)i != qi) A.qperm[T.begin + lane] = (uint32_t)i;
@@ -340,14 +340,13 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
     normal = flag == kQueryNormal;
     brute = flag == kQueryBrute;
     key = A.qkey[i];
-    tq.i = i;
+    tq.i = (uint32_t)i;
     tq.flag = flag;
     tq.key = key;
-    const double4 L = A.qline[i];  // the line of Eq. 2 and its norm, from the key pass
+    const double4 L = A.qline[i];  // the line of Eq. 2, from the key pass
     tq.a = L.x;
     tq.b = L.y;
     tq.c = L.z;
-    tq.n = L.w;
   }
   A.tile_q[(int64_t)t * kTileQ + lane] = tq;
   if (lane == 0) {
@@ -789,7 +788,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
       qa[lane] = tq.a;
       qb[lane] = tq.b;
       qc[lane] = tq.c;
-      qn[lane] = tq.n;
+      qn[lane] = line_norm(tq.a, tq.b);  // as the key pass rounds it
       qk[lane] = tq.key;
       qmode[lane] = tq.flag;
       qidx[lane] = tq.i;

@@ -78,3 +78,34 @@ def test_two_pass_queries():
     torch = torch_gpu()
     _check(torch, E, [_pair("far", 131073, 50, 5), _pair("forward", 700, 60, 6)], 2.0)
     _check(torch, E, [_pair("oblique", 40, 131100, 7)], 0.5)
+
+
+@pytest.mark.parametrize("m,n", [(70, 560), (70, 561), (70, 1121), (70, 2241), (9, 6000),
+                                 (500, 5000), (1, 300)])
+def test_uneven_pairs_take_smaller_tiles(m, n):
+    """8, 16 and 32 image-2 keypoints per query are the edges of the rule:
+    candidates and FP32 / BF16 matches equal the oracle's on both sides."""
+    import paper_2603_18401_amd as E
+    torch = torch_gpu()
+    dev = torch.device("cuda:0")
+    g = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    F, kp1, kp2 = _pair("oblique", m, n, m + n)
+    rng = np.random.default_rng(n)
+    d1 = synth.pairs._unit_rows(rng.standard_normal((m, 128)))
+    d2 = synth.pairs._unit_rows(rng.standard_normal((n, 128)))
+    for eps in (2.0, 12.0):
+        ro, rc, _ = oracle.candidates(F, kp1, kp2, eps)
+        rb, rbd, rsd = oracle.match(d1, d2, ro, rc)
+        idx = E.Index([E.PairSpec(F, 1920, 1080, m, n)], g(kp2), eps=eps)
+        f1, f2 = g(d1), g(d2)
+        for got in (idx.query_match(g(kp1), f1, f2),
+                    idx.query_match_bf16(g(kp1), E.quantize(f1, "bf16"), E.quantize(f2, "bf16"),
+                                         f1, f2)):
+            offs, cols, b, bd, sd = [t.cpu().numpy() for t in got]
+            assert np.array_equal(offs, ro) and np.array_equal(cols, rc)
+            assert np.array_equal(b, rb)
+            assert np.array_equal(bd.view(np.uint32), rbd.view(np.uint32))
+            assert np.array_equal(sd.view(np.uint32), rsd.view(np.uint32))
+        offs, cols = idx.query(g(kp1))
+        b, bd, sd = [t.cpu().numpy() for t in idx.match(offs, cols, f1, f2)]
+        assert np.array_equal(b, rb) and np.array_equal(sd.view(np.uint32), rsd.view(np.uint32))
