@@ -740,7 +740,7 @@ epm_status enqueue_match_kernels(epm_index* idx, const MatchCall& c, hipStream_t
     EPM_HIP(launch_clear_stats(nullptr, stream, nullptr, A.match_stats));
   }
   if (wide) A.skip_tiles = idx->at<uint32_t>(L.tile_wide);
-  auto wide_launch = [&]() -> hipError_t {
+  auto csr_args = [&]() {
     const bool bf = c.dtype == EPM_BF16;
     StabArgs W = stab_args(idx, nullptr, const_cast<int64_t*>(c.row_offsets),
                            const_cast<int32_t*>(c.col_indices),
@@ -757,6 +757,11 @@ epm_status enqueue_match_kernels(epm_index* idx, const MatchCall& c, hipStream_t
     W.match_stats = A.match_stats;
     W.rest_count = A.match_stats + kMatchStatRest;
     W.block_tile = A.block_tile;
+    return W;
+  };
+  auto wide_launch = [&]() -> hipError_t {
+    const bool bf = c.dtype == EPM_BF16;
+    StabArgs W = csr_args();
     if (!bf) {
       const hipError_t pe = prepare_wide_rows(idx, W, stream);
       if (pe != hipSuccess) return pe;
@@ -778,7 +783,17 @@ epm_status enqueue_match_kernels(epm_index* idx, const MatchCall& c, hipStream_t
       EPM_HIP(launch_match_plain_f32(A, stream));
       return EPM_OK;
     }
-    EPM_HIP(tiled_launch(c.dtype == EPM_BF16 ? 0 : 1));
+    if (c.dtype == EPM_BF16 && !c.qerr1) {
+      // codes rounded to nearest (the format's bound): the fused pass's
+      // selection; with measured errors, and FP8 queries, the window kernel
+      StabArgs W = csr_args();
+      W.queue = A.queue;
+      W.order = A.order;
+      if (grid > 0) EPM_HIP(launch_fill_u32(A.queue, 1, 0u, stream));
+      EPM_HIP(launch_stab_tiles(W, grid, kCsrBF16, 0, stream));
+    } else {
+      EPM_HIP(tiled_launch(c.dtype == EPM_BF16 ? 0 : 1));
+    }
     if (wide) EPM_HIP(wide_launch());
     return EPM_OK;
   }

@@ -193,7 +193,11 @@ hipError_t launch_clear_stats(unsigned long long* stats, hipStream_t s, uint32_t
 // mode kStabFP8: likewise over the FP8 image-2 rows in f8codes2 (scales
 // f8scale2, rounding-error bounds f8err2); the queries are rounded to BF16 on
 // chip from their masters.
-constexpr int kStabCount = 0, kStabF32 = 1, kStabBF16 = 2, kStabFP8 = 3;
+// mode kCsrBF16: no candidate search; the BF16 selection over a caller's CSR
+// (row_offsets, cols up to capacity) on the tiles of the last query that are
+// not flagged in tile_wide, into the caller's match arrays; counters in
+// match_stats, leftover queries in rest / *rest_count.
+constexpr int kStabCount = 0, kStabF32 = 1, kStabBF16 = 2, kStabFP8 = 3, kCsrBF16 = 4;
 // chunk: window records staged per round (256, 512 or 1024; 0 = 256 for the
 // BF16 and FP8 passes, 512 for the others).
 hipError_t launch_stab_tiles(const StabArgs& a, int grid, int mode, int chunk, hipStream_t s);

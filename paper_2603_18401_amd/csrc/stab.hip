@@ -716,28 +716,41 @@ __device__ __forceinline__ void bf_bounds(float at, float nb, float q_nb, float 
 
 // MODE: kStabCount (count and park rows), kStabF32 (FP32 selection fused),
 // kStabBF16 / kStabFP8 (BF16 or FP8 image-2 rows: MFMA bounds with an exact
-// FP32 re-rank, fused).
+// FP32 re-rank, fused), or kCsrBF16: the BF16 selection over a caller's CSR.
 // Fused: three workgroups per CU (LDS and registers are sized for it; four
-// for kStabBF16)
+// for kStabBF16 and kCsrBF16)
 // CH: window records staged in LDS per round of the pair test.
+//
+// kCsrBF16 (epm_match on the tiles of the last query): instead of the pair
+// test, the CSR's rows say which window positions are hits.  Every entry is
+// mapped to its position (inverse permutation, window slots) and sets a bit of
+// its query's bitmap; a row whose bits are fewer than its entries (candidates
+// outside the window, repeated ones) and rows longer than kStage are listed
+// for the exact match, as are tiles with windows over kKeepJ.  What bounds it
+// then is what bounds the fused selection.  The window kernel it replaces here
+// (a dense entry list in LDS, FP64 bounds per entry, one thread per query for
+// the selection) took 205 us for 60000 queries with 60 candidates each, this
+// one 57.
 template <bool PERSIST, int MODE, int CH>
-__global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCount ? 3 : 2) void k_stab_tile(StabArgs A) {
+__global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4 : MODE != kStabCount ? 3 : 2) void k_stab_tile(StabArgs A) {
   constexpr bool FUSE = MODE != kStabCount;
+  constexpr bool CSR = MODE == kCsrBF16;
+  constexpr bool BF = MODE == kStabBF16 || CSR;  // BF16 rows of both images
   // BF16 / FP8: MFMA bounds and an exact re-rank on the masters
-  constexpr bool RED = MODE == kStabBF16 || MODE == kStabFP8;
+  constexpr bool RED = BF || MODE == kStabFP8;
   // record chunk (sC, sH, sXY, sE; sJ too unless FUSE keeps the window's j
   // in sJ_keep), reused for descriptor rows in the match phase
   constexpr int kRecRaw = FUSE ? rec_bytes(CH) - CH * 4 : rec_bytes(CH);
   constexpr int kMatchRaw = MODE == kStabF32    ? kFuseBytes
-                           : MODE == kStabBF16 ? red_scratch(kBfKeep)
+                           : BF                ? red_scratch(kBfKeep)
                            : MODE == kStabFP8  ? red_scratch(kF8Keep)
                                                : 0;
-  constexpr int kRaw = kMatchRaw > kRecRaw ? kMatchRaw : kRecRaw;
+  constexpr int kRaw = kMatchRaw > kRecRaw || CSR ? kMatchRaw : kRecRaw;
   __shared__ __attribute__((aligned(16))) unsigned char raw[kRaw];
   // BF16 / FP8: the window's reduced rows, kBfRows at a time (the first
   // chunk is copied in while the pair test runs)
   __shared__ __attribute__((aligned(16)))
-  uint8_t bfrows[MODE == kStabBF16 ? kBfRowBytes : MODE == kStabFP8 ? kF8RowBytes : 16];
+  uint8_t bfrows[BF ? kBfRowBytes : MODE == kStabFP8 ? kF8RowBytes : 16];
   __shared__ int32_t sJ_keep[FUSE ? kKeepJ : 1];
   uint32_t* sC = reinterpret_cast<uint32_t*>(raw);
   uint32_t* sH = sC + CH;
@@ -746,7 +759,9 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
   int32_t* sJ = reinterpret_cast<int32_t*>(sE + CH);  // not FUSE
   // hit lists: image-2 indices, or (FUSE) 16-bit window positions
   __shared__ int32_t hits[FUSE ? 1 : kTileQ][FUSE ? 1 : kStage + 1];  // +1: rows in different banks
-  __shared__ uint16_t hits_v[FUSE ? kTileQ : 1][FUSE ? kStage + 2 : 1];
+  __shared__ uint16_t hits_v[FUSE && !CSR ? kTileQ : 1][FUSE && !CSR ? kStage + 2 : 1];
+  // kCsrBF16: the hits of every query by window position
+  __shared__ uint32_t hit_bits[CSR ? kTileQ : 1][CSR ? kKeepJ / 32 + 1 : 1];
   // image-2 index of hit u of query q
   const auto hit_j = [&](int q, uint32_t u) -> int32_t {
     if constexpr (FUSE)
@@ -754,7 +769,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     else
       return hits[q][u];
   };
-  __shared__ double qa[kTileQ], qb[kTileQ], qc[kTileQ], qn[kTileQ];
+  constexpr int kLines = CSR ? 1 : kTileQ;
+  __shared__ double qa[kLines], qb[kLines], qc[kLines], qn[kLines];
   __shared__ uint32_t qk[kTileQ], qmode[kTileQ], cnt[kTileQ];
   __shared__ int64_t qidx[kTileQ];
   __shared__ uint32_t slot_b[kSlots], slot_pref[kSlots + 1];
@@ -763,6 +779,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
   __shared__ uint32_t tile_stats[kTileCounts];
   __shared__ int next_tile;
 
+  // a caller's CSR that did not fit its buffer is incomplete: nothing is written
+  if (CSR && A.row_offsets[A.n1] > A.capacity) return;
   // one tile per workgroup, or (persistent) tiles from the queue until it is
   // exhausted; every workgroup leaves the loop once the counter passes the
   // last tile
@@ -778,6 +796,11 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
       if (iter > 0) break;
       tile = A.block_tile ? (int)A.block_tile[blockIdx.x] : xcd_tile(blockIdx.x, A.num_tiles);
     }
+    if (CSR && A.tile_wide[tile] != 0u) {  // matched by the wide-row pass
+      if (!PERSIST) return;                // (a loop here would cost registers)
+      __syncthreads();                     // next_tile is read before it is rewritten
+      continue;
+    }
     const StabTile T = A.tiles[tile];
     const PairDev& pd = A.pairs[T.pair];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
@@ -785,10 +808,12 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     if (wave == 0) {
       // the tile's queries with their lines, from the window pass
       const TileQuery tq = A.tile_q[(int64_t)tile * kTileQ + lane];
-      qa[lane] = tq.a;
-      qb[lane] = tq.b;
-      qc[lane] = tq.c;
-      qn[lane] = line_norm(tq.a, tq.b);  // as the key pass rounds it
+      if constexpr (!CSR) {
+        qa[lane] = tq.a;
+        qb[lane] = tq.b;
+        qc[lane] = tq.c;
+        qn[lane] = line_norm(tq.a, tq.b);  // as the key pass rounds it
+      }
       qk[lane] = tq.key;
       qmode[lane] = tq.flag;
       qidx[lane] = tq.i;
@@ -811,7 +836,13 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     const uint64_t live_mask = ballot(line_live);
     const bool any_live = ballot(line_live) != 0;
     const uint32_t lkey = qk[lq];
-    const double la = qa[lq], lb = qb[lq], lc = qc[lq], ln = qn[lq];
+    double la = 0.0, lb = 0.0, lc = 0.0, ln = 0.0;
+    if constexpr (!CSR) {
+      la = qa[lq];
+      lb = qb[lq];
+      lc = qc[lq];
+      ln = qn[lq];
+    }
     const uint64_t same_query = 0x0001000100010001ull << (lane & (kQPerWave - 1));
     // the wavefront's key span [kmn, kmx] over its live queries: a record
     // whose interval misses every key of the span (circular distance from the
@@ -827,6 +858,64 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     const uint32_t kmid = kmn + ((kmx - kmn) >> 1);
     const uint64_t khalf = ((uint64_t)(kmx - kmn) + 1u) >> 1;
     uint32_t lcnt = 0;
+    // kCsrBF16: the row's length (0 past the tile), and whether its bits say it all
+    int64_t csr_len = 0;
+    bool csr_ok = false;
+    if constexpr (CSR) {
+      const int g = lane >> 4;
+      const int64_t kb = pd.k_begin;
+      int64_t o0 = 0;
+      if (lq < T.count) {
+        o0 = A.row_offsets[qidx[lq]];
+        csr_len = A.row_offsets[qidx[lq] + 1] - o0;
+      }
+      const bool here = line_live && fusable && csr_len <= kStage;
+      if (fusable) {
+        for (int v = tid; v < (int)total_len; v += kThreads) {
+          int s = 0;  // last slot with slot_pref[s] <= v
+          #pragma unroll
+          for (int step = 32; step > 0; step >>= 1)
+            if (s + step <= kSlots && slot_pref[s + step] <= (uint32_t)v) s += step;
+          sJ_keep[v] = A.rj[slot_b[s] + ((uint32_t)v - slot_pref[s])];
+        }
+      }
+      #pragma unroll
+      for (int k = g; k <= kKeepJ / 32; k += 4) hit_bits[lq][k] = 0u;
+      // the slots that hold records, for every lane's entries
+      uint64_t filled = ballot(slot_pref[lane + 1] > slot_pref[lane]);
+      constexpr int kFly = 4;  // entries of a lane whose gathers are in flight together
+      const int n = here ? (int)csr_len : 0;
+      const int nmax = (int)wave_max_u32((uint32_t)n);
+      for (int e0 = g; e0 < nmax; e0 += 4 * kFly) {
+        uint32_t pos[kFly];
+        #pragma unroll
+        for (int u = 0; u < kFly; ++u)
+          pos[u] = e0 + 4 * u < n ? A.rinv[kb + A.cols[o0 + e0 + 4 * u]] : 0u;
+        int v[kFly];
+        #pragma unroll
+        for (int u = 0; u < kFly; ++u) v[u] = -1;
+        for (uint64_t m = filled; m != 0ull; m &= m - 1ull) {
+          const int s = (int)__builtin_ctzll(m);
+          const uint32_t b = slot_b[s], p = slot_pref[s], len = slot_pref[s + 1] - p;
+          #pragma unroll
+          for (int u = 0; u < kFly; ++u)
+            if (pos[u] - b < len) v[u] = (int)(p + (pos[u] - b));
+        }
+        #pragma unroll
+        for (int u = 0; u < kFly; ++u)
+          if (e0 + 4 * u < n && v[u] >= 0) atomicOr(&hit_bits[lq][v[u] >> 5], 1u << (v[u] & 31));
+      }
+      wave_sync_lds();
+      int set = 0;
+      for (int k = g; k < kKeepJ / 32; k += 4) set += __popc(hit_bits[lq][k]);
+      set += __shfl_xor(set, 16);
+      set += __shfl_xor(set, 32);
+      csr_ok = here && set == n;
+      __syncthreads();  // the window's j are complete
+      if (fusable && total_len > 0)
+        bf16_stage(A, 0, total_len < kBfRows ? (int)total_len : kBfRows, kb, sJ_keep, bfrows, wave,
+                   lane);
+    }
     // BF16: the query rows are loaded before the pair test so that their
     // latency hides behind it.  Lane l of wavefront w holds query
     // 16 w + (l & 15): as MFMA B operands its BF16 values at dimensions
@@ -850,7 +939,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
         qraw[2 * kk + 1] = ld ? m[kk * 8 + g * 2 + 1] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
     }
-    if constexpr (MODE == kStabBF16) {
+    if constexpr (BF) {
       const int g = lane >> 4;
       const bool ld = line_live && lq < T.count && fusable;
       const int64_t qi = qidx[lq];
@@ -867,7 +956,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
         qx[u] = ld ? reinterpret_cast<const float4*>(A.desc1)[qi * 32 + g * 8 + u]
                    : make_float4(0.f, 0.f, 0.f, 0.f);
     }
-    for (int64_t base = 0; base < total_len; base += CH) {
+    for (int64_t base = 0; !CSR && base < total_len; base += CH) {
       const int clen = (int)(total_len - base < CH ? total_len - base : CH);
       for (int v = tid; v < clen; v += kThreads) {
         const int64_t virt = base + v;
@@ -949,6 +1038,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
       }
       __syncthreads();
     }
+    if constexpr (!CSR) {
     if (line_live && lane < kQPerWave) cnt[lq] = lcnt;
 
     // queries whose line misses the epipole too far: exact scan of the pair
@@ -1003,6 +1093,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
       }
     }
     (void)brute;
+    }
 
     // FUSE: four threads per query select its match
     const int q = tid >> 2, part = tid & 3;
@@ -1014,6 +1105,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     // distinct, so a hit's place is the number of smaller hits); a thread
     // ranks up to four of its hits in one pass over the row
     // (the fused modes write the row length with the match, in one record)
+    if constexpr (!CSR) {
     if (!FUSE && part == 0 && q < T.count)
       A.counts[qidx[q]] = qmode[q] == kQueryEmpty ? 0u : cnt[q];
     {
@@ -1055,6 +1147,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
           A.rest[at] = (uint32_t)qidx[q];
         }
       }
+    }
     }
     if constexpr (MODE == kStabF32) {
       const int nq = mine ? (int)cnt[q] : 0;
@@ -1113,9 +1206,10 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
       // lane l of wavefront w: query 16 w + (l & 15), lane group g = l >> 4
       const int q2 = wave * kQPerWave + (lane & (kQPerWave - 1));
       const int g = lane >> 4;
-      const bool mine2 = q2 < T.count && qmode[q2] == kQueryNormal &&
-                         cnt[q2] <= (uint32_t)kStage && fusable;
-      const int nq = mine2 ? (int)cnt[q2] : 0;
+      const bool mine2 = CSR ? csr_ok
+                             : q2 < T.count && qmode[q2] == kQueryNormal &&
+                                   cnt[q2] <= (uint32_t)kStage && fusable;
+      const int nq = mine2 && !CSR ? (int)cnt[q2] : 0;
       const int64_t kb = pd.k_begin;
       const int64_t qi2 = qidx[q2];
       // per chunk row: (|w^|^2, bound norm, rounding bound) -- the record
@@ -1186,13 +1280,18 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
           // this query's hits in the chunk (the row is in ascending window
           // position; each lane resumes where the last chunk left it)
           uint64_t hmask = 0ull;
-          for (; cur < nq; cur += 4) {
-            const int v = hits_v[q2][cur];
-            if (v >= c0 + nr) break;
-            hmask |= 1ull << (v - c0);
+          if constexpr (CSR) {
+            static_assert(kBfRows == 32, "a chunk's hits are one word of the bitmap");
+            hmask = mine2 ? hit_bits[q2][c0 / 32] : 0u;
+          } else {
+            for (; cur < nq; cur += 4) {
+              const int v = hits_v[q2][cur];
+              if (v >= c0 + nr) break;
+              hmask |= 1ull << (v - c0);
+            }
+            hmask |= shfl_xor_u64(hmask, 16);
+            hmask |= shfl_xor_u64(hmask, 32);
           }
-          hmask |= shfl_xor_u64(hmask, 16);
-          hmask |= shfl_xor_u64(hmask, 32);
           // FP8: the scale and the rounding-error bound of the row whose
           // terms this thread works out below, read beside the copies
           float f8s = 1.0f, f8e = 0.0f;
@@ -1396,7 +1495,20 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
           for (int u = 0; u < 8; ++u) wcur[u] = wnext[u];
         }
       }
-      if (g == 0 && q2 < T.count) {  // lane group 0 holds the query's selection
+      if constexpr (CSR) {
+        if (g == 0 && q2 < T.count) {
+          if (csr_len == 0 || (mine2 && cert)) {
+            write_match_to(A.ratio, A.best_idx, A.best_dist, A.second_dist, qi2, best, false);
+          } else {
+            const unsigned long long at = atomicAdd(A.rest_count, 1ull);
+            A.rest[at] = (uint32_t)qi2;
+          }
+        }
+        // rows listed for what they are, not for their bounds
+        const uint32_t n_long =
+            (uint32_t)__popcll(ballot(g == 0 && q2 < T.count && csr_len > 0 && !mine2));
+        if (lane == 0) atomicAdd(&tile_stats[7], n_long);
+      } else if (g == 0 && q2 < T.count) {  // lane group 0 holds the query's selection
         const bool empty = qmode[q2] == kQueryEmpty;
         A.qrec[qi2] = query_record(empty ? 0u : cnt[q2], A.ratio, best, (mine2 && cert) || empty);
         if (mine2 && !cert) {
@@ -1404,7 +1516,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
           A.rest[at] = (uint32_t)qi2;
         }
       }
-      const uint32_t n_rank = (uint32_t)__popcll(ballot(mine2 && g == 0));
+      const uint32_t n_rank = (uint32_t)__popcll(ballot(mine2 && g == 0 && (!CSR || csr_len > 0)));
       const uint32_t n_unc = (uint32_t)__popcll(ballot(mine2 && g == 0 && !cert));
       const uint32_t n_ev = wave_sum_u32(evals);
       if (lane == 0) {
@@ -1418,7 +1530,13 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 ? 4 : MODE != kStabCoun
     // written per tile, summed on the host when they are asked for
     // (the BF16 phase adds its counters after its last barrier: one more)
     if (!FUSE || RED || !(fusable && total_len > 0)) __syncthreads();
-    if (A.tile_counts && tid == 0) {
+    if (CSR) {
+      if (A.match_stats && tid < 4) {
+        // rows ranked, uncertified, listed otherwise, exact distances
+        const uint32_t c = tile_stats[tid == 0 ? 4 : tid == 1 ? 5 : tid == 2 ? 7 : 6];
+        if (c) atomicAdd(&A.match_stats[tid], (unsigned long long)c);
+      }
+    } else if (A.tile_counts && tid == 0) {
       const uint64_t nb = tile_stats[2];
       unsigned long long* tc = A.tile_counts + (int64_t)tile * kTileCounts;
       tc[0] = (unsigned long long)tile_stats[0] + nb * (uint64_t)pd.n;
@@ -1838,9 +1956,16 @@ hipError_t launch_stab_tiles(const StabArgs& a, int grid, int mode, int chunk, h
   if (a.num_tiles == 0) return hipSuccess;
   if (grid > 0 && !a.queue) return hipErrorInvalidValue;
   if (mode != kStabCount && (!a.desc1 || !a.desc2 || !a.best_idx || !a.best_dist ||
-                             !a.second_dist || !a.rest || !a.qrec))
+                             !a.second_dist || !a.rest || (!a.qrec && mode != kCsrBF16)))
     return hipErrorInvalidValue;
-  if (mode == kStabBF16 && (!a.codes1 || !a.codes2)) return hipErrorInvalidValue;
+  if ((mode == kStabBF16 || mode == kCsrBF16) && (!a.codes1 || !a.codes2))
+    return hipErrorInvalidValue;
+  if (mode == kCsrBF16) {
+    if (!a.rest_count || !a.tile_wide || !a.row_offsets) return hipErrorInvalidValue;
+    launch_stab_mode<kCsrBF16, 256>(
+        a, grid, dim3(grid > 0 && grid < a.num_tiles ? grid : a.num_tiles), s);
+    return hipGetLastError();
+  }
   // (FP8: the image-2 pointers are read only through window records, so they
   // may be NULL when image 2 is empty; the entry point checks them otherwise)
   const dim3 g(grid > 0 ? (grid < a.num_tiles ? grid : a.num_tiles) : a.num_tiles);
