@@ -246,27 +246,57 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int off) {
   return ((uint64_t)hi << 32) | lo;
 }
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-  #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) v += __shfl_xor(v, off);
+// Reductions over the wavefront (uniform results), over each row of 16 lanes
+// and inclusive sums, by DPP: a step is one vector instruction, where a shuffle
+// through LDS takes a hundred cycles.  Lanes that have no neighbour in a step
+// get `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t none, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+template <class OP>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t v, uint32_t none, OP op) {
+  v = op(v, dpp<0xB1, 0xF>(none, v));   // quad [1,0,3,2]
+  v = op(v, dpp<0x4E, 0xF>(none, v));   // quad [2,3,0,1]
+  v = op(v, dpp<0x141, 0xF>(none, v));  // half-row mirror
+  v = op(v, dpp<0x140, 0xF>(none, v));  // row mirror
   return v;
 }
 
+template <class OP>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t none, OP op) {
+  v = row_reduce(v, none, op);
+  // rows 1 and 3 take lane 15 of the row below, rows 2 and 3 lane 31; lane 63
+  // ends with all rows
+  v = op(v, dpp<0x142, 0xA>(none, v));
+  v = op(v, dpp<0x143, 0xC>(none, v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+struct OpSum {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; }
+};
+struct OpMin {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
+};
+struct OpMax {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
+};
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_reduce(v, 0u, OpSum()); }
 __device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
-  #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t o = __shfl_xor(v, off);
-    v = o < v ? o : v;
-  }
-  return v;
+  return wave_reduce(v, 0xFFFFFFFFu, OpMin());
 }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return wave_reduce(v, 0u, OpMax()); }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-  #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const uint32_t o = __shfl_xor(v, off);
-    v = o > v ? o : v;
-  }
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += dpp<0x111, 0xF>(0u, v);  // one, two, four and eight lanes below, in the row
+  v += dpp<0x112, 0xF>(0u, v);
+  v += dpp<0x114, 0xF>(0u, v);
+  v += dpp<0x118, 0xF>(0u, v);
+  v += dpp<0x142, 0xA>(0u, v);
+  v += dpp<0x143, 0xC>(0u, v);
   return v;
 }
 
@@ -432,15 +462,17 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
 // up to kStage candidates in ascending j in the staging buffer.  The window
 // records of the tile are staged in LDS; wavefront w owns queries 16w..16w+15
 // (lane & 15), whose lines stay in registers, and tests them against four
-// records per step (lane >> 4, LDS broadcasts): angle test, FP64 test, and the
-// hit's slot from a ballot over the query's four lanes, so no atomics are
-// needed and every row lists its hits in ascending window position.
+// records per step (lane >> 4, LDS broadcasts): angle test and FP64 test.  A
+// hit sets a bit of its query's bitmap by window position; in kStabF32 it goes
+// to the query's list, in ascending window position, its slot from a ballot
+// over the query's four lanes.  Windows longer than kKeepJ have no bitmaps
+// (kStabCount lists the hits' j for those).
 //
 // FUSE: the same pass also selects every query's match (Sec. 4.3) from its
-// hit list while the list is still in LDS.  The hits are kept as 16-bit
-// window positions (their j from the window's j, kept in LDS for windows of
-// up to kKeepJ records); the window's descriptor rows are copied to LDS
-// kFuseRows at a time (over the record chunk buffers, dead by then), and four
+// hits while they are still in LDS (window positions; their j from the
+// window's j, kept in LDS for windows of up to kKeepJ records).  kStabF32: the
+// window's descriptor rows are copied to LDS kFuseRows at a time (over the
+// record chunk buffers and the window's order, dead by then), and four
 // lanes per query evaluate canonical FP32 distances of that query's hits in
 // the chunk, each lane resuming where the last chunk left it, and keep a
 // top-2, merged across the four lanes at the end.  Rows longer than kStage are
@@ -448,11 +480,11 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
 // queries, windows longer than kKeepJ) are marked for the fill pass to
 // rebuild, and those queries are listed for the listed-query match after the
 // CSR is complete; empty rows get their (-1, inf, inf) here.  The LDS and
-// register budget allows three workgroups per CU.  After the pair test every
-// wavefront works on its own 16 queries until the descriptor rows are staged,
-// so the tile needs only the barriers of the record and row chunks; its
-// counters gather in LDS and go to global memory once per tile (per-wavefront
-// global atomics on the same counters cost more than a barrier).
+// register budget allows three workgroups per CU.  Outside the order of the
+// window every wavefront works on its own 16 queries, so the tile needs only
+// the barriers of the record and row chunks and of the order; its counters
+// gather in LDS and go to global memory once per tile (per-wavefront global
+// atomics on the same counters cost more than a barrier).
 constexpr int kFuseRows = 48;
 constexpr int kFuseStride = 132;  // floats per staged row: 16-byte reads of rows hit distinct banks
 // LDS bytes of a round of CH window records (C, H, x y, eps, j).
@@ -527,7 +559,6 @@ constexpr int kBfPieces = kBfStride / 16;   // 16-byte pieces per row (the last 
 constexpr int kBfCopies = (kBfRows * kBfPieces + kWave - 1) / kWave;
 constexpr int kBfRowBytes = kBfCopies * kWave * 16;
 constexpr int kBfKeep = 3;
-static_assert(kBfRows % 16 == 0 && kBfRows <= 64, "the hit mask of a chunk is one 64-bit word");
 // MODE kStabFP8: the image-2 rows are 128 one-byte E4M3 codes c with a scale
 // s per row (w^ = s c), staged at a stride of 144 bytes (the padding
 // staggers the rows over the LDS banks) and decoded to BF16 for the MFMA,
@@ -714,6 +745,85 @@ __device__ __forceinline__ void bf_bounds(float at, float nb, float q_nb, float 
               dlo, dhi);
 }
 
+// The order by j of a tile's window of W <= kKeepJ records with distinct j:
+// rank[v] for every window position and the j in ascending order.  The window's
+// j are dealt to kOrderBuckets buckets over their span (the map is monotone),
+// the buckets are laid out one after the other, and a record's rank is its
+// bucket's start plus the smaller j in the bucket: about one compare each for
+// scattered j, and never more than the window.  scratch: the j by bucket
+// [kKeepJ], then counts, cursors and starts of the buckets; counts and cursors
+// are zero at the start.  A barrier goes between two of the three passes.
+constexpr int kOrderBuckets = 256;
+constexpr int kOrderBytes = kKeepJ * 6;      // rank and sorted j
+constexpr int kBruteBytes = kWaves * kStage * 4;  // kStabCount: a row per wavefront
+constexpr int kRankWords = kKeepJ / 32 + 1;  // bitmap row: + 1 puts rows in different banks
+constexpr int kRankBytes = kTileQ * kRankWords * 4;
+constexpr int kWordsPer = kKeepJ / 32 / 4;   // bitmap words of each of a row's four threads
+static_assert((kKeepJ + 3 * kOrderBuckets + 1) * 4 <= kRankBytes, "scratch of the order");
+static_assert(kOrderBuckets == 4 * kWave, "four buckets per lane");
+
+struct BucketMap {
+  int32_t lo;
+  float scale;
+  __device__ __forceinline__ explicit BucketMap(const uint32_t* span) {
+    lo = (int32_t)~span[0];
+    scale = (float)kOrderBuckets / ((float)((int32_t)span[1] - lo) + 1.0f);
+  }
+  __device__ __forceinline__ int operator()(int32_t j) const {
+    const int b = (int)((float)(j - lo) * scale);
+    return b < kOrderBuckets ? b : kOrderBuckets - 1;
+  }
+};
+
+__device__ __forceinline__ void order_count(const int32_t* sJ, int W, const uint32_t* span,
+                                            uint32_t* scratch, int tid) {
+  const BucketMap bucket(span);
+  for (int v = tid; v < W; v += kThreads) atomicAdd(&scratch[kKeepJ + bucket(sJ[v])], 1u);
+}
+
+__device__ __forceinline__ void order_place(const int32_t* sJ, int W, const uint32_t* span,
+                                            uint32_t* scratch, int tid) {
+  const BucketMap bucket(span);
+  const int lane = lane_id();
+  uint32_t* cursor = scratch + kKeepJ + kOrderBuckets;
+  uint32_t* start = cursor + kOrderBuckets;
+  // every wavefront scans the counts and writes the same starts, so that it
+  // can go on without a barrier
+  uint32_t c[4];
+  #pragma unroll
+  for (int u = 0; u < 4; ++u) c[u] = scratch[kKeepJ + 4 * lane + u];
+  const uint32_t own = c[0] + c[1] + c[2] + c[3];
+  uint32_t b = wave_scan_u32(own) - own;
+  #pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    start[4 * lane + u] = b;
+    b += c[u];
+  }
+  if (lane == kWave - 1) start[kOrderBuckets] = b;
+  wave_sync_lds();
+  for (int v = tid; v < W; v += kThreads) {
+    const int32_t j = sJ[v];
+    const int k = bucket(j);
+    scratch[start[k] + atomicAdd(&cursor[k], 1u)] = (uint32_t)j;
+  }
+}
+
+__device__ __forceinline__ void order_rank(const int32_t* sJ, int W, const uint32_t* span,
+                                           const uint32_t* scratch, uint16_t* rank,
+                                           int32_t* sorted, int tid) {
+  const BucketMap bucket(span);
+  const uint32_t* start = scratch + kKeepJ + 2 * kOrderBuckets;
+  for (int v = tid; v < W; v += kThreads) {
+    const int32_t j = sJ[v];
+    const int k = bucket(j);
+    const uint32_t s = start[k], e = start[k + 1];
+    uint32_t r = s;
+    for (uint32_t u = s; u < e; ++u) r += (int32_t)scratch[u] < j ? 1u : 0u;
+    rank[v] = (uint16_t)r;
+    sorted[r] = j;
+  }
+}
+
 // MODE: kStabCount (count and park rows), kStabF32 (FP32 selection fused),
 // kStabBF16 / kStabFP8 (BF16 or FP8 image-2 rows: MFMA bounds with an exact
 // FP32 re-rank, fused), or kCsrBF16: the BF16 selection over a caller's CSR.
@@ -731,6 +841,17 @@ __device__ __forceinline__ void bf_bounds(float at, float nb, float q_nb, float 
 // (a dense entry list in LDS, FP64 bounds per entry, one thread per query for
 // the selection) took 205 us for 60000 queries with 60 candidates each, this
 // one 57.
+//
+// Parked rows: a row's hits are known by window position and have to leave in
+// ascending j.  The window's order by j is worked out once per tile
+// (order_count, order_place, order_rank below: a bucket sort over the span of
+// the window's j, O(window)); a row's hits then set bits by rank in a bitmap,
+// and its four threads write the words in turn, from the places that the bits
+// before them give.  (Ranking every row's hits against each other took 12400
+// cycles of a tile's 59000 at 31 hits per row and 41900 of 161000 at 90; the
+// order takes 3400 whatever the rows, the bitmaps 5000 and 20000.  The tile pass
+// went from 87 to 81 us at six pairs of 20000 keypoints, from 137 to 113 at one
+// of 60000 with FP8 rows, and the counting pass from 54 to 44.6 there.)
 template <bool PERSIST, int MODE, int CH>
 __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4 : MODE != kStabCount ? 3 : 2) void k_stab_tile(StabArgs A) {
   constexpr bool FUSE = MODE != kStabCount;
@@ -738,6 +859,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
   constexpr bool BF = MODE == kStabBF16 || CSR;  // BF16 rows of both images
   // BF16 / FP8: MFMA bounds and an exact re-rank on the masters
   constexpr bool RED = BF || MODE == kStabFP8;
+  // hits by window position in bitmaps (kStabF32 lists them)
+  constexpr bool BITS = RED || !FUSE;
   // record chunk (sC, sH, sXY, sE; sJ too unless FUSE keeps the window's j
   // in sJ_keep), reused for descriptor rows in the match phase
   constexpr int kRecRaw = FUSE ? rec_bytes(CH) - CH * 4 : rec_bytes(CH);
@@ -745,30 +868,50 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
                            : BF                ? red_scratch(kBfKeep)
                            : MODE == kStabFP8  ? red_scratch(kF8Keep)
                                                : 0;
-  constexpr int kRaw = kMatchRaw > kRecRaw || CSR ? kMatchRaw : kRecRaw;
+  // the window's order by j is kept there after the pair test; in kStabF32 its
+  // scratch (then the bitmaps by rank) lies behind the record chunk, elsewhere
+  // it is an array of its own
+  constexpr bool kScratchInRaw = MODE == kStabF32;
+  constexpr int kOrderRaw =
+      CSR     ? 0
+      : !FUSE ? kOrderBytes + kBruteBytes
+      : kScratchInRaw ? (kRecRaw > kOrderBytes ? kRecRaw : kOrderBytes) + kRankBytes
+                      : kOrderBytes;
+  constexpr int kPairRaw = CSR ? 0 : kRecRaw > kOrderRaw ? kRecRaw : kOrderRaw;
+  constexpr int kRaw = kMatchRaw > kPairRaw ? kMatchRaw : kPairRaw;
   __shared__ __attribute__((aligned(16))) unsigned char raw[kRaw];
   // BF16 / FP8: the window's reduced rows, kBfRows at a time (the first
   // chunk is copied in while the pair test runs)
   __shared__ __attribute__((aligned(16)))
   uint8_t bfrows[BF ? kBfRowBytes : MODE == kStabFP8 ? kF8RowBytes : 16];
-  __shared__ int32_t sJ_keep[FUSE ? kKeepJ : 1];
+  __shared__ int32_t sJ_store[FUSE ? kKeepJ : 1];
   uint32_t* sC = reinterpret_cast<uint32_t*>(raw);
   uint32_t* sH = sC + CH;
   float2* sXY = reinterpret_cast<float2*>(sH + CH);
   float* sE = reinterpret_cast<float*>(sXY + CH);
   int32_t* sJ = reinterpret_cast<int32_t*>(sE + CH);  // not FUSE
-  // hit lists: image-2 indices, or (FUSE) 16-bit window positions
-  __shared__ int32_t hits[FUSE ? 1 : kTileQ][FUSE ? 1 : kStage + 1];  // +1: rows in different banks
-  __shared__ uint16_t hits_v[FUSE && !CSR ? kTileQ : 1][FUSE && !CSR ? kStage + 2 : 1];
-  // kCsrBF16: the hits of every query by window position
-  __shared__ uint32_t hit_bits[CSR ? kTileQ : 1][CSR ? kKeepJ / 32 + 1 : 1];
-  // image-2 index of hit u of query q
-  const auto hit_j = [&](int q, uint32_t u) -> int32_t {
-    if constexpr (FUSE)
-      return sJ_keep[hits_v[q][u]];
-    else
-      return hits[q][u];
-  };
+  // kStabF32: the hits of every query as 16-bit window positions
+  __shared__ uint16_t hits_v[MODE == kStabF32 ? kTileQ : 1][MODE == kStabF32 ? kStage + 2 : 1];
+  // the others: the hits of every query by window position
+  __shared__ uint32_t bits_store[RED ? kTileQ * kRankWords : 1];
+  __shared__ uint32_t rank_store[RED && !CSR ? kTileQ * kRankWords : 1];
+  // kStabCount: the hits' image-2 indices where the window is longer than
+  // kKeepJ (+ 1: rows in different banks), else the window's j and the bitmaps
+  constexpr int kHitRow = kStage + 1;
+  constexpr int kCountWords = kTileQ * kHitRow;
+  static_assert(kCountWords >= 2 * kTileQ * kRankWords + kKeepJ, "bitmaps and the window's j");
+  __shared__ uint32_t count_store[FUSE ? 1 : kCountWords];
+  int32_t* hits = reinterpret_cast<int32_t*>(count_store);
+  uint32_t* bit_rows = FUSE ? bits_store : count_store;
+  const auto hit_bits = [&](int q) { return bit_rows + q * kRankWords; };
+  uint32_t* scratch = kScratchInRaw ? reinterpret_cast<uint32_t*>(raw + kRaw - kRankBytes)
+                      : FUSE        ? rank_store
+                                    : count_store + kTileQ * kRankWords;
+  int32_t* sJ_keep = FUSE ? sJ_store
+                          : reinterpret_cast<int32_t*>(count_store + 2 * kTileQ * kRankWords);
+  uint16_t* j_rank = reinterpret_cast<uint16_t*>(raw);          // by window position
+  int32_t* j_sorted = reinterpret_cast<int32_t*>(raw + kKeepJ * 2);  // by rank
+  __shared__ uint32_t j_span[2];  // the window's largest ~j and largest j
   constexpr int kLines = CSR ? 1 : kTileQ;
   __shared__ double qa[kLines], qb[kLines], qc[kLines], qn[kLines];
   __shared__ uint32_t qk[kTileQ], qmode[kTileQ], cnt[kTileQ];
@@ -819,6 +962,12 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       qidx[lane] = tq.i;
       cnt[lane] = 0;
       if (lane < kTileCounts) tile_stats[lane] = 0u;
+      if (lane < 2) j_span[lane] = 0u;
+    }
+    if constexpr (!CSR) {
+      for (int k = tid; k < 2 * kOrderBuckets; k += kThreads) scratch[kKeepJ + k] = 0u;
+      if constexpr (BITS)
+        for (int k = tid; k < kTileQ * kRankWords; k += kThreads) bit_rows[k] = 0u;
     }
     {
       const TileWindow* w = A.windows + tile;
@@ -850,11 +999,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
     // triangle inequality on the circle of keys) cannot meet any of them and
     // is skipped without the per-query test
     uint32_t kmn = line_live ? lkey : 0xFFFFFFFFu, kmx = line_live ? lkey : 0u;
-    #pragma unroll
-    for (int off = 1; off < kQPerWave; off <<= 1) {
-      kmn = min(kmn, (uint32_t)__shfl_xor((int)kmn, off));
-      kmx = max(kmx, (uint32_t)__shfl_xor((int)kmx, off));
-    }
+    kmn = row_reduce(kmn, 0xFFFFFFFFu, OpMin());
+    kmx = row_reduce(kmx, 0u, OpMax());
     const uint32_t kmid = kmn + ((kmx - kmn) >> 1);
     const uint64_t khalf = ((uint64_t)(kmx - kmn) + 1u) >> 1;
     uint32_t lcnt = 0;
@@ -880,7 +1026,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         }
       }
       #pragma unroll
-      for (int k = g; k <= kKeepJ / 32; k += 4) hit_bits[lq][k] = 0u;
+      for (int k = g; k < kRankWords; k += 4) hit_bits(lq)[k] = 0u;
       // the slots that hold records, for every lane's entries
       uint64_t filled = ballot(slot_pref[lane + 1] > slot_pref[lane]);
       constexpr int kFly = 4;  // entries of a lane whose gathers are in flight together
@@ -903,11 +1049,11 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         }
         #pragma unroll
         for (int u = 0; u < kFly; ++u)
-          if (e0 + 4 * u < n && v[u] >= 0) atomicOr(&hit_bits[lq][v[u] >> 5], 1u << (v[u] & 31));
+          if (e0 + 4 * u < n && v[u] >= 0) atomicOr(&hit_bits(lq)[v[u] >> 5], 1u << (v[u] & 31));
       }
       wave_sync_lds();
       int set = 0;
-      for (int k = g; k < kKeepJ / 32; k += 4) set += __popc(hit_bits[lq][k]);
+      for (int k = g; k < kKeepJ / 32; k += 4) set += __popc(hit_bits(lq)[k]);
       set += __shfl_xor(set, 16);
       set += __shfl_xor(set, 32);
       csr_ok = here && set == n;
@@ -958,6 +1104,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
     }
     for (int64_t base = 0; !CSR && base < total_len; base += CH) {
       const int clen = (int)(total_len - base < CH ? total_len - base : CH);
+      uint32_t jn = 0u, jx = 0u;  // largest ~j and j of this thread's records
       for (int v = tid; v < clen; v += kThreads) {
         const int64_t virt = base + v;
         int s = 0;  // last slot with slot_pref[s] <= virt
@@ -969,10 +1116,22 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         sH[v] = A.rH[pos];
         sXY[v] = A.rxy[pos];
         sE[v] = A.reps[pos];
-        if (!FUSE)
+        if (FUSE ? virt < kKeepJ : fusable) {
+          const int32_t j = A.rj[pos];
+          sJ_keep[virt] = j;
+          jn = max(jn, ~(uint32_t)j);
+          jx = max(jx, (uint32_t)j);
+        } else if (!FUSE) {
           sJ[v] = A.rj[pos];
-        else if (virt < kKeepJ)
-          sJ_keep[virt] = A.rj[pos];
+        }
+      }
+      if (fusable && wave * kWave < clen) {
+        jn = wave_max_u32(jn);
+        jx = wave_max_u32(jx);
+        if (lane == 0) {
+          atomicMax(&j_span[0], jn);
+          atomicMax(&j_span[1], jx);
+        }
       }
       __syncthreads();
       if constexpr (RED) {
@@ -985,6 +1144,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             bf16_stage(A, 0, nr0, pd.k_begin, sJ_keep, bfrows, wave, lane);
         }
       }
+      if (fusable && base + CH >= total_len)
+        order_count(sJ_keep, (int)total_len, j_span, scratch, tid);
       if (any_live) {
         // this wave's 16 queries (lane & 15) against four records per step
         // (lane >> 4), over the records of each group of 64 that can meet
@@ -1023,13 +1184,18 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             const uint64_t all_hits = am & ballot(fp_ok);
             const bool hit = line_live & (pick < kWave) & key_ok & fp_ok;  // this lane's bit
             const uint64_t hm = all_hits & same_query;
-            if (hit) {
+            if (BITS && fusable) {
+              if (hit) {
+                const uint32_t v = (uint32_t)base + (uint32_t)r;
+                atomicOr(&hit_bits(lq)[v >> 5], 1u << (v & 31u));
+              }
+            } else if (!RED && hit) {
               const uint32_t slot = lcnt + lanes_below(hm);
               if (slot < (uint32_t)kStage) {
                 if (FUSE)
                   hits_v[lq][slot] = (uint16_t)(base + r);
                 else
-                  hits[lq][slot] = sJ[r];
+                  hits[lq * kHitRow + slot] = sJ[r];
               }
             }
             lcnt += (uint32_t)__popcll(hm);
@@ -1043,9 +1209,10 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
 
     // queries whose line misses the epipole too far: exact scan of the pair
     uint32_t brute = 0;
-    for (int qq = 0; qq < kQPerWave; ++qq) {
-      const int q = wave * kQPerWave + qq;
-      if (qmode[q] != kQueryBrute) continue;
+    int32_t* brute_row = reinterpret_cast<int32_t*>(raw + kOrderBytes) + wave * kStage;  // not FUSE
+    for (uint64_t bm = ballot(lane < kQPerWave && qmode[lq] == kQueryBrute); bm != 0ull;
+         bm &= bm - 1ull) {
+      const int q = wave * kQPerWave + (int)__builtin_ctzll(bm);
       const double a = qa[q], b = qb[q], c = qc[q], nrm = qn[q];
       uint32_t c0 = 0;
       brute += 1;
@@ -1059,15 +1226,21 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         const uint64_t m = ballot(hit);
         if (!FUSE && hit) {  // FUSE: counted only, the row is rebuilt by the fill pass
           const uint32_t slot = c0 + lanes_below(m);
-          if (slot < (uint32_t)kStage) hits[q][slot] = A.rj[pos];
+          if (slot < (uint32_t)kStage) brute_row[slot] = A.rj[pos];
         }
         c0 += (uint32_t)__popcll(m);
       }
       if (lane == 0) cnt[q] = c0;
+      if (!FUSE && c0 <= (uint32_t)kStage) {  // a short row is sorted and parked here
+        for (int t = (int)c0 + lane; t < kStage; t += kWave) brute_row[t] = INT32_MAX;
+        wave_sync_lds();
+        wave_sort_lds(brute_row, kStage);
+        for (int t = lane; t < (int)c0; t += kWave) A.staging[qidx[q] * kStage + t] = brute_row[t];
+        wave_sync_lds();
+      }
     }
-    // From here to the match phase every wavefront works on its own 16
-    // queries only (their hits and counts were written by this wavefront),
-    // so no barrier is needed.
+    // The hits and counts of a wavefront's 16 queries were written by it, so
+    // they are read without a barrier.
     {
       // the tile's counters gather in LDS; one thread adds them to the
       // query's counters once every wavefront has passed a later barrier
@@ -1097,49 +1270,126 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
 
     // FUSE: four threads per query select its match
     const int q = tid >> 2, part = tid & 3;
-    const bool mine = FUSE && q < T.count && qmode[q] == kQueryNormal &&
+    const bool mine = q < T.count && qmode[q] == kQueryNormal &&
                       cnt[q] <= (uint32_t)kStage && fusable;
 
-    // row lengths, and short rows parked in ascending j: four threads per
-    // row, each placing a quarter of its hits by rank (the j of a row are
-    // distinct, so a hit's place is the number of smaller hits); a thread
-    // ranks up to four of its hits in one pass over the row
+    // row lengths, and short rows parked in ascending j
     // (the fused modes write the row length with the match, in one record)
     if constexpr (!CSR) {
-    if (!FUSE && part == 0 && q < T.count)
-      A.counts[qidx[q]] = qmode[q] == kQueryEmpty ? 0u : cnt[q];
-    {
+      if (!FUSE && part == 0 && q < T.count)
+        A.counts[qidx[q]] = qmode[q] == kQueryEmpty ? 0u : cnt[q];
       const uint32_t n = q < T.count && qmode[q] != kQueryEmpty ? cnt[q] : 0u;
-      // FUSE keeps only the hits of normal queries in fused windows; other
-      // short rows are marked (first entry -1) for the fill pass to rebuild
-      const bool here = !FUSE || (fusable && qmode[q] == kQueryNormal);
       int32_t* dst = A.staging + qidx[q] * kStage;
-      if (n <= (uint32_t)kStage && here) {
-        for (uint32_t t0 = part; t0 < n; t0 += 16) {
-          int32_t v[4];
-          uint32_t r[4];
-          #pragma unroll
-          for (int m = 0; m < 4; ++m) {
-            v[m] = t0 + 4 * m < n ? hit_j(q, t0 + 4 * m) : INT32_MIN;
-            r[m] = 0;
-          }
-          #pragma unroll 4
-          for (uint32_t u = 0; u < n; ++u) {
-            const int32_t h = hit_j(q, u);
+      if (fusable && total_len > 0) {
+        order_place(sJ_keep, (int)total_len, j_span, scratch, tid);
+        __syncthreads();
+        order_rank(sJ_keep, (int)total_len, j_span, scratch, j_rank, j_sorted, tid);
+        __syncthreads();
+        const int words = ((int)total_len + 31) >> 5;
+        uint32_t* bits = scratch + q * kRankWords;
+        for (int k = part; k < words; k += 4) bits[k] = 0u;
+        wave_sync_lds();
+        if (mine) {
+          if constexpr (BITS) {
+            uint32_t w[kWordsPer];
             #pragma unroll
-            for (int m = 0; m < 4; ++m) r[m] += h < v[m] ? 1u : 0u;
+            for (int i = 0; i < kWordsPer; ++i) w[i] = hit_bits(q)[4 * i + part];
+            #pragma unroll
+            for (int i = 0; i < kWordsPer; ++i) {
+              if (4 * i >= words) break;
+              const uint16_t* of = j_rank + (4 * i + part) * 32;
+              while (w[i] != 0u) {  // four hits at a time, their ranks read together
+                uint32_t r[4];
+                bool has[4];
+                #pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                  has[m] = w[i] != 0u;
+                  r[m] = of[__builtin_ctz(w[i] | 0x80000000u)];
+                  w[i] &= w[i] - 1u;
+                }
+                #pragma unroll
+                for (int m = 0; m < 4; ++m)
+                  if (has[m]) atomicOr(&bits[r[m] >> 5], 1u << (r[m] & 31u));
+              }
+            }
+          } else {
+            #pragma unroll 4
+            for (uint32_t u = part; u < n; u += 4) {
+              const uint32_t r = j_rank[hits_v[q][u]];
+              atomicOr(&bits[r >> 5], 1u << (r & 31u));
+            }
           }
-          #pragma unroll
-          for (int m = 0; m < 4; ++m)
-            if (t0 + 4 * m < n) dst[r[m]] = v[m];
         }
-      } else if (n > 0 && n <= (uint32_t)kStage && part == 0) {
+        wave_sync_lds();
+        // words k = part (mod 4) are the thread's, so that the row's four
+        // threads write to neighbouring places
+        uint32_t w[kWordsPer];
+        #pragma unroll
+        for (int i = 0; i < kWordsPer; ++i)
+          w[i] = mine && 4 * i + part < words ? bits[4 * i + part] : 0u;
+        uint32_t row = 0u;  // the row's entries in words [0, 4 i)
+        #pragma unroll
+        for (int i = 0; i < kWordsPer; ++i) {
+          if (4 * i >= words) break;
+          const uint32_t own = (uint32_t)__popc(w[i]);
+          uint32_t sum = own;  // over the row's threads up to this one
+          const uint32_t t1 = dpp<0x111, 0xF>(0u, sum);
+          sum += part >= 1 ? t1 : 0u;
+          const uint32_t t2 = dpp<0x112, 0xF>(0u, sum);
+          sum += part >= 2 ? t2 : 0u;
+          int32_t* to = dst + row + (sum - own);
+          row += dpp<0xFF, 0xF>(0u, sum);  // the sum of the last of the four
+          const int32_t* of = j_sorted + (4 * i + part) * 32;
+          while (w[i] != 0u) {  // four hits at a time
+            int32_t j[4];
+            bool has[4];
+            #pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              has[m] = w[i] != 0u;
+              j[m] = of[__builtin_ctz(w[i] | 0x80000000u)];
+              w[i] &= w[i] - 1u;
+            }
+            #pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              if (has[m]) to[m] = j[m];
+            }
+            to += 4;
+          }
+        }
+      }
+      if constexpr (!FUSE) {
+        // longer windows: four threads per row, each placing a quarter of its
+        // hits by rank (the j of a row are distinct, so a hit's place is the
+        // number of smaller hits); a thread ranks up to four of its hits in one
+        // pass over the row
+        if (!fusable && n <= (uint32_t)kStage && qmode[q] == kQueryNormal) {
+          const int32_t* row = hits + q * kHitRow;
+          for (uint32_t t0 = part; t0 < n; t0 += 16) {
+            int32_t v[4];
+            uint32_t r[4];
+            #pragma unroll
+            for (int m = 0; m < 4; ++m) {
+              v[m] = t0 + 4 * m < n ? row[t0 + 4 * m] : INT32_MIN;
+              r[m] = 0;
+            }
+            #pragma unroll 4
+            for (uint32_t u = 0; u < n; ++u) {
+              const int32_t h = row[u];
+              #pragma unroll
+              for (int m = 0; m < 4; ++m) r[m] += h < v[m] ? 1u : 0u;
+            }
+            #pragma unroll
+            for (int m = 0; m < 4; ++m)
+              if (t0 + 4 * m < n) dst[r[m]] = v[m];
+          }
+        }
+      } else if (n > 0 && n <= (uint32_t)kStage && !mine && part == 0) {
+        // rows that are not kept (brute-force queries, windows that are not
+        // fused) are marked for the fill pass to rebuild
         dst[0] = kRowNotParked;
       }
-    }
 
-    if (FUSE) {
-      if (part == 0 && q < T.count) {
+      if (FUSE && part == 0 && q < T.count) {
         const uint32_t mode = qmode[q];
         if (mode != kQueryEmpty &&
             (mode != kQueryNormal || (cnt[q] <= (uint32_t)kStage && !fusable))) {
@@ -1147,7 +1397,6 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
           A.rest[at] = (uint32_t)qidx[q];
         }
       }
-    }
     }
     if constexpr (MODE == kStabF32) {
       const int nq = mine ? (int)cnt[q] : 0;
@@ -1162,13 +1411,12 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       }
       Top2 best;
       int cur = part;
-      // the record chunk is dead since the pair test's last barrier, so the
-      // first rows go in without one
       if (fusable && total_len > 0) {
         const int wlen = (int)total_len;
         for (int c0 = 0; c0 < wlen; c0 += kFuseRows) {
           const int nr = wlen - c0 < kFuseRows ? wlen - c0 : kFuseRows;
-          if (c0 > 0) __syncthreads();  // the previous rows are no longer read
+          // the window's order (first) or the previous rows are no longer read
+          __syncthreads();
           fuse_stage(A, c0, nr, kb, sJ_keep, rows4, wave, lane);
           wait_lds_copies();
           __syncthreads();
@@ -1209,7 +1457,6 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       const bool mine2 = CSR ? csr_ok
                              : q2 < T.count && qmode[q2] == kQueryNormal &&
                                    cnt[q2] <= (uint32_t)kStage && fusable;
-      const int nq = mine2 && !CSR ? (int)cnt[q2] : 0;
       const int64_t kb = pd.k_begin;
       const int64_t qi2 = qidx[q2];
       // per chunk row: (|w^|^2, bound norm, rounding bound) -- the record
@@ -1262,7 +1509,6 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       const float q_nb = sqrtf(qn_part) * (1.0f + 2e-5f);
       const float q_db = sqrtf(qe_part) * (1.0f + 2e-5f) + 1e-30f;
       BfKeep<kKeep> st;
-      int cur = g;
       Top2 best;
       uint32_t evals = 0;
       bool cert = mine2;  // a tile without window records has only empty rows
@@ -1277,21 +1523,9 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             else
               bf16_stage(A, c0, nr, kb, sJ_keep, bfrows, wave, lane);
           }  // the first rows were started during the pair test
-          // this query's hits in the chunk (the row is in ascending window
-          // position; each lane resumes where the last chunk left it)
-          uint64_t hmask = 0ull;
-          if constexpr (CSR) {
-            static_assert(kBfRows == 32, "a chunk's hits are one word of the bitmap");
-            hmask = mine2 ? hit_bits[q2][c0 / 32] : 0u;
-          } else {
-            for (; cur < nq; cur += 4) {
-              const int v = hits_v[q2][cur];
-              if (v >= c0 + nr) break;
-              hmask |= 1ull << (v - c0);
-            }
-            hmask |= shfl_xor_u64(hmask, 16);
-            hmask |= shfl_xor_u64(hmask, 32);
-          }
+          // this query's hits in the chunk
+          static_assert(kBfRows == 32, "a chunk's hits are one word of the bitmap");
+          const uint32_t hmask = mine2 ? hit_bits(q2)[c0 / 32] : 0u;
           // FP8: the scale and the rounding-error bound of the row whose
           // terms this thread works out below, read beside the copies
           float f8s = 1.0f, f8e = 0.0f;
@@ -1349,7 +1583,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             }
           }
           __syncthreads();
-          if (ballot(hmask != 0ull) != 0ull) {
+          if (ballot(hmask != 0u) != 0ull) {
             // S^T = W^ Q^T on MFMA, for the row blocks where one of the
             // wave's queries has a hit (the others are never read).  Block
             // position m of block cb holds window row 16 cb + 4 (m & 3) +
@@ -1361,7 +1595,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             #pragma unroll
             for (int cb = 0; cb < kBfBlocks; ++cb) {
               acc[cb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
-              if (ballot(((hmask >> (16 * cb)) & 0xFFFFull) != 0ull) == 0ull) continue;
+              if (ballot(((hmask >> (16 * cb)) & 0xFFFFu) != 0u) == 0ull) continue;
               #pragma unroll
               for (int kk = 0; kk < 4; ++kk) {
                 bf16x8 a;
@@ -1382,7 +1616,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
             for (int cb = 0; cb < kBfBlocks; ++cb)
               #pragma unroll
               for (int i = 0; i < 4; ++i)
-                slots |= (uint32_t)((hmask >> (16 * cb + 4 * i + g)) & 1ull) << (4 * cb + i);
+                slots |= ((hmask >> (16 * cb + 4 * i + g)) & 1u) << (4 * cb + i);
             // the slots in a fixed order, a block's four row terms read
             // together; a slot without a hit leaves the state unchanged
             #pragma unroll
