@@ -15,9 +15,17 @@
 //      by construction, so no row is sorted;
 //   3. (match) the entries' descriptor rows, as BF16 (copies rounded once
 //      per call, or rounded on chip), are scored against the BF16 query rows
-//      on MFMA; every hit gets the approximate key |w^|^2 - 2 q^.w^, and a
-//      hit below the query's kPicks+1-th smallest key so far enters its list
-//      of the kPicks+1 smallest keys.
+//      on MFMA; every hit gets the approximate key |w^|^2 - 2 q^.w^, and each
+//      of a query's four lanes keeps the three smallest keys of its quarter of
+//      the entries, and the smallest key of the rest.  A query's twelve kept
+//      keys are merged into its kPicks+1 smallest at the end, the last one
+//      lowered to the smallest key that a lane did not keep.
+// (One list of six keys per query, extended hit by hit with the wavefront's
+// lanes, took a third of the time: 1810 us at six pairs of 50000 keypoints with
+// 1300 candidates per query, 1290 with the lanes' own lists, free of branches,
+// and the rows' write positions in lanes.  What bounds it now: the instructions
+// of 16 x 64 exact tests, appends and list steps per block, at three wavefronts
+// per SIMD; the row appends, 145 of a tile's 500 thousand cycles, most.)
 // The kPicks best keys of a query are re-ranked with canonical FP32 chains on
 // the FP32 rows.  The last kept key bounds every other candidate from below
 // (the rounding bound of the BF16 rows, of the MFMA accumulation and of the
@@ -51,12 +59,10 @@ constexpr int kSub = kSC / kL;                           // blocks per super-chu
 constexpr int kRS = 256 + 16;  // LDS bytes per BF16 row: fragment reads of 16 rows hit distinct banks
 constexpr int kQS = 132;       // floats per FP32 query row of the re-rank (rows start 4 banks apart)
 constexpr int kPicks = 5;      // exactly re-ranked candidates per query
-constexpr int kMergeMin = 16;  // more survivors than this: merged by wavefront minima
 constexpr int kQPerWave = kTileQ / kWaves;
 constexpr int kRowPer = kL * 32 / kThreads;  // 16-byte pieces of a block's rows per thread
 static_assert(kL == kWave && kQPerWave == 16, "one block row per lane, 16 queries per wavefront");
 static_assert(kRowPer == 8 && kThreads == 256, "row sums: eight rows per half-wavefront");
-static_assert(kPicks + 1 <= 16, "a query's kept keys are lanes 0 .. kPicks of the first DPP row");
 static_assert(kThreads * 4 == kSlabWords, "four bitmap words per thread in the prefix count");
 static_assert((kTileQ / 2) * kQS * 4 <= kL * kRS, "FP32 rows of half the queries fit the row area");
 static_assert((kTileQ / 2) * kPicks <= kThreads, "one pick per thread in the re-rank");
@@ -94,27 +100,10 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ float readlane_f(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
   const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, l);
   const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), l);
   return ((uint64_t)hi << 32) | lo;
-}
-
-__device__ __forceinline__ double readlane_d(double v, int l) {
-  return __longlong_as_double((long long)readlane_u64((uint64_t)__double_as_longlong(v), l));
-}
-
-// Value of the next lower lane within each row of 16 lanes (DPP row_shr:1;
-// lane 0 of a row keeps its own value).
-__device__ __forceinline__ int32_t row_shift_up(int32_t v) {
-  return __builtin_amdgcn_update_dpp(v, v, 0x111, 0xF, 0xF, false);
-}
-__device__ __forceinline__ float row_shift_up(float v) {
-  return __int_as_float(row_shift_up(__float_as_int(v)));
 }
 
 // Value of lane l ^ M (M < 32): DPP quad permutations for 1 and 2, the
@@ -327,22 +316,14 @@ __device__ __forceinline__ void stage_pre(const Rows& R, uint8_t* dst, float* nr
 }
 
 // One window entry in ascending j: its image-2 index and record.
+typedef __attribute__((address_space(1))) int32_t* GlobalInt;
+
 struct Entry {
   int32_t j;
   uint32_t C, H;
   float2 xy;
   float e;
 };
-
-// Signed-integer image of a float that keeps the order of non-NaN values
-// (negative values get their magnitude bits flipped).
-__device__ __forceinline__ int32_t order_key(float f) {
-  const int32_t b = __float_as_int(f);
-  return b >= 0 ? b : b ^ 0x7FFFFFFF;
-}
-__device__ __forceinline__ float order_key_inv(int32_t k) {
-  return __int_as_float(k >= 0 ? k : k ^ 0x7FFFFFFF);
-}
 
 // Minimum over the wavefront (uniform result): lanes take the minimum with a
 // neighbour's value by DPP, INT32_MAX standing in where no neighbour is given.
@@ -363,60 +344,34 @@ __device__ __forceinline__ float wave_max(float v) {
   return __int_as_float(-wave_min(-__float_as_int(v)));
 }
 
-// A 4 x 4 transpose of 16-lane rows across four registers: afterwards row g
-// of register r holds what row r of register g held (v_permlane32_swap swaps
-// the upper half of its first operand with the lower half of its second,
-// v_permlane16_swap the odd rows of its first with the even rows of its second).
-__device__ __forceinline__ void transpose_rows(float& r0, float& r1, float& r2, float& r3) {
-  auto s02 = __builtin_amdgcn_permlane32_swap(__float_as_uint(r0), __float_as_uint(r2), false, false);
-  auto s13 = __builtin_amdgcn_permlane32_swap(__float_as_uint(r1), __float_as_uint(r3), false, false);
-  auto s01 = __builtin_amdgcn_permlane16_swap(s02[0], s13[0], false, false);
-  auto s23 = __builtin_amdgcn_permlane16_swap(s02[1], s13[1], false, false);
-  r0 = __uint_as_float(s01[0]);
-  r1 = __uint_as_float(s01[1]);
-  r2 = __uint_as_float(s23[0]);
-  r3 = __uint_as_float(s23[1]);
-}
-
-// Merges a block's survivors into a query's kept list: lk / lj in lanes
-// 0 .. kK - 1 hold the list (ascending keys, +inf and -1 past its end), the
-// lanes of surv the survivors' keys kv and image-2 indices jv.  The kK
-// smallest keys of both are taken one at a time by wavefront minima and
-// leave lk / lj ascending; returns the largest kept key (+inf while fewer
-// than kK are kept).  Equal keys may be taken in any order.
-template <int kK>
-__device__ __forceinline__ float merge_list(float& lk, int32_t& lj, uint64_t surv, float kv,
-                                            int32_t jv) {
-  const int lane = lane_id();
-  constexpr int32_t kInf = 0x7F800000;  // order_key(+inf)
-  int32_t ca = order_key(lk);
-  int32_t cb = (surv >> lane) & 1ull ? order_key(kv) : INT32_MAX;
-  float nk = __builtin_inff();
-  int32_t nj = -1;
-  #pragma unroll 1
-  for (int r = 0; r < kK; ++r) {
-    const int32_t mn = wave_min(min(ca, cb));
-    if (mn >= kInf) break;  // uniform: nothing left
-    const uint64_t at_a = ballot(ca == mn);
-    int32_t js;
-    if (at_a) {
-      const int L = __builtin_ctzll(at_a);
-      js = __builtin_amdgcn_readlane(lj, L);
-      if (lane == L) ca = INT32_MAX;
-    } else {
-      const int L = __builtin_ctzll(ballot(cb == mn));
-      js = __builtin_amdgcn_readlane(jv, L);
-      if (lane == L) cb = INT32_MAX;
-    }
-    if (lane == r) {
-      nk = order_key_inv(mn);
-      nj = js;
-    }
+// The smallest keys among the entries that a lane has seen, in registers:
+// a[0] <= a[1] <= a[2] with their j (-1: none), and the smallest key among the
+// others.  A key that is not smaller than what is kept changes nothing but
+// `drop`; equal keys may be kept in any order.  No branches: a new key moves
+// through the four by medians.
+struct Kept {
+  float a[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
+  int32_t j[3] = {-1, -1, -1};
+  float drop = __builtin_inff();
+  __device__ __forceinline__ void add(float k, int32_t jk) {
+    const bool c0 = k < a[0], c1 = k < a[1], c2 = k < a[2];
+    drop = __builtin_amdgcn_fmed3f(a[2], drop, k);
+    a[2] = __builtin_amdgcn_fmed3f(a[1], a[2], k);
+    a[1] = __builtin_amdgcn_fmed3f(a[0], a[1], k);
+    a[0] = pick(c0, k, a[0]);
+    j[2] = pick(c1, j[1], pick(c2, jk, j[2]));
+    j[1] = pick(c0, j[0], pick(c1, jk, j[1]));
+    j[0] = pick(c0, jk, j[0]);
   }
-  lk = nk;
-  lj = nj;
-  return readlane_f(nk, kK - 1);
-}
+  __device__ __forceinline__ void settle() {
+    asm volatile(""
+                 : "+v"(a[0]), "+v"(a[1]), "+v"(a[2]), "+v"(drop), "+v"(j[0]), "+v"(j[1]), "+v"(j[2]));
+  }
+  template <typename T>
+  static __device__ __forceinline__ T pick(bool c, T x, T y) {
+    return __builtin_unpredictable(c) ? x : y;  // a select, not a branch
+  }
+};
 
 // Copies of the image-2 rows (A.wcodes2, A.wterms2, for the pairs pair_pre
 // picks) by PRE: kPreNone none (rounding on chip); kPreOnly the tiles of
@@ -435,7 +390,7 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
   uint32_t* wpref = reinterpret_cast<uint32_t*>(slab_raw + kSlabWords * 8);
   __shared__ uint32_t wsum[kWaves], n_entries;
   // one super-chunk of window entries
-  __shared__ int32_t lj[kSC];
+  __shared__ __attribute__((aligned(16))) int32_t lj[kSC];
   __shared__ uint32_t lC[kSC], lH[kSC];
   __shared__ float2 lXY[kSC];
   __shared__ float lE[kSC];
@@ -450,7 +405,8 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
   // BF16 query rows, then block rows, then FP32 query rows of the re-rank
   __shared__ __attribute__((aligned(16))) uint8_t raw[kRaw];
   __shared__ int64_t row_of[MATCH ? kSC : 1];  // global image-2 row of each entry, -1 past the end
-  __shared__ float w_norm[MATCH ? kL : 1];
+  // norms of the block rows: two buffers, read until the next block is staged
+  __shared__ __attribute__((aligned(16))) float w_norm[MATCH ? 2 * kL : 4];
   __shared__ float q_norm[kQ], q_err[kQ];
   __shared__ uint32_t max_nb, max_db;  // float bits of the largest window row terms
   __shared__ uint32_t n_cert, n_fallback;
@@ -529,28 +485,19 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
   // lane l < 16 holds query q0 + l's row start, its CSR write position and
   // (match) the largest kept key of its list -- read through readlane
   const int ql = q0 + (lane & (kQPerWave - 1));
-  const int64_t qp_o0 = q_o0[ql];
-  const uint32_t qp_len = q_len[ql];
-  uint32_t run[kQPerWave];  // hits so far of each query of the wavefront (uniform)
-  #pragma unroll
-  for (int qq = 0; qq < kQPerWave; ++qq) run[qq] = 0u;
+  GlobalInt row_at = (GlobalInt)(A.cols + q_o0[ql]);  // where the row of query q0 + (lane & 15) goes on
+  uint32_t row_left = q_len[ql];        // its entries from there on (past its end: wraps)
   // a CSR that fits the caller's buffer whole needs no check per hit
   const bool fits = A.row_offsets[A.n1] <= A.capacity;
-  float thr[kQPerWave];  // (match) the largest kept key of each query's list (uniform)
-  #pragma unroll
-  for (int qq = 0; qq < kQPerWave; ++qq) thr[qq] = __builtin_inff();
+  Kept kept;  // (match) of query q0 + (lane & 15), among the lane's quarter of the entries
   uint32_t badbits = 0u;  // matching a caller's CSR: queries whose row differs here
   // largest squared norm (and rounding error) of the window rows this thread summed
   float mx_n = 0.0f, mx_e = 0.0f;
 
-  // the MFMA's A operand: BF16 rows of this wavefront's queries, k-slices
+  // the MFMA's B operand: BF16 rows of this wavefront's queries, k-slices
   // 32 kk + 8 (lane >> 4) .. + 7 of row q0 + (lane & 15)
-  bf16x8 afrag[4];
+  bf16x8 qfrag[4];
   if (MATCH) {
-    for (int t = tid; t < kTileQ * kK; t += kThreads) {
-      tkl[t] = __builtin_inff();
-      tjl[t] = -1;
-    }
     if (CODES)  // zero rows for the queries that are not wide
       stage_codes(fetch_query_codes(A.codes1, q_i, wide_mask, tid), raw, q_norm, nullptr, tid);
     else
@@ -559,7 +506,7 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
     __syncthreads();
     #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-      afrag[kk] = *reinterpret_cast<const bf16x8*>(raw + ql * kRS + (kk * 32 + (lane >> 4) * 8) * 2);
+      qfrag[kk] = *reinterpret_cast<const bf16x8*>(raw + ql * kRS + (kk * 32 + (lane >> 4) * 8) * 2);
     // the block rows overwrite these only after the slab set-up's barriers
   }
   uint8_t* wrows = raw;
@@ -671,13 +618,12 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
       for (int sub = 0; sub < kSub; ++sub) {
         const int base = sub * kL;
         if (e0 + base >= E) break;  // uniform
-        float wn = 0.0f;
+        float* const wn_of = w_norm + (sub & 1) * kL;
         if (MATCH) {
-          if (CODES) stage_codes(prc, wrows, w_norm, &mx_n, tid);
-          else if (pre) stage_pre(rw, wrows, w_norm, &mx_n, &mx_e, tid);
-          else stage_bf16(rw, wrows, w_norm, nullptr, &mx_n, &mx_e, tid);
+          if (CODES) stage_codes(prc, wrows, wn_of, &mx_n, tid);
+          else if (pre) stage_pre(rw, wrows, wn_of, &mx_n, &mx_e, tid);
+          else stage_bf16(rw, wrows, wn_of, nullptr, &mx_n, &mx_e, tid);
           __syncthreads();  // block rows and norms complete
-          wn = w_norm[lane];
           if (sub + 1 < kSub && e0 + base + kL < E) {
             if (CODES) prc = fetch_codes(A.codes2, row_of + base + kL, tid);
             else if (pre) fetch_pre(rw, A.wcodes2, A.wterms2, row_of + base + kL, tid);
@@ -707,32 +653,48 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
           hm[qq] = ballot(hit);
           if ((qq & 3) == 3) __builtin_amdgcn_sched_barrier(0);  // four queries' terms at a time
         }
-        // 2. the hits extend (or are checked against) the queries' CSR rows,
-        // in ascending j
+        // the hit mask of query q0 + (lane & 15)
+        uint32_t mlo = 0u, mhi = 0u;
         #pragma unroll
         for (int qq = 0; qq < kQPerWave; ++qq) {
-          const uint64_t m = hm[qq];
-          if (m == 0ull) continue;  // uniform
-          if ((m >> lane) & 1ull) {
-            const uint32_t k = run[qq] + lanes_below(m);
-            const int64_t dst = (int64_t)readlane_u64((uint64_t)qp_o0, qq) + k;
-            if (WRITE) {
-              if (fits || dst < A.capacity) A.cols[dst] = ej;
-            } else {
-              // the caller's row must hold this hit at this place
-              const int32_t got =
-                  k < (uint32_t)__builtin_amdgcn_readlane((int)qp_len, qq) ? A.cols[dst] : -2;
-              if (got != ej) badbits |= 1u << qq;
+          const bool own = __builtin_amdgcn_inverse_ballot_w64(0x0001000100010001ull << qq);
+          mlo = own ? (uint32_t)hm[qq] : mlo;
+          mhi = own ? (uint32_t)(hm[qq] >> 32) : mhi;
+        }
+        // 2. the hits extend (or are checked against) the queries' CSR rows,
+        // in ascending j
+        if (!WRITE || !fits) {
+          #pragma unroll
+          for (int qq = 0; qq < kQPerWave; ++qq) {
+            GlobalInt at = (GlobalInt)readlane_u64((uint64_t)row_at, qq);  // uniform
+            if (__builtin_amdgcn_inverse_ballot_w64(hm[qq])) {
+              const uint32_t k = lanes_below(hm[qq]);
+              if (WRITE) {
+                if (at + k < (GlobalInt)(A.cols + A.capacity)) at[k] = ej;
+              } else {
+                // the caller's row must hold this hit at this place
+                const uint32_t left = (uint32_t)__builtin_amdgcn_readlane((int)row_left, qq);
+                if ((int32_t)left <= (int32_t)k || at[k] != ej) badbits |= 1u << qq;
+              }
             }
           }
-          run[qq] += (uint32_t)__popcll(m);
+        } else {
+          #pragma unroll
+          for (int qq = 0; qq < kQPerWave; ++qq) {
+            GlobalInt at = (GlobalInt)readlane_u64((uint64_t)row_at, qq);
+            if (__builtin_amdgcn_inverse_ballot_w64(hm[qq])) at[lanes_below(hm[qq])] = ej;
+          }
         }
-        // approximate keys |w^|^2 - 2 q^.w^ of this lane's entry base + lane
-        // for the wavefront's 16 queries
-        float kf[kQPerWave];
+        {
+          const uint32_t n = (uint32_t)__popc(mlo) + (uint32_t)__popc(mhi);
+          row_at += n;
+          row_left -= n;
+        }
+        // 3. (match) approximate keys |w^|^2 - 2 q^.w^, and the smallest ones kept
         if (MATCH) {
-          // S = Q W^T: the wavefront's 16 queries against the 64 rows; lane
-          // (g, c) = (lane >> 4, lane & 15) gets S[4 g + i][16 cb + c] in acc[cb][i]
+          // S^T = W Q^T: the 64 rows against the wavefront's 16 queries; lane
+          // (g, c) = (lane >> 4, lane & 15) gets S^T[16 cb + 4 g + i][c] in
+          // acc[cb][i]: query q0 + c against a quarter of the entries
           f32x4 acc[4];
           #pragma unroll
           for (int cb = 0; cb < 4; ++cb) acc[cb] = (f32x4){0.0f, 0.0f, 0.0f, 0.0f};
@@ -741,69 +703,29 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
             const int koff = kk * 32 + (lane >> 4) * 8;  // element offset of this lane's 8 values
             #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
-              const bf16x8 b = *reinterpret_cast<const bf16x8*>(
+              const bf16x8 w = *reinterpret_cast<const bf16x8*>(
                   wrows + (cb * 16 + (lane & 15)) * kRS + koff * 2);
-              acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(afrag[kk], b, acc[cb], 0, 0, 0);
+              acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, qfrag[kk], acc[cb], 0, 0, 0);
             }
+            if (kk == 1) __builtin_amdgcn_sched_barrier(0);  // half the slices' rows at a time
           }
+          // from this lane's entry 4 g on
+          const int hlo = (int)(mlo >> (4 * (lane >> 4))), hhi = (int)(mhi >> (4 * (lane >> 4)));
           __syncthreads();  // every wavefront has read the block rows
-          // exchange rows and blocks: lane (g, c) then holds S[4 r + i][16 g + c],
-          // the scores of its own entry 16 g + c, in acc[r][i]
           #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            float r0 = acc[0][i], r1 = acc[1][i], r2 = acc[2][i], r3 = acc[3][i];
-            transpose_rows(r0, r1, r2, r3);
-            kf[i] = __builtin_fmaf(-2.0f, r0, wn);
-            kf[4 + i] = __builtin_fmaf(-2.0f, r1, wn);
-            kf[8 + i] = __builtin_fmaf(-2.0f, r2, wn);
-            kf[12 + i] = __builtin_fmaf(-2.0f, r3, wn);
-          }
-        }
-        // 3. (match) hits below a query's kept (kPicks+1)-th key enter its list
-        if (MATCH) {
-          // this lane's slot of the wavefront's first list (constant offsets from here)
-          float* const tk0 = tkl + q0 * kK + lane;
-          int32_t* const tj0 = tjl + q0 * kK + lane;
-          #pragma unroll
-          for (int qq = 0; qq < kQPerWave; ++qq) {
-            const uint64_t m = hm[qq];
-            if (m == 0ull) continue;
-            const float th0 = thr[qq];
-            uint64_t surv = m & ballot(kf[qq] < th0);
-            if (surv == 0ull) continue;
-            const bool in = lane < kK;
-            float lk = in ? tk0[qq * kK] : __builtin_inff();
-            int32_t lji = in ? tj0[qq * kK] : -1;
-            float th = th0;
-            if (__popcll(surv) > kMergeMin) {
-              th = merge_list<kK>(lk, lji, surv, kf[qq], ej);
-            } else {
-              do {  // one survivor at a time
-                const int sl = __builtin_ctzll(surv);
-                surv &= surv - 1;
-                const float ks = readlane_f(kf[qq], sl);
-                if (!(ks < th)) continue;
-                const int32_t js = __builtin_amdgcn_readlane(ej, sl);
-                // the new key goes after the kept keys that are <= it; the
-                // ones above move up one lane
-                const int pos = __popcll(ballot(in && lk <= ks));
-                const float up_k = row_shift_up(lk);
-                const int32_t up_j = row_shift_up(lji);
-                if (lane == pos) {
-                  lk = ks;
-                  lji = js;
-                } else if (lane > pos) {
-                  lk = up_k;
-                  lji = up_j;
-                }
-                th = readlane_f(lk, kPicks);
-              } while (surv);
+          for (int cb = 0; cb < 4; ++cb) {
+            const float4 wn4 = *reinterpret_cast<const float4*>(wn_of + cb * 16 + 4 * (lane >> 4));
+            const int4 j4 =
+                *reinterpret_cast<const int4*>(lj + base + cb * 16 + 4 * (lane >> 4));
+            const float wn[4] = {wn4.x, wn4.y, wn4.z, wn4.w};
+            const int32_t jw[4] = {j4.x, j4.y, j4.z, j4.w};
+            #pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const float key = fminf(__builtin_fmaf(-2.0f, acc[cb][i], wn[i]), __builtin_inff());
+              const int hit = __builtin_amdgcn_sbfe(cb < 2 ? hlo : hhi, (cb & 1) * 16 + i, 1);
+              kept.add(__int_as_float((__float_as_int(key) & hit) | (0x7F800000 & ~hit)), jw[i]);
             }
-            if (in) {
-              tk0[qq * kK] = lk;
-              tj0[qq * kK] = lji;
-            }
-            thr[qq] = th;
+            kept.settle();  // a row block at a time: the compares' masks would pile up
           }
         }
       }
@@ -817,6 +739,46 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
   }
 
   if (!MATCH) return;
+  {
+    // a query's kK smallest keys among what its four lanes kept; the last one
+    // bounds all others, so it is lowered to the smallest that a lane dropped
+    float lk[kK];
+    int32_t lji[kK];
+    #pragma unroll
+    for (int u = 0; u < kK; ++u) {
+      lk[u] = __builtin_inff();
+      lji[u] = -1;
+    }
+    float drop = kept.drop;
+    drop = fminf(drop, __shfl_xor(drop, 16));
+    drop = fminf(drop, __shfl_xor(drop, 32));
+    #pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      #pragma unroll
+      for (int t = 0; t < 3; ++t) {
+        float k = __shfl(kept.a[t], (lane & 15) + 16 * g);
+        int32_t j = __shfl(kept.j[t], (lane & 15) + 16 * g);
+        #pragma unroll
+        for (int u = 0; u < kK; ++u) {  // the larger of the two moves on
+          const bool c = k < lk[u];
+          const float ok = lk[u];
+          const int32_t oj = lji[u];
+          lk[u] = c ? k : ok;
+          lji[u] = c ? j : oj;
+          k = c ? ok : k;
+          j = c ? oj : j;
+        }
+      }
+    }
+    lk[kPicks] = fminf(lk[kPicks], drop);
+    if (lane < kQPerWave) {
+      #pragma unroll
+      for (int u = 0; u < kK; ++u) {
+        tkl[(q0 + lane) * kK + u] = lk[u];
+        tjl[(q0 + lane) * kK + u] = lji[u];
+      }
+    }
+  }
   {
     // the largest row terms of the window (the bound terms are monotone in
     // the sums): relative slack 2e-5 covers the FP32 sums (at most 2^-24 per term)
@@ -836,7 +798,7 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
     #pragma unroll
     for (int qq = 0; qq < kQPerWave; ++qq) {
       const bool bad = ballot((badbits >> qq) & 1u) != 0ull;
-      if (lane == qq) q_bad[q0 + qq] = bad || run[qq] != qp_len ? 1u : 0u;
+      if (lane == qq) q_bad[q0 + qq] = bad || row_left != 0u ? 1u : 0u;
     }
   }
   // the picks are the first kPicks of every list; the bitmap area holds their
