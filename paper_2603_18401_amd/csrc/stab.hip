@@ -27,225 +27,6 @@ constexpr int kThreads = 256;
 constexpr int kWaves = kThreads / kWave;
 constexpr int kFinishRows = 256;  // queries per workgroup of k_finish_rows
 
-// Bitonic sort of one value per lane, ascending over the wavefront.
-__device__ __forceinline__ int32_t wave_sort64(int32_t v) {
-  const int lane = lane_id();
-  #pragma unroll
-  for (int k = 2; k <= kWave; k <<= 1) {
-    #pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const int32_t o = __shfl_xor(v, j);
-      const bool up = (lane & k) == 0;
-      const bool lower = (lane & j) == 0;
-      const int32_t mn = v < o ? v : o, mx = v < o ? o : v;
-      v = (lower == up) ? mn : mx;
-    }
-  }
-  return v;
-}
-
-__device__ __forceinline__ void wave_sync_lds() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Bitonic sort of buf[0..len) (len a power of two, 128..kRowSortMax) by one
-// wavefront.
-__device__ void wave_sort_lds(int32_t* buf, int len) {
-  const int lane = lane_id();
-  for (int k = 2; k <= len; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      for (int t = lane; t < len / 2; t += kWave) {
-        // comparator t: element pair (lo, lo + j)
-        const int lo = ((t / j) * 2 * j) + (t % j);
-        const int hi = lo + j;
-        const bool up = (lo & k) == 0;
-        const int32_t a = buf[lo], b = buf[hi];
-        if ((a > b) == up) {
-          buf[lo] = b;
-          buf[hi] = a;
-        }
-      }
-      wave_sync_lds();
-    }
-  }
-}
-
-struct QueryCtx {
-  double a, b, c;
-  uint32_t key;
-  bool brute;
-};
-
-// Scans sorted records [r0, r1): returns the number of hits; in the fill
-// pass appends the hit image-2 indices to buf (up to kRowSortMax).
-template <bool FILL>
-__device__ __forceinline__ uint32_t scan_range(const StabArgs& A, const QueryCtx& q, int64_t r0,
-                                               int64_t r1, int32_t* buf, uint32_t total) {
-  const int lane = lane_id();
-  for (int64_t base = r0; base < r1; base += kWave) {
-    const int64_t pos = base + lane;
-    bool hit = false;
-    if (pos < r1) {
-      const uint32_t C = A.rC[pos], H = A.rH[pos];
-      if (q.brute || key_distance(q.key, C) <= H) {
-        const float2 xy = A.rxy[pos];
-        hit = within_tolerance(q.a, q.b, q.c, xy.x, xy.y, A.reps[pos]);
-      }
-    }
-    const uint64_t m = ballot(hit);
-    if (FILL && hit) {
-      const uint32_t slot = total + lanes_below(m);
-      if (slot < (uint32_t)kRowSortMax) buf[slot] = A.rj[pos];
-    }
-    total += (uint32_t)__popcll(m);
-  }
-  return total;
-}
-
-template <bool FILL>
-__device__ uint32_t stab_query(const StabArgs& A, const PairDev& pd, int pair, const QueryCtx& q,
-                               int32_t* buf) {
-  const int64_t* cb = A.class_begin + (int64_t)pair * kClassSlots;
-  uint32_t total = 0;
-  for (int c = 0; c < kNumClasses; ++c) {
-    const int64_t beg = cb[c], end = cb[c + 1];
-    if (beg == end) continue;
-    if (q.brute || c == kWideClass) {
-      total = scan_range<FILL>(A, q, beg, end, buf, total);
-      continue;
-    }
-    const uint32_t span = (1u << c) - 1u;
-    const uint32_t lo = q.key - span, hi = q.key + span;
-    const uint32_t cls = (uint32_t)c << kCentreBits;
-    const uint32_t blo = cls | position_code(pd, lo), bhi = cls | position_code(pd, hi);
-    if (lo <= hi) {
-      const int64_t r0 = wave_lower_bound(A.skey, beg, end, blo);
-      const int64_t r1 = wave_lower_bound(A.skey, r0, end, bhi + 1u);
-      total = scan_range<FILL>(A, q, r0, r1, buf, total);
-    } else {
-      // the window wraps through the pair's cut
-      const int64_t r0 = wave_lower_bound(A.skey, beg, end, blo);
-      total = scan_range<FILL>(A, q, r0, end, buf, total);
-      const int64_t r1 = wave_lower_bound(A.skey, beg, r0, bhi + 1u);
-      total = scan_range<FILL>(A, q, beg, r1, buf, total);
-    }
-  }
-  return total;
-}
-
-// Writes query i's CSR row in ascending j (rows of any length).
-__device__ void fill_row(const StabArgs& A, int64_t i, int32_t* buf) {
-  const int lane = lane_id();
-  const int pair = find_pair(A.qstart, A.num_pairs, i);
-  const PairDev& pd = A.pairs[pair];
-  const uint32_t flag = A.qflag[i];
-  const int64_t o0 = A.row_offsets[i];
-  const int64_t len = A.row_offsets[i + 1] - o0;
-  if (len == 0 || flag == kQueryEmpty) return;
-  QueryCtx q;
-  epipolar_line(pd.F, A.kp1[2 * i], A.kp1[2 * i + 1], q.a, q.b, q.c);
-  q.key = A.qkey[i];
-  q.brute = flag == kQueryBrute;
-
-  if (len > kRowSortMax) {
-    // long row: rebuild it in ascending j directly from the definition
-    const int64_t kb = pd.k_begin;
-    uint32_t total = 0;
-    constexpr int kU = 4;  // blocks of 64 j whose gathers are in flight together
-    for (int64_t j0 = 0; j0 < pd.n; j0 += kU * kWave) {
-      uint32_t pos[kU];
-      #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t j = j0 + u * kWave + lane;
-        pos[u] = j < pd.n ? A.rinv[kb + j] : 0u;
-      }
-      float2 xy[kU];
-      float ee[kU];
-      #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t j = j0 + u * kWave + lane;
-        xy[u] = j < pd.n ? A.rxy[pos[u]] : make_float2(0.0f, 0.0f);
-        ee[u] = j < pd.n ? A.reps[pos[u]] : 0.0f;
-      }
-      #pragma unroll
-      for (int u = 0; u < kU; ++u) {
-        const int64_t j = j0 + u * kWave + lane;
-        const bool hit = j < pd.n && within_tolerance(q.a, q.b, q.c, xy[u].x, xy[u].y, ee[u]);
-        const uint64_t m = ballot(hit);
-        const int64_t dst = o0 + total + lanes_below(m);
-        if (hit && dst < A.capacity) A.cols[dst] = (int32_t)j;
-        total += (uint32_t)__popcll(m);
-      }
-    }
-    return;
-  }
-
-  const uint32_t total = stab_query<true>(A, pd, pair, q, buf);
-  wave_sync_lds();
-  const int n = (int)(total < (uint32_t)len ? total : (uint32_t)len);
-  if (n <= kWave) {
-    const int32_t v = wave_sort64(lane < n ? buf[lane] : INT32_MAX);
-    if (lane < n && o0 + lane < A.capacity) A.cols[o0 + lane] = v;
-  } else {
-    int p2 = 128;
-    while (p2 < n) p2 <<= 1;
-    for (int t = n + lane; t < p2; t += kWave) buf[t] = INT32_MAX;
-    wave_sync_lds();
-    wave_sort_lds(buf, p2);
-    for (int t = lane; t < n; t += kWave)
-      if (o0 + t < A.capacity) A.cols[o0 + t] = buf[t];
-  }
-  wave_sync_lds();
-}
-
-// The fused pass's record of a query: its row length and its match (as
-// write_match_to would store it), or kMatchDeferred for a match that a later
-// pass writes.
-__device__ __forceinline__ uint4 query_record(uint32_t count, float ratio, const Top2& t,
-                                              bool matched) {
-  int32_t idx = t.bj == INT32_MAX ? -1 : t.bj;
-  if (idx >= 0 && ratio > 0.0f && !(t.bd < ratio * ratio * t.sd)) idx = -1;
-  if (!matched) idx = kMatchDeferred;
-  return make_uint4(count, (uint32_t)idx, __float_as_uint(t.bd), __float_as_uint(t.sd));
-}
-
-// ------------------------------------------------------------- tiled pass
-constexpr int kQPerWave = kTileQ / kWaves;
-static_assert(kQPerWave == 16, "the pair test packs four records of 16 queries per wavefront");
-static_assert(kTileQ == 64, "pair indexing uses a 6-bit query field");
-
-// First index in [lo, hi) whose key is >= target (keys ascending), by one
-// lane: seven probes in flight per step cut the range to an eighth.
-__device__ __forceinline__ int64_t lower_bound_scalar(const uint32_t* __restrict__ keys,
-                                                      int64_t lo, int64_t hi, uint32_t target) {
-  // the answer lies in [lo, hi]
-  while (hi - lo > 8) {
-    const int64_t step = (hi - lo) / 8;
-    uint32_t k[7];
-    #pragma unroll
-    for (int m = 0; m < 7; ++m) k[m] = keys[lo + (m + 1) * step];
-    int c = 0;  // the probes below the target are a prefix
-    #pragma unroll
-    for (int m = 0; m < 7; ++m) c += k[m] < target ? 1 : 0;
-    const int64_t nlo = c == 0 ? lo : lo + c * step + 1;
-    const int64_t nhi = c == 7 ? hi : lo + (c + 1) * step;
-    lo = nlo;
-    hi = nhi;
-  }
-  int c = 0;
-  #pragma unroll
-  for (int m = 0; m < 8; ++m) c += lo + m < hi && keys[lo + m] < target ? 1 : 0;
-  return lo + c;
-}
-
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int off) {
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, off);
-  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), off);
-  return ((uint64_t)hi << 32) | lo;
-}
-
 // Reductions over the wavefront (uniform results), over each row of 16 lanes
 // and inclusive sums, by DPP: a step is one vector instruction, where a shuffle
 // through LDS takes a hundred cycles.  Lanes that have no neighbour in a step
@@ -300,14 +81,285 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
   return v;
 }
 
+// Value of lane l ^ J: DPP within a row of 16 lanes, the swizzle's bit mode for
+// 16, a shuffle for 32.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (J == 1) return dpp<0xB1, 0xF>(v, v);
+  else if constexpr (J == 2) return dpp<0x4E, 0xF>(v, v);
+  else if constexpr (J == 4) return dpp<0x1B, 0xF>(v, dpp<0x141, 0xF>(v, v));  // ^ 7, then ^ 3
+  else if constexpr (J == 8) return dpp<0x128, 0xF>(v, v);                     // rotate by 8
+  else if constexpr (J == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
+  else return (uint32_t)__shfl_xor((int)v, J);
+}
+template <int J>
+__device__ __forceinline__ int32_t lane_xor(int32_t v) {
+  return (int32_t)lane_xor<J>((uint32_t)v);
+}
+template <int J>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+  return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
+}
+
+// Bitonic sort of one value per lane, ascending over the wavefront (21
+// exchanges, 18 of them by DPP).
+template <int K, int J, typename T>
+__device__ __forceinline__ void sort_step(T& v, int lane) {
+  const T o = lane_xor<J>(v);
+  const bool low = ((lane & K) == 0) == ((lane & J) == 0);
+  v = (o < v) == low ? o : v;
+  if constexpr (J > 1) sort_step<K, J / 2>(v, lane);
+  else if constexpr (K < kWave) sort_step<2 * K, K>(v, lane);
+}
+template <typename T>
+__device__ __forceinline__ T wave_sort64(T v) {
+  sort_step<2, 1>(v, lane_id());
+  return v;
+}
+
+__device__ __forceinline__ void wave_sync_lds() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Bitonic sort of buf[0..len) (len a power of two, 128..kRowSortMax) by one
+// wavefront.
+__device__ void wave_sort_lds(int32_t* buf, int len) {
+  const int lane = lane_id();
+  for (int k = 2; k <= len; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int t = lane; t < len / 2; t += kWave) {
+        // comparator t: element pair (lo, lo + j)
+        const int lo = ((t / j) * 2 * j) + (t % j);
+        const int hi = lo + j;
+        const bool up = (lo & k) == 0;
+        const int32_t a = buf[lo], b = buf[hi];
+        if ((a > b) == up) {
+          buf[lo] = b;
+          buf[hi] = a;
+        }
+      }
+      wave_sync_lds();
+    }
+  }
+}
+
+struct QueryCtx {
+  double a, b, c;
+  uint32_t key;
+  bool brute;
+};
+
+// First index in [lo, hi) whose key is >= target (keys ascending), by one
+// lane: seven probes in flight per step cut the range to an eighth.
+__device__ __forceinline__ int64_t lower_bound_scalar(const uint32_t* __restrict__ keys,
+                                                      int64_t lo, int64_t hi, uint32_t target) {
+  // the answer lies in [lo, hi]
+  while (hi - lo > 8) {
+    const int64_t step = (hi - lo) / 8;
+    uint32_t k[7];
+    #pragma unroll
+    for (int m = 0; m < 7; ++m) k[m] = keys[lo + (m + 1) * step];
+    int c = 0;  // the probes below the target are a prefix
+    #pragma unroll
+    for (int m = 0; m < 7; ++m) c += k[m] < target ? 1 : 0;
+    const int64_t nlo = c == 0 ? lo : lo + c * step + 1;
+    const int64_t nhi = c == 7 ? hi : lo + (c + 1) * step;
+    lo = nlo;
+    hi = nhi;
+  }
+  int c = 0;
+  #pragma unroll
+  for (int m = 0; m < 8; ++m) c += lo + m < hi && keys[lo + m] < target ? 1 : 0;
+  return lo + c;
+}
+
+// The record ranges of the pair that can meet the keys [kmin, kmax]: every
+// width class's centres within [kmin - 2^c + 1, kmax + 2^c - 1], as slots.  Slot
+// s = lane is part s % 2 of class s / 2 (the second part only where the range
+// runs through the pair's cut); returns this lane's slot, its begin in `begin`
+// and its length as the result.  Lane c < 32 searches the start of class c's
+// range, lane c + 32 its end: all searches run side by side.
+__device__ __forceinline__ uint32_t class_ranges(const StabArgs& A, const PairDev& pd, int pair,
+                                                 uint32_t kmin, uint32_t kmax, bool any,
+                                                 uint32_t& begin) {
+  const int lane = lane_id();
+  const int c = lane & (kNumClasses - 1);
+  static_assert(2 * kNumClasses == kWave, "two lanes per width class");
+  int64_t beg = 0, end = 0, r = 0;
+  bool full = false, wrap = false;
+  if (any) {
+    const int64_t* cb = A.class_begin + (int64_t)pair * kClassSlots;
+    beg = cb[c];
+    end = cb[c + 1];
+    if (beg < end) {
+      const uint32_t span = c == kWideClass ? 0u : (1u << c) - 1u;
+      const uint64_t width = (uint64_t)(kmax - kmin) + 2ull * span;
+      full = c == kWideClass || width >= 0xFFFFE000ull;
+      if (!full) {
+        const uint32_t lo = kmin - span, hi = kmax + span;
+        const uint32_t cls = (uint32_t)c << kCentreBits;
+        const uint32_t blo = cls | position_code(pd, lo), bhi = cls | position_code(pd, hi);
+        // bhi + 1 > blo without a wrap; through the cut the two ranges may
+        // meet in one code (and then take the whole class once)
+        wrap = lo > hi;
+        r = lower_bound_scalar(A.skey, beg, end, lane < kNumClasses ? blo : bhi + 1u);
+      }
+    }
+  }
+  // record positions fit 32 bits (the windows store them so)
+  const uint32_t rb = (uint32_t)r, re = (uint32_t)__shfl((int)rb, c + kNumClasses);
+  const uint32_t ub = (uint32_t)beg, ue = (uint32_t)end;
+  uint32_t b0 = 0, l0 = 0, b1 = 0, l1 = 0;
+  if (any && ub < ue) {
+    b0 = full ? ub : rb;
+    l0 = full || wrap ? ue - b0 : re - rb;
+    b1 = ub;
+    l1 = !full && wrap ? (re < rb ? re : rb) - ub : 0u;
+  }
+  const int src = lane >> 1;
+  const uint32_t be = (uint32_t)__shfl((int)b0, src), bo = (uint32_t)__shfl((int)b1, src);
+  const uint32_t le = (uint32_t)__shfl((int)l0, src), lo_ = (uint32_t)__shfl((int)l1, src);
+  begin = (lane & 1) ? bo : be;
+  return (lane & 1) ? lo_ : le;
+}
+
+// The row of query q: the image-2 indices of its hits in buf (the first
+// kRowSortMax, in any order); returns their number.  The record ranges are
+// found for all classes at once and scanned as one sequence.  What bounds it:
+// the latency of a row's dependent loads.  (Class after class, each with two
+// searches of its own: 22.4 us for the rows of 48 pairs of 500 to 10000
+// keypoints whose windows are too long for the tile pass, 9.2 this way; 37 and
+// 18.9 at 512 pairs.)
+__device__ uint32_t stab_query(const StabArgs& A, const PairDev& pd, int pair, const QueryCtx& q,
+                               int32_t* buf) {
+  const int lane = lane_id();
+  uint32_t begin = (uint32_t)pd.k_begin, len = lane == 0 ? (uint32_t)pd.n : 0u;
+  if (!q.brute) len = class_ranges(A, pd, pair, q.key, q.key, true, begin);
+  const uint32_t incl = wave_scan_u32(len);
+  const uint32_t all = (uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
+  const uint32_t off = begin - (incl - len);  // position of entry v: off + v
+  uint32_t total = 0;
+  for (uint32_t base = 0; base < all; base += kWave) {
+    const uint32_t v = base + (uint32_t)lane;
+    int s = 0;  // the slot that holds entry v: slots before it end at or below v
+    #pragma unroll
+    for (int step = 32; step > 0; step >>= 1) {
+      const uint32_t e = (uint32_t)__shfl((int)incl, s + step - 1);
+      if (e <= v) s += step;
+    }
+    const uint32_t pos = (uint32_t)__shfl((int)off, s) + v;
+    bool hit = false;
+    int32_t j = 0;
+    if (v < all) {
+      j = A.rj[pos];
+      const float2 xy = A.rxy[pos];
+      hit = (q.brute || key_distance(q.key, A.rC[pos]) <= A.rH[pos]) &&
+            within_tolerance(q.a, q.b, q.c, xy.x, xy.y, A.reps[pos]);
+    }
+    const uint64_t m = ballot(hit);
+    const uint32_t slot = total + lanes_below(m);
+    if (hit && slot < (uint32_t)kRowSortMax) buf[slot] = j;
+    total += (uint32_t)__popcll(m);
+  }
+  return total;
+}
+
+// Writes query i's CSR row in ascending j (rows of any length).
+__device__ void fill_row(const StabArgs& A, int64_t i, int32_t* buf) {
+  const int lane = lane_id();
+  const int pair = find_pair(A.qstart, A.num_pairs, i);
+  const PairDev& pd = A.pairs[pair];
+  const uint32_t flag = A.qflag[i];
+  const int64_t o0 = A.row_offsets[i];
+  const int64_t len = A.row_offsets[i + 1] - o0;
+  if (len == 0 || flag == kQueryEmpty) return;
+  QueryCtx q;
+  epipolar_line(pd.F, A.kp1[2 * i], A.kp1[2 * i + 1], q.a, q.b, q.c);
+  q.key = A.qkey[i];
+  q.brute = flag == kQueryBrute;
+
+  if (len > kRowSortMax) {
+    // long row: rebuild it in ascending j directly from the definition
+    const int64_t kb = pd.k_begin;
+    uint32_t total = 0;
+    constexpr int kU = 4;  // blocks of 64 j whose gathers are in flight together
+    for (int64_t j0 = 0; j0 < pd.n; j0 += kU * kWave) {
+      uint32_t pos[kU];
+      #pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t j = j0 + u * kWave + lane;
+        pos[u] = j < pd.n ? A.rinv[kb + j] : 0u;
+      }
+      float2 xy[kU];
+      float ee[kU];
+      #pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t j = j0 + u * kWave + lane;
+        xy[u] = j < pd.n ? A.rxy[pos[u]] : make_float2(0.0f, 0.0f);
+        ee[u] = j < pd.n ? A.reps[pos[u]] : 0.0f;
+      }
+      #pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const int64_t j = j0 + u * kWave + lane;
+        const bool hit = j < pd.n && within_tolerance(q.a, q.b, q.c, xy[u].x, xy[u].y, ee[u]);
+        const uint64_t m = ballot(hit);
+        const int64_t dst = o0 + total + lanes_below(m);
+        if (hit && dst < A.capacity) A.cols[dst] = (int32_t)j;
+        total += (uint32_t)__popcll(m);
+      }
+    }
+    return;
+  }
+
+  const uint32_t total = stab_query(A, pd, pair, q, buf);
+  wave_sync_lds();
+  const int n = (int)(total < (uint32_t)len ? total : (uint32_t)len);
+  if (n <= kWave) {
+    const int32_t v = wave_sort64(lane < n ? buf[lane] : INT32_MAX);
+    if (lane < n && o0 + lane < A.capacity) A.cols[o0 + lane] = v;
+  } else {
+    int p2 = 128;
+    while (p2 < n) p2 <<= 1;
+    for (int t = n + lane; t < p2; t += kWave) buf[t] = INT32_MAX;
+    wave_sync_lds();
+    wave_sort_lds(buf, p2);
+    for (int t = lane; t < n; t += kWave)
+      if (o0 + t < A.capacity) A.cols[o0 + t] = buf[t];
+  }
+  wave_sync_lds();
+}
+
+// The fused pass's record of a query: its row length and its match (as
+// write_match_to would store it), or kMatchDeferred for a match that a later
+// pass writes.
+__device__ __forceinline__ uint4 query_record(uint32_t count, float ratio, const Top2& t,
+                                              bool matched) {
+  int32_t idx = t.bj == INT32_MAX ? -1 : t.bj;
+  if (idx >= 0 && ratio > 0.0f && !(t.bd < ratio * ratio * t.sd)) idx = -1;
+  if (!matched) idx = kMatchDeferred;
+  return make_uint4(count, (uint32_t)idx, __float_as_uint(t.bd), __float_as_uint(t.sd));
+}
+
+// ------------------------------------------------------------- tiled pass
+constexpr int kQPerWave = kTileQ / kWaves;
+static_assert(kQPerWave == 16, "the pair test packs four records of 16 queries per wavefront");
+static_assert(kTileQ == 64, "pair indexing uses a 6-bit query field");
+
 // Window pass: for tile t, the record ranges of every width class whose
 // centres lie within [min key - 2^c + 1, max key + 2^c - 1] of the tile's
-// queries; lane c searches class c.  No LDS, so every tile's searches are in
-// flight at once.
+// queries (class_ranges), one wavefront per tile, so every tile's searches are
+// in flight at once.
 constexpr int kWindowTiles = 4;  // tiles (one wavefront each) per workgroup
 __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs A) {
   const int lane = lane_id();
-  const int t = blockIdx.x * kWindowTiles + wave_id();
+  // each XCD takes one run of consecutive tiles: the queries of a pair are
+  // gathered in their sorted order, and a line of them holds several tiles'
+  // (12.5 us with the workgroups dealt in turn, 10.8 so, at 1878 tiles)
+  const int run = (int)gridDim.x / kNumXcd;
+  const int t =
+      (((int)blockIdx.x % kNumXcd) * run + (int)blockIdx.x / kNumXcd) * kWindowTiles + wave_id();
   // the look-back words of the pass over the rows (one per 256 queries, a
   // tile holds at most 64) start from zero
   for (int64_t k = (int64_t)blockIdx.x * (kWave * kWindowTiles) + threadIdx.x;
@@ -341,15 +393,7 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
   uint32_t moved = 0u;
   if (joined) {
     uint64_t v = ((uint64_t)s_k[slot + kTileQ / 2] << 6) | (uint64_t)lane;
-    #pragma unroll
-    for (int k = 2; k <= kWave; k <<= 1) {
-      #pragma unroll
-      for (int j = k >> 1; j > 0; j >>= 1) {
-        const uint64_t o = shfl_xor_u64(v, j);
-        const bool low = ((lane & k) == 0) == ((lane & j) == 0);
-        v = (o < v) == low ? o : v;
-      }
-    }
+    v = wave_sort64(v);
     moved = s_i[slot - lane + kTileQ / 2 + (int)(v & 63ull)];
   }
   __syncthreads();
@@ -387,67 +431,17 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
   const uint32_t kmin = wave_min_u32(normal ? key : 0xFFFFFFFFu);
   const uint32_t kmax = wave_max_u32(normal ? key : 0u);
   const bool any = ballot(normal) != 0;
-  // lane c < 32 searches the start of class c's window, lane c + 32 its end:
-  // the two searches run side by side
-  const int c = lane & (kNumClasses - 1);
-  static_assert(2 * kNumClasses == kWave, "two lanes per width class");
-  int64_t beg = 0, end = 0, r = 0;
-  bool full = false, wrap = false;
-  if (any) {
-    const int64_t* cb = A.class_begin + (int64_t)T.pair * kClassSlots;
-    beg = cb[c];
-    end = cb[c + 1];
-    if (beg < end) {
-      const uint32_t span = c == kWideClass ? 0u : (1u << c) - 1u;
-      const uint64_t width = (uint64_t)(kmax - kmin) + 2ull * span;
-      full = c == kWideClass || width >= 0xFFFFE000ull;
-      if (!full) {
-        const uint32_t lo = kmin - span, hi = kmax + span;
-        const uint32_t cls = (uint32_t)c << kCentreBits;
-        const PairDev& pd = A.pairs[T.pair];
-        const uint32_t blo = cls | position_code(pd, lo), bhi = cls | position_code(pd, hi);
-        // bhi + 1 > blo without a wrap; through the cut the two ranges may
-        // meet in one code (and then take the whole class once)
-        wrap = lo > hi;
-        r = lower_bound_scalar(A.skey, beg, end, lane < kNumClasses ? blo : bhi + 1u);
-      }
-    }
-  }
-  const int64_t r_end = __shfl(r, c + kNumClasses);
-  int64_t b0 = 0, l0 = 0, b1 = 0, l1 = 0;
-  if (lane < kNumClasses && any && beg < end) {
-    if (full) {
-      b0 = beg;
-      l0 = end - beg;
-    } else if (!wrap) {
-      b0 = r;
-      l0 = r_end - r;
-    } else {
-      b0 = r;
-      l0 = end - r;
-      b1 = beg;
-      l1 = (r_end < r ? r_end : r) - beg;
-    }
-  }
-  // slot s = class s/2, part s%2; inclusive scan of the 64 slot lengths
-  const int src = lane >> 1;
-  const int64_t be = __shfl(b0, src), bo = __shfl(b1, src);
-  const int64_t le = __shfl(l0, src), lo_ = __shfl(l1, src);
-  const int64_t myb = (lane & 1) ? bo : be;
-  int64_t incl = (lane & 1) ? lo_ : le;
-  #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    const int64_t o = __shfl_up(incl, off);
-    if (lane >= off) incl += o;
-  }
+  uint32_t begin = 0;
+  const uint32_t len = class_ranges(A, A.pairs[T.pair], T.pair, kmin, kmax, any, begin);
+  const uint32_t incl = wave_scan_u32(len);
   TileWindow* w = A.windows + t;
-  w->slot_b[lane] = (uint32_t)myb;
-  w->slot_pref[lane + 1] = (uint32_t)incl;
+  w->slot_b[lane] = begin;
+  w->slot_pref[lane + 1] = incl;
   if (lane == 0) w->slot_pref[0] = 0u;
   if (A.tile_cost) {
     // work estimate: (query, record) pairs of the window scan, brute-force
     // scans, and one unit per query
-    const uint64_t wlen = (uint64_t)__shfl(incl, kWave - 1);
+    const uint64_t wlen = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)incl, kWave - 1);
     const uint64_t nn = (uint64_t)__popcll(ballot(normal));
     const uint64_t nb = (uint64_t)__popcll(ballot(brute));
     if (lane == 0) {
@@ -2156,7 +2150,8 @@ hipError_t launch_clear_stats(unsigned long long* stats, hipStream_t s, uint32_t
 
 hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s) {
   if (a.num_tiles == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_tile_windows, dim3((a.num_tiles + kWindowTiles - 1) / kWindowTiles),
+  const int blocks = (a.num_tiles + kWindowTiles - 1) / kWindowTiles;
+  hipLaunchKernelGGL(k_tile_windows, dim3((blocks + kNumXcd - 1) / kNumXcd * kNumXcd),
                      dim3(kWave * kWindowTiles), 0, s, a);
   return hipGetLastError();
 }
