@@ -541,7 +541,9 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   const bool persistent = S.stab_workgroups > 0 || S.match_workgroups > 0;
   const bool lpt = persistent && S.lpt == 1;
   // one workgroup per tile: the tiles of every XCD run longest first
-  const bool xcd_lpt = S.stab_workgroups == 0;
+  // (grids that the chip holds at once start together: an order would not
+  // change when they end, and its launch costs 5 us)
+  const bool xcd_lpt = S.stab_workgroups == 0 && A.num_tiles > kResidentTiles;
   uint32_t* sched = idx->at<uint32_t>(L.sched);  // cleared by the key pass
   A.tile_cost = lpt || xcd_lpt ? idx->at<uint32_t>(L.tile_cost) : nullptr;
   EPM_HIP(launch_tile_windows(A, stream));
@@ -567,12 +569,9 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   return EPM_OK;
 }
 
-// The rows that were not parked: brute-force rows and those of tiles that the
-// fused pass leaves, then the wide-row pass (match: with its FP32 selection,
-// see launch_wide_tiles).
 // BF16 copies of the image-2 rows of the pairs with wide tiles, for a
 // matching wide-row pass (A.desc2 set): they go to the staging area, whose
-// parked rows the fill pass has copied out by then, when it holds 256 bytes
+// parked rows have been copied out by then, when it holds 256 bytes
 // of codes and 8 of terms per row; otherwise the pass rounds on chip.
 hipError_t prepare_wide_rows(epm_index* idx, StabArgs& A, hipStream_t stream) {
   const size_t n2 = (size_t)idx->N2;
@@ -600,10 +599,13 @@ epm_status read_totals(const epm_index* idx, const StabArgs& A, int64_t* nnz_hos
   return *nnz_host > A.capacity ? EPM_ERR_CAPACITY : EPM_OK;
 }
 
+// The rows that were not parked: those of brute-force queries, then the wide-row
+// pass (match: with its FP32 selection, see launch_wide_tiles).
 epm_status enqueue_fill(epm_index* idx, StabArgs& A, hipStream_t stream, bool match = false) {
   if (idx->N1 == 0) return EPM_OK;
-  EPM_HIP(launch_fill_long(A, stream));
+  // (match: the rows that the tiles left are rebuilt where they are matched)
   if (match) EPM_HIP(prepare_wide_rows(idx, A, stream));
+  else EPM_HIP(launch_fill_long(A, stream));
   const bool timed = idx->ev_start && idx->timed == EPM_TIMED_WIDE;
   if (timed) EPM_HIP(hipEventRecord(idx->ev_start, stream));
   EPM_HIP(launch_wide_tiles(A, match ? kWideFused : kWideFill, stream));
@@ -815,8 +817,8 @@ epm_status enqueue_match_kernels(epm_index* idx, const MatchCall& c, hipStream_t
   }
 }
 
-// Stabbing with fused FP32 selection, then the CSR fill with the wide-row
-// selection, and the listed-query match of the rows the two passes left.
+// Stabbing with fused FP32 selection, then the wide-row pass with its
+// selection, and the rows and matches of the queries the two passes left.
 // nnz_host as in epm_query_candidates.
 epm_status enqueue_query_match(epm_index* idx, StabArgs& A, int64_t* row_offsets,
                                int64_t* nnz_host, const MatchCall& c, hipStream_t stream,
@@ -862,7 +864,7 @@ epm_status enqueue_query_match(epm_index* idx, StabArgs& A, int64_t* row_offsets
   MatchArgs M = match_args(idx, c);
   M.desc1 = A.desc1;  // FP32 rows (the masters for BF16)
   M.desc2 = A.desc2;
-  EPM_HIP(launch_match_listed_f32(M, A.rest, A.stats + kStatRest, n1, stream));
+  EPM_HIP(launch_finish_listed(A, M, stream));
   return EPM_OK;
 }
 

@@ -170,8 +170,10 @@ hipError_t launch_xcd_lpt_order(const uint32_t* cost, int num_tiles, uint32_t* b
 // One wavefront per tile finds the tile's window in every width class.
 hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s);
 
+// Tiles that the chip holds at once: three workgroups on each of 256 CUs.
+constexpr int kResidentTiles = 768;
 // Device-wide counters of a query: the lengths of its two queues (long rows
-// for the fill pass, rows left to the listed-query match), whether any tile
+// for the fill pass, queries left over by the fused passes), whether any tile
 // has wide rows, and the total of candidates.
 constexpr int kStatLongRows = 0, kStatRest = 1, kStatWide = 2, kStatNnz = 3;
 constexpr int kNumStats = 4;
@@ -185,8 +187,7 @@ hipError_t launch_clear_stats(unsigned long long* stats, hipStream_t s, uint32_t
 // workgroup per tile; grid > 0: that many workgroups take tiles from a.queue.
 // mode kStabF32 / kStabBF16: also selects the FP32 matches of the rows it can
 // (desc1/desc2 and the outputs in a); the other queries are appended to
-// a.rest, counted in stats[kStatRest], for launch_match_listed_f32 once the
-// CSR is complete.
+// a.rest, counted in stats[kStatRest], for launch_finish_listed.
 // mode kStabBF16: BF16 codes in codes1/codes2 with the FP32 masters in
 // desc1/desc2; the match is selected through certified MFMA bounds and an
 // exact re-rank on the masters (rows it cannot certify go to a.rest).
@@ -209,8 +210,8 @@ constexpr int32_t kMatchDeferred = INT32_MIN;
 int64_t finish_state_words(int64_t n1);
 hipError_t launch_finish_rows(const StabArgs& a, int64_t* partials, int64_t* offsets,
                               hipStream_t s);
-// Rebuilds the rows that launch_finish_rows queued (brute-force queries, rows
-// of tiles that the fused pass leaves).
+// Rebuilds the rows that launch_finish_rows queued after a counting pass (long
+// rows of brute-force queries).
 hipError_t launch_fill_long(const StabArgs& a, hipStream_t s);
 // Wide-row pass over the tiles flagged in a.tile_wide.
 //   kWideFill:  writes the rows longer than kStage of normal queries (after
@@ -286,6 +287,11 @@ constexpr int kMatchStatWords = kMatchStatRest + 1;
 // fmt 0: BF16, 1: FP8-E4M3 with row scales.
 // grid as for launch_stab_tiles.
 hipError_t launch_match_window_mfma(const MatchArgs& a, int fmt, int grid, hipStream_t s);
+
+// The queries that the fused passes left over (a.rest, counted in
+// stats[kStatRest]): their rows rebuilt where they are not in the CSR yet, then
+// their FP32 matches.
+hipError_t launch_finish_listed(const StabArgs& a, const MatchArgs& m, hipStream_t s);
 
 hipError_t launch_match_plain_f32(const MatchArgs& a, hipStream_t s);
 // FP32 matches of the queries list[0 .. *count) (count on the device, at most

@@ -167,4 +167,30 @@ __device__ __forceinline__ void write_match(const MatchArgs& A, int64_t i, const
   write_match_to(A.ratio, A.best_idx, A.best_dist, A.second_dist, i, t, binary);
 }
 
+// FP32 match of query i over its CSR row, by one wavefront (qdesc: room for
+// its descriptor in LDS).
+__device__ __forceinline__ void match_row_f32(const MatchArgs& A, int64_t i, float4* qdesc) {
+  const int lane = lane_id();
+  const int pair = find_pair(A.qstart, A.num_pairs, i);
+  const int64_t kb = A.kstart[pair];
+  if (lane < 32) qdesc[lane] = reinterpret_cast<const float4*>(A.desc1)[i * 32 + lane];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const int64_t o0 = A.row_offsets[i], o1 = A.row_offsets[i + 1];
+  Top2 tp;
+  for (int64_t e = o0 + lane; e < o1; e += kWave) {
+    const int32_t j = A.cols[e];
+    const float4* d2 = reinterpret_cast<const float4*>(A.desc2) + (kb + j) * 32;
+    float acc = 0.0f;
+    #pragma unroll 8
+    for (int k = 0; k < 32; ++k) acc = canonical_step4(acc, qdesc[k], d2[k]);
+    tp.insert(acc, j);
+  }
+  tp = wave_merge_top2(tp);
+  if (lane == 0) write_match(A, i, tp, false);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 }  // namespace epm

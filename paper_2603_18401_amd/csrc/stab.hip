@@ -8,9 +8,9 @@
 // units of it, so the window pass finds each tile's record window in every
 // class; the tile pass tests every (query, record) pair of the window, writes
 // the row lengths and parks short rows.  After the scan of the lengths the
-// fill pass copies the parked rows and rebuilds the long rows of brute-force
-// queries one wavefront per query (scan, LDS sort by j); long rows of normal
-// queries are written tile by tile by the wide-row pass.  The tile pass can
+// parked rows are copied and the long rows of brute-force queries rebuilt one
+// wavefront per query (scan, LDS sort by j); long rows of normal queries are
+// written tile by tile by the wide-row pass.  The tile pass can
 // also select every short row's match (Sec. 4.3) while its hits are on chip:
 // FP32 chains, or MFMA bounds over BF16 or FP8 rows with an exact FP32
 // re-rank.
@@ -471,9 +471,9 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
 // the chunk, each lane resuming where the last chunk left it, and keep a
 // top-2, merged across the four lanes at the end.  Rows longer than kStage are
 // matched by the wide-row pass; the rows this pass does not keep (brute-force
-// queries, windows longer than kKeepJ) are marked for the fill pass to
-// rebuild, and those queries are listed for the listed-query match after the
-// CSR is complete; empty rows get their (-1, inf, inf) here.  The LDS and
+// queries, windows longer than kKeepJ) are marked and their queries listed:
+// k_finish_listed rebuilds the rows and matches them; empty rows get their
+// (-1, inf, inf) here.  The LDS and
 // register budget allows three workgroups per CU.  Outside the order of the
 // window every wavefront works on its own 16 queries, so the tile needs only
 // the barriers of the record and row chunks and of the order; its counters
@@ -489,12 +489,15 @@ constexpr int rec_bytes(int CH) { return CH * (4 + 4 + 8 + 4 + 4); }
 constexpr int kFuseChunks = kFuseRows * (kFuseStride / 4);
 constexpr int kFuseCopies = (kFuseChunks + kWave - 1) / kWave;
 constexpr int kFuseBytes = kFuseCopies * kWave * 16;
-// First entry of a parked row that was not parked: the fill pass rebuilds it.
+// First entry of a parked row that was not parked: k_finish_listed rebuilds it.
 constexpr int32_t kRowNotParked = -1;
+// Flag of a listed query (a.rest) whose row has to be rebuilt first; there are
+// fewer than 2^31 queries (their parked rows alone would fill 1 TB).
+constexpr uint32_t kRestRebuild = 0x80000000u;
 
 // FUSE: the j of the first kKeepJ window positions stay in LDS; the hits
 // are kept as 16-bit window positions, and tiles with longer windows are not
-// fused (their rows are rebuilt by the fill pass and matched from the list)
+// fused (their rows are rebuilt and matched from the list)
 constexpr int kKeepJ = 1024;
 constexpr int64_t kFuseMaxWindow = kKeepJ;
 
@@ -1218,7 +1221,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
           hit = within_tolerance_n(a, b, c, nrm, xy.x, xy.y, A.reps[pos]);
         }
         const uint64_t m = ballot(hit);
-        if (!FUSE && hit) {  // FUSE: counted only, the row is rebuilt by the fill pass
+        if (!FUSE && hit) {  // FUSE: counted only, the row is rebuilt from the list
           const uint32_t slot = c0 + lanes_below(m);
           if (slot < (uint32_t)kStage) brute_row[slot] = A.rj[pos];
         }
@@ -1379,7 +1382,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         }
       } else if (n > 0 && n <= (uint32_t)kStage && !mine && part == 0) {
         // rows that are not kept (brute-force queries, windows that are not
-        // fused) are marked for the fill pass to rebuild
+        // fused) are marked and rebuilt from the list
         dst[0] = kRowNotParked;
       }
 
@@ -1388,7 +1391,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         if (mode != kQueryEmpty &&
             (mode != kQueryNormal || (cnt[q] <= (uint32_t)kStage && !fusable))) {
           const unsigned long long at = atomicAdd(&A.stats[kStatRest], 1ull);
-          A.rest[at] = (uint32_t)qidx[q];
+          A.rest[at] = (uint32_t)qidx[q] | kRestRebuild;
         }
       }
     }
@@ -1785,9 +1788,9 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
 // lengths, publishes their sum, finds the sum of all earlier workgroups by
 // looking back over what those have published, and then writes its offsets,
 // the fused pass's matches (unless a later pass writes them) and the parked
-// (already sorted) short rows.  Short rows marked as not parked and longer
-// rows of brute-force queries are queued for k_fill_long; long rows of normal
-// queries belong to the wide-row pass.
+// (already sorted) short rows.  After a counting pass the long rows of
+// brute-force queries are queued for k_fill_long (a fused pass has listed what
+// it leaves); long rows of normal queries belong to the wide-row pass.
 //
 // A word of row_sums is a sum with a flag in its top bits: of the workgroup
 // alone, or of it and all before it.  Nothing has to be waited for: the row
@@ -1933,7 +1936,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_rows(StabArgs A,
       if ((uint32_t)sub < len && dst < A.capacity) A.cols[dst] = v[u];
       parked |= 1u << u;
       longest = len > longest ? len : longest;
-    } else if (sub == 0 &&
+    } else if (sub == 0 && !A.qrec &&
                (len <= (uint32_t)kStage || A.qflag[i0 + row] != kQueryNormal)) {
       const unsigned long long slot = atomicAdd(&A.stats[kStatLongRows], 1ull);
       A.long_rows[slot] = (uint32_t)(i0 + row);
@@ -1992,7 +1995,7 @@ __global__ __launch_bounds__(kThreads) void k_copy_rows(StabArgs A) {
       const int32_t* src = A.staging + i * kStage;
       for (int k = sub + kCopyLanes; k < (int)len; k += kCopyLanes)
         if (o0[u] + k < A.capacity) A.cols[o0[u] + k] = src[k];
-    } else if (sub == 0 && (len <= kStage || A.qflag[i] != kQueryNormal)) {
+    } else if (sub == 0 && !A.qrec && (len <= kStage || A.qflag[i] != kQueryNormal)) {
       // long rows of normal queries belong to the wide-row pass of their tile
       const unsigned long long slot = atomicAdd(&A.stats[kStatLongRows], 1ull);
       A.long_rows[slot] = (uint32_t)i;
@@ -2022,6 +2025,32 @@ __global__ __launch_bounds__(kThreads) void k_fill_long(StabArgs A) {
   for (uint64_t t = (uint64_t)blockIdx.x * kWaves + wave; t < n;
        t += (uint64_t)gridDim.x * kWaves)
     fill_row(A, (int64_t)A.long_rows[t], rowbuf[wave]);
+}
+
+// The queries that the fused passes left over, a wavefront each: rows that are
+// not in the CSR yet are rebuilt, then the match is taken from the row.  (As
+// two launches, the rebuild took 4.4 us of a call even where there was nothing
+// to rebuild.)
+__global__ __launch_bounds__(kThreads) void k_finish_listed(StabArgs A, MatchArgs M) {
+  __shared__ int32_t rowbuf[kWaves][kRowSortMax];
+  __shared__ float4 qdesc[kWaves][32];
+  const int wave = wave_id();
+  const uint64_t n = A.stats[kStatRest];
+  if (n == 0) return;
+  const bool fits = !csr_overflow(M);  // an incomplete CSR is completed, not matched
+  for (uint64_t t = (uint64_t)blockIdx.x * kWaves + wave; t < n;
+       t += (uint64_t)gridDim.x * kWaves) {
+    const uint32_t w = A.rest[t];
+    const int64_t i = (int64_t)(w & ~kRestRebuild);
+    if (w & kRestRebuild) {
+      fill_row(A, i, rowbuf[wave]);
+      // the row is read back by other lanes of the wavefront
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+    if (fits) match_row_f32(M, i, qdesc[wave]);
+  }
 }
 
 // ------------------------------------------------------------------ scan
@@ -2216,6 +2245,15 @@ hipError_t launch_fill_long(const StabArgs& a, hipStream_t s) {
   // (8192 wavefronts) take them from the queue
   const int64_t lblocks = blocks < 2048 ? blocks : 2048;
   hipLaunchKernelGGL(k_fill_long, dim3((unsigned)lblocks), dim3(kThreads), 0, s, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_finish_listed(const StabArgs& a, const MatchArgs& m, hipStream_t s) {
+  if (a.n1 == 0) return hipSuccess;
+  // as many workgroups as fit with their row buffers, and no more than queries
+  const int64_t blocks = (a.n1 + kWaves - 1) / kWaves;
+  hipLaunchKernelGGL(k_finish_listed, dim3((unsigned)(blocks < 1024 ? blocks : 1024)),
+                     dim3(kThreads), 0, s, a, m);
   return hipGetLastError();
 }
 

@@ -82,3 +82,43 @@ def test_rows_of_scanned_queries(n):
         offs, cols = [t.cpu().numpy() for t in idx.query(g(kp1))]
         assert idx.stats()["scanned_queries"] > 0
         assert np.array_equal(offs, ro) and np.array_equal(cols, rc)
+
+
+@pytest.mark.parametrize("n", [60, 900, 2500])
+def test_left_over_rows_are_rebuilt_and_matched(n):
+    """Scanned queries after a fused pass, without a wait in between: the rows
+    and their matches, and in a buffer that is too small the rows as far as
+    they go."""
+    import paper_2603_18401_amd as E
+    torch = torch_gpu()
+    dev = torch.device("cuda:0")
+    g = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(dev)  # noqa: E731
+    m = 130
+    F, kp1, kp2 = _strip(m, n, "raster", n)
+    F = F + 1e-5 * np.abs(F).max() * np.eye(3)
+    rng = np.random.default_rng(n)
+    d1 = synth.pairs._unit_rows(rng.standard_normal((m, 128)))
+    d2 = synth.pairs._unit_rows(rng.standard_normal((n, 128)))
+    f1, f2, k1 = g(d1), g(d2), g(kp1)
+    c1, c2 = E.quantize(f1, "bf16"), E.quantize(f2, "bf16")
+    for eps in (0.5, 4.0):
+        ro, rc, _ = oracle.candidates(F, kp1, kp2, eps)
+        rb, rbd, rsd = oracle.match(d1, d2, ro, rc)
+        for room in (len(rc) + 3, max(1, len(rc) // 2)):
+            idx = E.Index([E.PairSpec(F, 1920, 1080, m, n)], g(kp2), eps=eps)
+            for bf16 in (False, True):
+                offs = torch.empty(m + 1, dtype=torch.int64, device=dev)
+                cols = torch.full((room,), -7, dtype=torch.int32, device=dev)
+                kw = dict(row_offsets=offs, col_indices=cols, sync=False)
+                out = (idx.query_match_bf16(k1, c1, c2, f1, f2, **kw) if bf16
+                       else idx.query_match(k1, f1, f2, **kw))
+                assert idx.stats()["scanned_queries"] > 0
+                assert np.array_equal(offs.cpu().numpy(), ro)
+                k = min(room, len(rc))
+                assert np.array_equal(cols.cpu().numpy()[:k], rc[:k])
+                assert np.all(cols.cpu().numpy()[k:] == -7)
+                if room >= len(rc):
+                    b, bd, sd = [t.cpu().numpy() for t in out[2:]]
+                    assert np.array_equal(b, rb)
+                    assert np.array_equal(bd.view(np.uint32), rbd.view(np.uint32))
+                    assert np.array_equal(sd.view(np.uint32), rsd.view(np.uint32))
