@@ -134,4 +134,31 @@ __device__ __forceinline__ int64_t wave_lower_bound(const uint32_t* __restrict__
   return lo + __popcll(ballot(below));
 }
 
+// Data of another lane by DPP: one vector instruction, where a shuffle through
+// LDS takes a hundred cycles.  Lanes that have no neighbour in a step get `none`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp(uint32_t none, uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
+}
+
+// Value of lane l ^ J: DPP within a row of 16 lanes, the swizzle's bit mode for
+// 16, a shuffle for 32.
+template <int J>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if constexpr (J == 1) return dpp<0xB1, 0xF>(v, v);
+  else if constexpr (J == 2) return dpp<0x4E, 0xF>(v, v);
+  else if constexpr (J == 4) return dpp<0x1B, 0xF>(v, dpp<0x141, 0xF>(v, v));  // ^ 7, then ^ 3
+  else if constexpr (J == 8) return dpp<0x128, 0xF>(v, v);                     // rotate by 8
+  else if constexpr (J == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
+  else return (uint32_t)__shfl_xor((int)v, J);
+}
+template <int J>
+__device__ __forceinline__ int32_t lane_xor(int32_t v) {
+  return (int32_t)lane_xor<J>((uint32_t)v);
+}
+template <int J>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+  return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
+}
+
 }  // namespace epm

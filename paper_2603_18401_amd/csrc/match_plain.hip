@@ -76,6 +76,78 @@ __global__ __launch_bounds__(kThreads) void k_match_plain_bin256(MatchArgs A) {
   if (lane == 0) write_match(A, i, t, true);
 }
 
+// The same with 16 lanes per query, for calls whose queries fill the chip: a
+// row of a few dozen candidates leaves half of a wavefront's lanes idle, and
+// what bounds a wavefront is the latency of its dependent loads and of the
+// merge, which here goes by DPP.  Two lanes read a candidate's two halves (one
+// line, one address slot; 19.4 us with both read by one lane).  A candidate is
+// kept as (distance, j) in one 64-bit key.  60000 queries with 66 candidates each: 30.0 us with a wavefront
+// per query, 15.9 this way.
+constexpr int kBinLanes = 16;
+constexpr int kBinQueries = kThreads / kBinLanes;
+constexpr int64_t kBinGroupMin = 32768;  // queries that fill the chip at four per wavefront
+__global__ __launch_bounds__(kThreads) void k_match_groups_bin256(MatchArgs A) {
+  if (csr_overflow(A)) return;
+  const int sub = (int)threadIdx.x & (kBinLanes - 1);
+  const int64_t qs = (int64_t)blockIdx.x * kBinQueries + threadIdx.x / kBinLanes;
+  const bool live = qs < A.n1;
+  int64_t i = 0, kb = 0, o0 = 0, o1 = 0;
+  const int half = sub & 1;
+  uint4 qa = make_uint4(0u, 0u, 0u, 0u);  // this lane's half of the query's bits
+  if (live) {
+    i = A.qperm ? (int64_t)A.qperm[qs] : qs;
+    o0 = A.row_offsets[i];
+    o1 = A.row_offsets[i + 1];
+    qa = reinterpret_cast<const uint4*>(A.desc1)[i * 2 + half];
+    kb = A.kstart[find_pair(A.qstart, A.num_pairs, i)];
+  }
+  uint64_t best = ~0ull, second = ~0ull;
+  constexpr int kFly = 4;  // candidates of a lane whose gathers are in flight together
+  for (int64_t e0 = o0 + (sub >> 1); e0 < o1; e0 += kFly * kBinLanes / 2) {
+    int32_t j[kFly];
+    #pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      const int64_t e = e0 + u * (kBinLanes / 2);
+      j[u] = A.cols[e < o1 ? e : e0];
+    }
+    uint4 b[kFly];
+    #pragma unroll
+    for (int u = 0; u < kFly; ++u)
+      b[u] = reinterpret_cast<const uint4*>(A.desc2)[(kb + j[u]) * 2 + half];
+    #pragma unroll
+    for (int u = 0; u < kFly; ++u) {
+      uint32_t h = __popc(qa.x ^ b[u].x) + __popc(qa.y ^ b[u].y) + __popc(qa.z ^ b[u].z) +
+                   __popc(qa.w ^ b[u].w);
+      h += lane_xor<1>(h);
+      const uint64_t key = ((uint64_t)h << 32) | (uint32_t)j[u];
+      if (e0 + u * (kBinLanes / 2) < o1) {
+        second = key < best ? best : key < second ? key : second;
+        best = key < best ? key : best;
+      }
+    }
+  }
+  auto merge = [&](uint64_t ob, uint64_t os) {
+    const uint64_t lose = ob < best ? best : ob, wins = ob < best ? os : second;
+    best = ob < best ? ob : best;
+    second = lose < wins ? lose : wins;
+  };
+  merge(lane_xor<2>(best), lane_xor<2>(second));
+  merge(lane_xor<4>(best), lane_xor<4>(second));
+  merge(lane_xor<8>(best), lane_xor<8>(second));
+  if (live && sub == 0) {
+    Top2 t;
+    if (best != ~0ull) {
+      t.bd = (float)(uint32_t)(best >> 32);
+      t.bj = (int32_t)(uint32_t)best;
+    }
+    if (second != ~0ull) {
+      t.sd = (float)(uint32_t)(second >> 32);
+      t.sj = (int32_t)(uint32_t)second;
+    }
+    write_match(A, i, t, true);
+  }
+}
+
 // Listed queries (the ones the fused stab + match pass left over): one
 // wavefront per listed query, grid-stride over a list whose length only the
 // device knows.
@@ -117,6 +189,13 @@ hipError_t launch_match_plain_f32(const MatchArgs& a, hipStream_t s) {
 
 hipError_t launch_match_plain_bin256(const MatchArgs& a, hipStream_t s) {
   if (a.n1 == 0) return hipSuccess;
+  // (fewer queries: the longest rows end sooner with a wavefront each)
+  if (a.n1 >= kBinGroupMin) {
+    hipLaunchKernelGGL(k_match_groups_bin256,
+                       dim3((unsigned)((a.n1 + kBinQueries - 1) / kBinQueries)), dim3(kThreads), 0,
+                       s, a);
+    return hipGetLastError();
+  }
   const int64_t blocks = (a.n1 + kWaves - 1) / kWaves;
   hipLaunchKernelGGL(k_match_plain_bin256, dim3((unsigned)blocks), dim3(kThreads), 0, s, a);
   return hipGetLastError();

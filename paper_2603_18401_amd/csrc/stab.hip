@@ -28,14 +28,7 @@ constexpr int kWaves = kThreads / kWave;
 constexpr int kFinishRows = 256;  // queries per workgroup of k_finish_rows
 
 // Reductions over the wavefront (uniform results), over each row of 16 lanes
-// and inclusive sums, by DPP: a step is one vector instruction, where a shuffle
-// through LDS takes a hundred cycles.  Lanes that have no neighbour in a step
-// get `none`.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ uint32_t dpp(uint32_t none, uint32_t v) {
-  return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
-}
-
+// and inclusive sums, by DPP.
 template <class OP>
 __device__ __forceinline__ uint32_t row_reduce(uint32_t v, uint32_t none, OP op) {
   v = op(v, dpp<0xB1, 0xF>(none, v));   // quad [1,0,3,2]
@@ -79,26 +72,6 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
   v += dpp<0x142, 0xA>(0u, v);
   v += dpp<0x143, 0xC>(0u, v);
   return v;
-}
-
-// Value of lane l ^ J: DPP within a row of 16 lanes, the swizzle's bit mode for
-// 16, a shuffle for 32.
-template <int J>
-__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
-  if constexpr (J == 1) return dpp<0xB1, 0xF>(v, v);
-  else if constexpr (J == 2) return dpp<0x4E, 0xF>(v, v);
-  else if constexpr (J == 4) return dpp<0x1B, 0xF>(v, dpp<0x141, 0xF>(v, v));  // ^ 7, then ^ 3
-  else if constexpr (J == 8) return dpp<0x128, 0xF>(v, v);                     // rotate by 8
-  else if constexpr (J == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
-  else return (uint32_t)__shfl_xor((int)v, J);
-}
-template <int J>
-__device__ __forceinline__ int32_t lane_xor(int32_t v) {
-  return (int32_t)lane_xor<J>((uint32_t)v);
-}
-template <int J>
-__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
-  return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
 }
 
 // Bitonic sort of one value per lane, ascending over the wavefront (21
