@@ -161,4 +161,51 @@ __device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
   return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
 }
 
+// Reductions over the wavefront (uniform results), over each row of 16 lanes
+// and inclusive sums, by DPP.
+template <class OP>
+__device__ __forceinline__ uint32_t row_reduce(uint32_t v, uint32_t none, OP op) {
+  v = op(v, dpp<0xB1, 0xF>(none, v));   // quad [1,0,3,2]
+  v = op(v, dpp<0x4E, 0xF>(none, v));   // quad [2,3,0,1]
+  v = op(v, dpp<0x141, 0xF>(none, v));  // half-row mirror
+  v = op(v, dpp<0x140, 0xF>(none, v));  // row mirror
+  return v;
+}
+
+template <class OP>
+__device__ __forceinline__ uint32_t wave_reduce(uint32_t v, uint32_t none, OP op) {
+  v = row_reduce(v, none, op);
+  // rows 1 and 3 take lane 15 of the row below, rows 2 and 3 lane 31; lane 63
+  // ends with all rows
+  v = op(v, dpp<0x142, 0xA>(none, v));
+  v = op(v, dpp<0x143, 0xC>(none, v));
+  return (uint32_t)__builtin_amdgcn_readlane((int)v, kWave - 1);
+}
+
+struct OpSum {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; }
+};
+struct OpMin {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a < b ? a : b; }
+};
+struct OpMax {
+  __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a > b ? a : b; }
+};
+
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) { return wave_reduce(v, 0u, OpSum()); }
+__device__ __forceinline__ uint32_t wave_min_u32(uint32_t v) {
+  return wave_reduce(v, 0xFFFFFFFFu, OpMin());
+}
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) { return wave_reduce(v, 0u, OpMax()); }
+
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+  v += dpp<0x111, 0xF>(0u, v);  // one, two, four and eight lanes below, in the row
+  v += dpp<0x112, 0xF>(0u, v);
+  v += dpp<0x114, 0xF>(0u, v);
+  v += dpp<0x118, 0xF>(0u, v);
+  v += dpp<0x142, 0xA>(0u, v);
+  v += dpp<0x143, 0xC>(0u, v);
+  return v;
+}
+
 }  // namespace epm

@@ -97,10 +97,11 @@ __global__ __launch_bounds__(kXcdThreads) void k_xcd_lpt_order(const uint32_t* _
   for (int i = tid; i < nx; i += kXcdThreads)
     atomicAdd(&h[cost_bucket(cost[xcd_member(i, x, n)])], 1u);
   __syncthreads();
-  if (tid < kCostBuckets) {
-    uint32_t start = 0;
-    for (int c = kCostBuckets - 1; c > tid; --c) start += h[c];
-    cursor[tid] = start;
+  if (tid < kWave) {  // lane l starts bucket kWave - l behind the dearer ones
+    static_assert(kCostBuckets == kWave + 1, "the last lane starts bucket 0 too");
+    const uint32_t own = h[kWave - tid], incl = wave_scan_u32(own);
+    cursor[kWave - tid] = incl - own;
+    if (tid == kWave - 1) cursor[0] = incl;
   }
   __syncthreads();
   for (int i = tid; i < nx; i += kXcdThreads) {
