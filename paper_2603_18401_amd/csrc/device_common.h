@@ -141,24 +141,45 @@ __device__ __forceinline__ uint32_t dpp(uint32_t none, uint32_t v) {
   return (uint32_t)__builtin_amdgcn_update_dpp((int)none, (int)v, CTRL, ROWS, 0xF, false);
 }
 
-// Value of lane l ^ J: DPP within a row of 16 lanes, the swizzle's bit mode for
-// 16, a shuffle for 32.
+// Value of lane l ^ J: DPP within a row of 16 lanes, swaps of rows (halves) of
+// two copies beyond.
 template <int J>
 __device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
   if constexpr (J == 1) return dpp<0xB1, 0xF>(v, v);
   else if constexpr (J == 2) return dpp<0x4E, 0xF>(v, v);
   else if constexpr (J == 4) return dpp<0x1B, 0xF>(v, dpp<0x141, 0xF>(v, v));  // ^ 7, then ^ 3
   else if constexpr (J == 8) return dpp<0x128, 0xF>(v, v);                     // rotate by 8
-  else if constexpr (J == 16) return (uint32_t)__builtin_amdgcn_ds_swizzle((int)v, 0x401F);
-  else return (uint32_t)__shfl_xor((int)v, J);
+  else if constexpr (J == 16) {
+    // odd rows of the first with even rows of the second: rows 0 0 2 2 | 1 1 3 3
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (lane_id() & 16) ? r[0] : r[1];
+  } else {
+    static_assert(J == 32, "one lane bit");
+    // upper half of the first with the lower half of the second
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (lane_id() & 32) ? r[0] : r[1];
+  }
 }
 template <int J>
 __device__ __forceinline__ int32_t lane_xor(int32_t v) {
   return (int32_t)lane_xor<J>((uint32_t)v);
 }
 template <int J>
+__device__ __forceinline__ float lane_xor(float v) {
+  return __uint_as_float(lane_xor<J>(__float_as_uint(v)));
+}
+template <int J>
 __device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
   return ((uint64_t)lane_xor<J>((uint32_t)(v >> 32)) << 32) | lane_xor<J>((uint32_t)v);
+}
+
+// Row g of 16 lanes in every row.
+template <int G>
+__device__ __forceinline__ uint32_t row_bcast(uint32_t v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  const uint32_t w = r[G & 1];  // rows G & 1 and 2 + (G & 1), twice each
+  const auto h = __builtin_amdgcn_permlane32_swap(w, w, false, false);
+  return h[G >> 1];
 }
 
 // Reductions over the wavefront (uniform results), over each row of 16 lanes

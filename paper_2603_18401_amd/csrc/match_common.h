@@ -61,17 +61,23 @@ __device__ __forceinline__ Top2 merge_top2(const Top2& x, const Top2& y) {
   return r;
 }
 
+template <int J>
+__device__ __forceinline__ Top2 lane_xor_top2(const Top2& t) {
+  Top2 o;
+  o.bd = lane_xor<J>(t.bd);
+  o.bj = lane_xor<J>(t.bj);
+  o.sd = lane_xor<J>(t.sd);
+  o.sj = lane_xor<J>(t.sj);
+  return o;
+}
+
 __device__ __forceinline__ Top2 wave_merge_top2(Top2 t) {
-  #pragma unroll
-  for (int off = 1; off < kWave; off <<= 1) {
-    Top2 o;
-    o.bd = __shfl_xor(t.bd, off);
-    o.bj = __shfl_xor(t.bj, off);
-    o.sd = __shfl_xor(t.sd, off);
-    o.sj = __shfl_xor(t.sj, off);
-    t = merge_top2(t, o);
-  }
-  return t;
+  t = merge_top2(t, lane_xor_top2<1>(t));
+  t = merge_top2(t, lane_xor_top2<2>(t));
+  t = merge_top2(t, lane_xor_top2<4>(t));
+  t = merge_top2(t, lane_xor_top2<8>(t));
+  t = merge_top2(t, lane_xor_top2<16>(t));
+  return merge_top2(t, lane_xor_top2<32>(t));
 }
 
 // Dense (query, candidate) lists of the window kernels: entry e of query q is

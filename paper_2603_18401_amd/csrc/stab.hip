@@ -977,8 +977,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       wave_sync_lds();
       int set = 0;
       for (int k = g; k < kKeepJ / 32; k += 4) set += __popc(hit_bits(lq)[k]);
-      set += __shfl_xor(set, 16);
-      set += __shfl_xor(set, 32);
+      set += lane_xor<16>(set);
+      set += lane_xor<32>(set);
       csr_ok = here && set == n;
       __syncthreads();  // the window's j are complete
       if (fusable && total_len > 0)
@@ -1357,15 +1357,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         }
       }
       // the four parts of a query are adjacent lanes and hold distinct hits
-      #pragma unroll
-      for (int off = 1; off < 4; off <<= 1) {
-        Top2 o;
-        o.bd = __shfl_xor(best.bd, off);
-        o.bj = __shfl_xor(best.bj, off);
-        o.sd = __shfl_xor(best.sd, off);
-        o.sj = __shfl_xor(best.sj, off);
-        best = merge_top2(best, o);
-      }
+      best = merge_top2(best, lane_xor_top2<1>(best));
+      best = merge_top2(best, lane_xor_top2<2>(best));
       if (part == 0 && q < T.count) {
         const bool empty = qmode[q] == kQueryEmpty;
         A.qrec[qidx[q]] = query_record(empty ? 0u : cnt[q], A.ratio, best, mine || empty);
@@ -1424,10 +1417,10 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         #pragma unroll
         for (int u = 0; u < 8; ++u) qx[u] = ld ? m[u] : make_float4(0.f, 0.f, 0.f, 0.f);
       }
-      qn_part += __shfl_xor(qn_part, 16);
-      qe_part += __shfl_xor(qe_part, 16);
-      qn_part += __shfl_xor(qn_part, 32);
-      qe_part += __shfl_xor(qe_part, 32);
+      qn_part += lane_xor<16>(qn_part);
+      qe_part += lane_xor<16>(qe_part);
+      qn_part += lane_xor<32>(qn_part);
+      qe_part += lane_xor<32>(qe_part);
       // per-query bound terms, inflated for the FP32 sums (2^-24 per term)
       const float q_nb = sqrtf(qn_part) * (1.0f + 2e-5f);
       const float q_db = sqrtf(qe_part) * (1.0f + 2e-5f) + 1e-30f;
@@ -1486,8 +1479,10 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
                 }
               }
             }
-            #pragma unroll
-            for (int off = 1; off < kTpr; off <<= 1) sn += __shfl_xor(sn, off);
+            static_assert(kTpr == 8, "eight threads per row");
+            sn += lane_xor<1>(sn);
+            sn += lane_xor<2>(sn);
+            sn += lane_xor<4>(sn);
             if (part4 == 0) {
               if constexpr (F8) {
                 // w^ = s c: |w^|^2 = s^2 |c|^2, and the MFMA scores of the
@@ -1588,14 +1583,14 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         }
         bool bad = st.bad || !(u1 == u1) || !(u2 == u2) || !(dmin == dmin);
         // the row's U2 and smallest dropped bound over its four lanes
-        #pragma unroll
-        for (int off = 16; off < kWave; off <<= 1) {
-          const float o1 = __shfl_xor(u1, off), o2 = __shfl_xor(u2, off);
+        const auto join = [&](float o1, float o2, float od, uint32_t ob) {
           u2 = fminf(fmaxf(u1, o1), fminf(u2, o2));
           u1 = fminf(u1, o1);
-          dmin = fminf(dmin, __shfl_xor(dmin, off));
-          bad |= __shfl_xor((int)bad, off) != 0;
-        }
+          dmin = fminf(dmin, od);
+          bad |= ob != 0u;
+        };
+        join(lane_xor<16>(u1), lane_xor<16>(u2), lane_xor<16>(dmin), lane_xor<16>((uint32_t)bad));
+        join(lane_xor<32>(u1), lane_xor<32>(u2), lane_xor<32>(dmin), lane_xor<32>((uint32_t)bad));
         // nothing dropped (dmin = +inf): every candidate that can be best or
         // second is kept, including rows of fewer than two candidates (U2 = +inf)
         cert = mine2 && !bad && (dmin == __builtin_inff() || dmin > u2);
@@ -1606,9 +1601,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         for (int t = 0; t < kKeep; ++t)
           if (cert && st.pk[t] != kNoPick && klo[t] <= u2) tmask |= 1u << t;
         const uint32_t myn = (uint32_t)__popc(tmask);
-        const int qlane = lane & (kQPerWave - 1);
-        const uint32_t n0 = (uint32_t)__shfl((int)myn, qlane), n1 = (uint32_t)__shfl((int)myn, qlane + 16),
-                       n2 = (uint32_t)__shfl((int)myn, qlane + 32), n3 = (uint32_t)__shfl((int)myn, qlane + 48);
+        const uint32_t n0 = row_bcast<0>(myn), n1 = row_bcast<1>(myn), n2 = row_bcast<2>(myn),
+                       n3 = row_bcast<3>(myn);
         const uint32_t before = (g > 0 ? n0 : 0u) + (g > 1 ? n1 : 0u) + (g > 2 ? n2 : 0u);
         const uint32_t qtotal = n0 + n1 + n2 + n3;
         uint16_t* mylist = qtask + q2 * kQTasks;
@@ -1636,14 +1630,16 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         if (rounds > 0) wslice(0, wcur);
         for (uint32_t rd = 0; rd < rounds; ++rd) {
           if (rd + 1 < rounds) wslice(rd + 1, wnext);
-          float sum = 0.0f;
-          #pragma unroll
-          for (int gp = 0; gp < 4; ++gp) {
-            float acc = sum;
+          const auto quarter = [&](float acc) {
             #pragma unroll
             for (int u = 0; u < 8; ++u) acc = canonical_step4(acc, qx[u], wcur[u]);
-            sum = __shfl(acc, qlane + 16 * gp);  // quarter gp's result
-          }
+            return __float_as_uint(acc);
+          };
+          // quarter by quarter, each one's result from its own lane group
+          float sum = __uint_as_float(row_bcast<0>(quarter(0.0f)));
+          sum = __uint_as_float(row_bcast<1>(quarter(sum)));
+          sum = __uint_as_float(row_bcast<2>(quarter(sum)));
+          sum = __uint_as_float(row_bcast<3>(quarter(sum)));
           if (rd < qtotal && g == 0) {
             best.insert(sum, sJ_keep[mylist[rd]]);
             ++evals;
@@ -1807,11 +1803,8 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_rows(StabArgs A,
   int64_t incl = rec.x;
   if (wave < kFinishWaves) {
     s_len[tid] = rec.x;
-    #pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-      const int64_t o = __shfl_up(incl, off);
-      if (lane >= off) incl += o;
-    }
+    // (the halves' sums over a wavefront fit 32 bits)
+    incl = (int64_t)wave_scan_u32(rec.x & 0xFFFFu) + ((int64_t)wave_scan_u32(rec.x >> 16) << 16);
     if (lane == kWave - 1) s_sum[wave] = incl;
   }
   __syncthreads();
