@@ -25,7 +25,7 @@
 // 1300 candidates per query, 1290 with the lanes' own lists, free of branches,
 // and the rows' write positions in lanes.  What bounds it now: the instructions
 // of 16 x 64 exact tests, appends and list steps per block, at three wavefronts
-// per SIMD; the row appends, 145 of a tile's 500 thousand cycles, most.)
+// per SIMD; the appends take the largest share.)
 // The kPicks best keys of a query are re-ranked with canonical FP32 chains on
 // the FP32 rows.  The last kept key bounds every other candidate from below
 // (the rounding bound of the BF16 rows, of the MFMA accumulation and of the
@@ -92,12 +92,6 @@ __device__ __forceinline__ int select_bit(uint64_t w, uint32_t k) {
   if (k >= c) { k -= c; w >>= 2; pos += 2; }
   if (k >= ((uint32_t)w & 1u)) pos += 1;
   return pos;
-}
-
-__device__ __forceinline__ void wave_lds_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
