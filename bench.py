@@ -284,8 +284,8 @@ def cpu_model():
 
 
 def host_threads():
-    """Threads for the CPU oracle: the cores this process may run on (on the
-    GPU machine that is the CPU share of one GPU, 16 threads)."""
+    """Threads for the CPU oracle: the cores this process may run on, at most
+    the 16 that go with one GPU."""
     try:
         n = len(os.sched_getaffinity(0))
     except AttributeError:
