@@ -99,8 +99,9 @@ __global__ __launch_bounds__(kThreads) void k_match_window_mfma(MatchArgs A) {
       q_o0[q] = o0;
       q_k[q] = (uint32_t)k;
       // rows enter the dense list in order while they fit; the rest are
-      // evaluated by gathers
-      uint32_t incl = (uint32_t)(k < kMaxPairs ? k : kMaxPairs);
+      // evaluated by gathers (a row longer than the list counts as one entry
+      // more than it holds, so that neither it nor a later one fits)
+      uint32_t incl = (uint32_t)(k <= kMaxPairs ? k : kMaxPairs + 1);
       #pragma unroll
       for (int off = 1; off < kWave; off <<= 1) {
         const uint32_t o = __shfl_up(incl, off);
