@@ -649,7 +649,9 @@ __device__ __forceinline__ void bounds_from(float at, float nb, float q_nb, floa
   // sqrt(at +- em) from the hardware reciprocal square root (within a few
   // ulps): the 1e-6 factors cover it; arguments under 2^-100 take the
   // trivially valid bounds 0 and 2^-50
-  const float th = fmaxf(at, 0.0f) + em;
+  // (a row term past FP16's range is +inf: the upper bound is +inf then, and
+  // not the NaN that inf * rsqrt(inf) would make of it)
+  const float th = fminf(fmaxf(at, 0.0f) + em, 0x1.fffffep127f);
   const float tl = at - em;
   const float r_hi = th > 0x1p-100f ? th * __builtin_amdgcn_rsqf(th) * (1.0f + 1e-6f) : 0x1p-50f;
   const float r_lo = tl > 0x1p-100f ? tl * __builtin_amdgcn_rsqf(tl) * (1.0f - 1e-6f) : 0.0f;
