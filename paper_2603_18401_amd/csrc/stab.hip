@@ -599,7 +599,9 @@ struct BfKeep {
   // sorted insertion: entry t moves down one place when A goes before entry
   // t - 1, takes A when A goes between them, and the last entry drops out
   __device__ __forceinline__ void add(float at, uint32_t p, float nb, uint32_t ew) {
-    bad |= !(at == at);
+    // an infinite A (norms whose squares overflow) may stand for any distance:
+    // it is not kept below, and +inf would read as "nothing pushed out"
+    bad |= !(fabsf(at) < __builtin_inff());
     nb_max = fmaxf(nb_max, nb);
     ew_max = ew_max > ew ? ew_max : ew;
     if constexpr (K == 3) {  // written out: the compiler keeps it free of branches
