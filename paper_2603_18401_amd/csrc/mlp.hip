@@ -129,18 +129,44 @@ __device__ __forceinline__ void split8(const float (&x)[8], bf16x8 (&part)[3]) {
     part[p] = __builtin_bit_cast(bf16x8, make_uint4(w[p][0], w[p][1], w[p][2], w[p][3]));
 }
 
-// The network's z by one thread, left to right (weights in LDS).
+// The network's z by one thread, left to right (weights in LDS): kPlainRows
+// units of the second layer side by side, four inputs of each at a time, so
+// that the first layer is worked out twice in all and no more registers are
+// held than beside the matrix form (with the whole first layer in registers
+// the kernel loses a wavefront per SIMD).  What bounds it: the weights' LDS
+// reads.  2 M keypoints with one in every 64 that comes here take 487 us (1961
+// with the first layer worked out anew for every unit; a kernel of its own,
+// one thread per keypoint, takes 275), without any 74.
+constexpr int kPlainRows = 32;
 __device__ float infer_plain(const float* w, const float (&x)[kIn]) {
   float z = w[kOffB3];
-  for (int r = 0; r < kH; ++r) {
-    float a = w[kOffB2 + r];
-    for (int u = 0; u < kH; ++u) {
-      float h = w[kOffB1 + u];
+  #pragma unroll 1
+  for (int r0 = 0; r0 < kH; r0 += kPlainRows) {
+    float a[kPlainRows];
+    #pragma unroll
+    for (int r = 0; r < kPlainRows; ++r) a[r] = w[kOffB2 + r0 + r];
+    #pragma unroll 1
+    for (int u = 0; u < kH; u += 4) {
+      float h[4];
       #pragma unroll
-      for (int c = 0; c < kIn; ++c) h = fmaf(w[kOffW1 + u * kIn + c], x[c], h);
-      a = fmaf(w[kOffW2 + r * kH + u], fmaxf(h, 0.0f), a);
+      for (int e = 0; e < 4; ++e) {
+        h[e] = w[kOffB1 + u + e];
+        #pragma unroll
+        for (int c = 0; c < kIn; ++c) h[e] = fmaf(w[kOffW1 + (u + e) * kIn + c], x[c], h[e]);
+        h[e] = fmaxf(h[e], 0.0f);
+      }
+      #pragma unroll
+      for (int r = 0; r < kPlainRows; ++r) {
+        static_assert(kOffW2 % 4 == 0 && kH % 4 == 0, "aligned quadruples");
+        const float4 k = *reinterpret_cast<const float4*>(w + kOffW2 + (r0 + r) * kH + u);
+        a[r] = fmaf(k.x, h[0], a[r]);
+        a[r] = fmaf(k.y, h[1], a[r]);
+        a[r] = fmaf(k.z, h[2], a[r]);
+        a[r] = fmaf(k.w, h[3], a[r]);
+      }
     }
-    z = fmaf(w[kOffW3 + r], fmaxf(a, 0.0f), z);
+    #pragma unroll
+    for (int r = 0; r < kPlainRows; ++r) z = fmaf(w[kOffW3 + r0 + r], fmaxf(a[r], 0.0f), z);
   }
   return z;
 }
@@ -149,7 +175,7 @@ __global__ __launch_bounds__(kInferThreads, 2) void k_eps_infer(const float* __r
                                                              int64_t n,
                                                              const float* __restrict__ params,
                                                              float* __restrict__ eps) {
-  __shared__ float w[kParams];
+  __shared__ __attribute__((aligned(16))) float w[kParams];
   __shared__ uint4 parts[kInferWaves][3][kWave];  // a wavefront's split features
   const int lane = lane_id(), wave = wave_id();
   const int c = lane & 15, g = lane >> 4;
@@ -241,7 +267,8 @@ __global__ __launch_bounds__(kInferThreads, 2) void k_eps_infer(const float* __r
       zp += __shfl_xor(zp, 32);
       z = g == q ? zp + b3 : z;  // lane 16 q + c keeps keypoint 16 q + c
     }
-    if (plain_all || ballot(!fine) != 0ull) z = infer_plain(w, x);
+    // (a keypoint's tolerance does not depend on the others of its wavefront)
+    if (plain_all || !fine) z = infer_plain(w, x);
     if (j < n) eps[j] = fminf(fmaxf(softplus_f(z), kEpsMin), kEpsMax);
     __builtin_amdgcn_wave_barrier();  // the parts are read before they are written again
   }
