@@ -266,8 +266,7 @@ epm_status epm_descriptor_distances(epm_dtype dtype, int32_t dim, const void* de
  * contract as epm_query_candidates) and best_idx / best_dist / second_dist
  * (as epm_match, ratio 0 = off).  When nnz_host is NULL and the candidates
  * exceed `capacity`, the match outputs are incomplete (row_offsets[N1] tells);
- * with nnz_host, EPM_ERR_CAPACITY is returned as in epm_query_candidates (the
- * match outputs are incomplete then too).
+ * with nnz_host, EPM_ERR_CAPACITY is returned as in epm_query_candidates.
  */
 epm_status epm_query_match(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
                            int32_t* col_indices, int64_t capacity, int64_t* nnz_host,

@@ -458,6 +458,7 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.reps = idx->at<float>(L.reps);
   A.rinv = idx->at<uint32_t>(L.rinv);
   A.counts = idx->at<uint32_t>(L.counts);
+  A.whole_rows = false;
   A.row_sums = nullptr;
   A.qrec = nullptr;
   A.row_offsets = row_offsets;
@@ -584,7 +585,7 @@ hipError_t prepare_wide_rows(epm_index* idx, StabArgs& A, hipStream_t stream) {
   return launch_round_rows(A, (int64_t)n2, idx->at<int64_t>(idx->L.pre_pairs), stream);
 }
 
-// Reads the counters that the pass over the rows left (waits for the stream):
+// Reads the counters of the tile pass and of the pass over the rows (waits for the stream):
 // the total of candidates into *nnz_host, and whether a later pass has rows to
 // write or to match.  EPM_ERR_CAPACITY when the rows did not fit.
 epm_status read_totals(const epm_index* idx, const StabArgs& A, int64_t* nnz_host, bool* more,
@@ -841,6 +842,7 @@ epm_status enqueue_query_match(epm_index* idx, StabArgs& A, int64_t* row_offsets
   A.best_dist = c.best_dist;
   A.second_dist = c.second_dist;
   A.qrec = idx->at<uint4>(idx->L.qrec);
+  A.whole_rows = nnz_host != nullptr;
   // counters of the wide-row selection (certified / listed rows)
   A.match_stats = idx->at<unsigned long long>(idx->L.match_stats);  // cleared with the counters
   idx->have_match_stats = true;
@@ -1031,6 +1033,7 @@ epm_status epm_query_candidates(epm_index* idx, const float* kp1_xy, int64_t* ro
   if (capacity > 0 && !col_indices) return EPM_ERR_ARG;
   const int64_t n1 = idx->N1;
   StabArgs A = stab_args(idx, kp1_xy, row_offsets, col_indices, capacity);
+  A.whole_rows = nnz_host != nullptr;
   const epm_status st = enqueue_count(idx, A, row_offsets, stream);
   if (st != EPM_OK) return st;
   if (n1 > 0) {

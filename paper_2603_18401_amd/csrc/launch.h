@@ -94,6 +94,10 @@ struct StabArgs {
   const float* reps;
   const uint32_t* rinv;
   uint32_t* counts;
+  // nothing but the row offsets is written when the rows exceed `capacity` (a
+  // call that waits for the total and returns an error then); the tile pass
+  // adds the total up in stats[kStatNnz]
+  bool whole_rows;
   uint64_t* row_sums;  // look-back words of launch_finish_rows, cleared by the window pass
   // fused selection: per query (original index) one 16-byte record {row
   // length, best index, best distance, second distance} written in one store
@@ -174,7 +178,7 @@ hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s);
 constexpr int kResidentTiles = 768;
 // Device-wide counters of a query: the lengths of its two queues (long rows
 // for the fill pass, queries left over by the fused passes), whether any tile
-// has wide rows, and the total of candidates.
+// has wide rows, and (whole_rows) the total of candidates.
 constexpr int kStatLongRows = 0, kStatRest = 1, kStatWide = 2, kStatNnz = 3;
 constexpr int kNumStats = 4;
 // Clears the kNumStats counters unless stats is NULL, the kSchedWords
@@ -203,8 +207,8 @@ constexpr int kStabCount = 0, kStabF32 = 1, kStabBF16 = 2, kStabFP8 = 3, kCsrBF1
 // BF16 and FP8 passes, 512 for the others).
 hipError_t launch_stab_tiles(const StabArgs& a, int grid, int mode, int chunk, hipStream_t s);
 constexpr int32_t kMatchDeferred = INT32_MIN;
-// After launch_stab_tiles: row offsets (offsets[n1] and stats[kStatNnz] the
-// total), the fused pass's matches and the parked rows.  a.row_sums:
+// After launch_stab_tiles: row offsets (offsets[n1] the total), the fused
+// pass's matches and the parked rows (whole_rows: if they fit).  a.row_sums:
 // finish_state_words(n1) words, cleared by launch_tile_windows; partials:
 // scan_partials_count(n1) words.
 int64_t finish_state_words(int64_t n1);

@@ -876,6 +876,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
   // scanned, angle hits, brute-force and empty queries; BF16 fused: rows
   // ranked on bounds, rows left uncertified, exact distances evaluated
   __shared__ uint32_t tile_stats[kTileCounts];
+  __shared__ unsigned long long tile_nnz;  // whole_rows: the tile's candidates
   __shared__ int next_tile;
 
   // a caller's CSR that did not fit its buffer is incomplete: nothing is written
@@ -919,6 +920,7 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       cnt[lane] = 0;
       if (lane < kTileCounts) tile_stats[lane] = 0u;
       if (lane < 2) j_span[lane] = 0u;
+      if (lane == 0) tile_nnz = 0ull;
     }
     if constexpr (!CSR) {
       for (int k = tid; k < 2 * kOrderBuckets; k += kThreads) scratch[kKeepJ + k] = 0u;
@@ -1222,6 +1224,12 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
           A.stats[kStatWide] = 1ull;
           if (A.pair_wide) atomicAdd(&A.pair_wide[T.pair], 1u);
         }
+      }
+      if (A.whole_rows) {  // (the halves' sums over a wavefront fit 32 bits)
+        const uint32_t len = own && qmode[lq] != kQueryEmpty ? cnt[lq] : 0u;
+        const uint64_t sum =
+            wave_sum_u32(len & 0xFFFFu) + ((uint64_t)wave_sum_u32(len >> 16) << 16);
+        if (lane == 0) atomicAdd(&tile_nnz, (unsigned long long)sum);
       }
     }
     (void)brute;
@@ -1725,6 +1733,8 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
         const uint32_t c = tile_stats[tid == 0 ? 4 : tid == 1 ? 5 : tid == 2 ? 7 : 6];
         if (c) atomicAdd(&A.match_stats[tid], (unsigned long long)c);
       }
+    } else if (A.whole_rows && tid == kWave) {
+      atomicAdd(&A.stats[kStatNnz], tile_nnz);
     } else if (A.tile_counts && tid == 0) {
       const uint64_t nb = tile_stats[2];
       unsigned long long* tc = A.tile_counts + (int64_t)tile * kTileCounts;
@@ -1774,6 +1784,11 @@ constexpr uint64_t kSumOwn = 1ull << 62, kSumAll = 2ull << 62, kSumMask = (1ull 
 
 __device__ __forceinline__ uint32_t row_length(const StabArgs& A, int64_t i) {
   return A.qrec ? A.qrec[i].x : A.counts[i];
+}
+
+// The rows do not fit, and the caller is told so instead (uniform).
+__device__ __forceinline__ bool rows_dropped(const StabArgs& A) {
+  return A.whole_rows && (int64_t)A.stats[kStatNnz] > A.capacity;
 }
 
 // Sum of the row lengths before workgroup b, by its first kFinishRows threads
@@ -1830,6 +1845,7 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_rows(StabArgs A,
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const int64_t b = blockIdx.x, i0 = b * kFinishRows, i = i0 + tid;
   const bool mine = tid < kFinishRows && i < A.n1;  // this thread's query
+  const bool dropped = rows_dropped(A);
   uint4 rec = make_uint4(0u, (uint32_t)kMatchDeferred, 0u, 0u);
   if (mine) {
     if (A.qrec) rec = A.qrec[i];
@@ -1871,8 +1887,8 @@ __global__ __launch_bounds__(kFinishThreads) void k_finish_rows(StabArgs A,
   if (mine) offsets[i] = before + s_off[tid];
   if (b == (int64_t)gridDim.x - 1 && tid == 0) {
     offsets[A.n1] = before + total;
-    A.stats[kStatNnz] = (unsigned long long)(before + total);
   }
+  if (dropped) return;
   if (mine && (int32_t)rec.y != kMatchDeferred) {
     A.best_idx[i] = (int32_t)rec.y;
     A.best_dist[i] = __uint_as_float(rec.z);
@@ -1924,8 +1940,7 @@ __global__ __launch_bounds__(kThreads) void k_copy_rows(StabArgs A) {
   // kCopyUnroll consecutive rows per group of kCopyLanes, their loads in flight together
   const int64_t i0 =
       ((int64_t)blockIdx.x * kCopyQueries + (threadIdx.x / kCopyLanes)) * kCopyUnroll;
-  if (blockIdx.x == 0 && threadIdx.x == 0)
-    A.stats[kStatNnz] = (unsigned long long)A.row_offsets[A.n1];
+  if (rows_dropped(A)) return;
   if (i0 >= A.n1) return;  // whole groups of kCopyLanes leave together
   // each slot's first piece is read beside the row offsets (before the row's
   // length is known); its first word tells whether the row was parked
@@ -1963,7 +1978,7 @@ __global__ __launch_bounds__(kThreads) void k_copy_rows(StabArgs A) {
 // writes the query's match.
 __global__ __launch_bounds__(kThreads) void k_write_matches(StabArgs A) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= A.n1) return;
+  if (rows_dropped(A) || i >= A.n1) return;
   const uint4 r = A.qrec[i];
   if ((int32_t)r.y == kMatchDeferred) return;
   A.best_idx[i] = (int32_t)r.y;
