@@ -262,17 +262,22 @@ def _check(st, what):
 class PairSpec:
     """One image pair: F (3x3, row-major), image-2 size, keypoint counts."""
 
+    _row = None  # F where its memory is nine doubles in a row
+
     def __init__(self, F, w2, h2, m, n):
-        self.F = F
+        self.F = np.asarray(F, dtype=np.float64).reshape(9)
         self.w2, self.h2, self.m, self.n = int(w2), int(h2), int(m), int(n)
 
     @property
     def F(self):
-        return self._F
+        return self.__dict__["F"]
 
     @F.setter
     def F(self, F):
-        self._F = np.ascontiguousarray(F, dtype=np.float64).reshape(9)
+        # kept as it is: what is written to it later counts
+        self.__dict__["F"] = F
+        row = type(F) is np.ndarray and F.shape == (9,) and F.dtype == np.float64
+        self._row = F if row and F.dtype.isnative and F.flags.c_contiguous else None
 
 
 # the fields of epm_pair after F
@@ -283,18 +288,37 @@ assert 72 + _PAIR_TAIL.size == ctypes.sizeof(_Pair)
 def _pair_array(specs):
     """The epm_pair array of a batch and its keypoint totals (N1, N2), as one
     byte string: 0.15 ms for 512 pairs, where assigning the ctypes fields one
-    by one took 1.2 ms, a third of the batch's time on the GPU."""
+    by one takes 1.2 ms, a third of the batch's time on the GPU.  Specs that
+    hold anything else than nine doubles and integers in range are assigned
+    field by field."""
     parts = []
     q = k = 0
     pack = _PAIR_TAIL.pack
-    for s in specs:
-        m, n = s.m, s.n
-        parts.append(s._F if type(s) is PairSpec
-                     else np.ascontiguousarray(s.F, dtype=np.float64).reshape(9))
-        parts.append(pack(s.w2, s.h2, q, m, k, n))
-        q += m
-        k += n
+    try:
+        for s in specs:
+            row = s._row if type(s) is PairSpec else None
+            if row is None:
+                return _pair_array_by_field(specs)
+            m, n = s.m, s.n
+            parts.append(row)
+            parts.append(pack(s.w2, s.h2, q, m, k, n))
+            q += m
+            k += n
+    except struct.error:
+        return _pair_array_by_field(specs)
     return (_Pair * len(specs)).from_buffer(bytearray(b"".join(parts))), q, k
+
+
+def _pair_array_by_field(specs):
+    arr = (_Pair * len(specs))()
+    q = k = 0
+    for a, s in zip(arr, specs):
+        a.F[:] = [float(v) for v in s.F]
+        a.w2, a.h2 = s.w2, s.h2
+        a.q_begin, a.m, a.k_begin, a.n = q, s.m, k, s.n
+        q += s.m
+        k += s.n
+    return arr, q, k
 
 
 class Index:
