@@ -29,7 +29,7 @@ struct Layout {
   size_t qkey, qflag, qk0, qk1, qv1, qhist0, qhist1, counts, qrec, partials, staging, stats,
       long_rows;
   size_t windows, match_stats, sched, tile_cost, order, block_tile, rest, tile_wide,
-      pair_wide, pre_pairs, qline, tile_q, tile_counts;
+      pair_wide, groups, pre_pairs, qline, tile_q, tile_counts;
   size_t total;
 };
 
@@ -108,7 +108,10 @@ Layout make_layout(int P, int64_t n1, int64_t n2, const Tiles& T) {
   L.rest = take(sizeof(uint32_t) * N1);
   L.tile_wide = take(sizeof(uint32_t) * ts);
   L.pair_wide = take(sizeof(uint32_t) * P);
+  // what the sort says about the queries' groups is read by the window pass,
+  // before the list of pairs is made for the wide rows
   L.pre_pairs = take(sizeof(int64_t) * (2 * (size_t)P + 2));
+  L.groups = L.pre_pairs;
   L.qline = take(sizeof(double4) * N1);
   // the tiles' queries take the place of what only the sort of the records
   // needed, where they fit
@@ -266,7 +269,7 @@ void make_segs(const std::vector<int64_t>& starts, int P, int size, std::vector<
     segs[p].tile_begin = (int32_t)tiles;
     segs[p].tile_count = (int32_t)t;
     segs[p].hist_begin = (int32_t)rows;
-    segs[p].pad = 0;
+    segs[p].tile = 0;
     tiles += t;
     rows += t > 1 ? t : 0;
   }
@@ -286,7 +289,7 @@ struct epm_index {
   char* ws = nullptr;
   Layout L;
   bool have_qperm = false;
-  uint32_t* qperm = nullptr;
+  const uint32_t* qperm = nullptr;
   hipStream_t last_stream = nullptr;  // stream of the last query call
   const int64_t* last_offsets = nullptr;
   bool have_stats = false;
@@ -346,6 +349,7 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   idx->tiles = tiles_of(pairs, num_pairs);
   make_segs(idx->kstart, num_pairs, idx->tiles.rsize, idx->rsegs);
   make_segs(idx->qstart, num_pairs, idx->tiles.qsize, idx->qsegs);
+  for (int p = 0; p < num_pairs; ++p) idx->qsegs[p].tile = tile_queries(pairs[p].m, pairs[p].n);
   idx->stile_begin.resize(num_pairs + 1);
   idx->stile_begin[0] = 0;
   for (int p = 0; p < num_pairs; ++p)
@@ -449,6 +453,10 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.qkey = idx->at<uint32_t>(L.qkey);
   A.qflag = idx->at<uint32_t>(L.qflag);
   A.qperm = nullptr;
+  A.qperm_out = nullptr;
+  A.qsegs = idx->at<SortSeg>(L.qsegs);
+  A.group_starts = nullptr;
+  A.groups = nullptr;
   A.class_begin = idx->at<int64_t>(L.class_begin);
   A.skey = idx->at<uint32_t>(L.rk0);
   A.rC = idx->at<uint32_t>(L.rC);
@@ -527,14 +535,20 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   c.v1 = idx->at<uint32_t>(L.qv1);
   c.hist0 = idx->at<uint32_t>(L.qhist0);
   c.hist1 = idx->at<uint32_t>(L.qhist1);
-  // one pass leaves the keys' buffer free afterwards, two passes the other
-  idx->qperm = two ? c.k0 : c.v1;
+  // the sort's order of the queries, and the window pass's: one pass leaves
+  // both key buffers free afterwards, two passes the second and the indices
+  uint32_t* sorted = two ? c.k0 : c.v1;
+  uint32_t* groups = idx->at<uint32_t>(L.groups);
+  A.qperm_out = two ? c.v1 : c.k1;
+  idx->qperm = A.qperm_out;
   idx->have_qperm = true;
   EPM_HIP(launch_query_keys(A.pairs, c, two, A.kp1, idx->at<uint32_t>(L.qkey),
                             idx->at<uint32_t>(L.qflag), A.qline, A.stats,
                             idx->at<uint32_t>(L.sched), A.match_stats, stream));
-  EPM_HIP(sort_queries(c, two, idx->qperm, stream));
-  A.qperm = idx->qperm;
+  EPM_HIP(sort_queries(A.pairs, c, two, sorted, groups, stream));
+  A.qperm = sorted;
+  A.group_starts = c.hist1;
+  A.groups = two ? nullptr : groups;
   // 8 bytes per 256 queries in 4 bytes per query
   A.row_sums = reinterpret_cast<uint64_t*>(two ? c.k1 : c.k0);
   if (records_ready) EPM_HIP(hipStreamWaitEvent(stream, records_ready, 0));
@@ -548,6 +562,7 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   uint32_t* sched = idx->at<uint32_t>(L.sched);  // cleared by the key pass
   A.tile_cost = lpt || xcd_lpt ? idx->at<uint32_t>(L.tile_cost) : nullptr;
   EPM_HIP(launch_tile_windows(A, stream));
+  A.qperm = idx->qperm;
   if (lpt) {
     EPM_HIP(launch_lpt_order(A.tile_cost, A.num_tiles, sched, idx->at<uint32_t>(L.order), stream));
     idx->have_order = true;

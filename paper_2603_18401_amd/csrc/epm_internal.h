@@ -130,6 +130,13 @@ __host__ __device__ inline uint32_t position_code(const PairDev& pd, uint32_t ke
   return y >= pd.arc_len ? (1u << kCentreBits) - 1u : (uint32_t)(((uint64_t)y * pd.arc_mul) >> 32);
 }
 
+// Whether the digit of the one-pass query sort can crowd: with an arc, its two
+// ends hold the keys beyond it, of lines that miss image 2, and their order is
+// of no account.
+__host__ __device__ inline bool digit_counts(const PairDev& pd, uint32_t digit) {
+  return pd.arc_len == 0xFFFFFFFFu || (digit != 0u && digit != (1u << kRadixBits) - 1u);
+}
+
 struct SortTile {
   int64_t begin;  // global element index
   int32_t count;
@@ -142,7 +149,8 @@ struct SortSeg {
   int64_t begin;
   int64_t count;
   int32_t tile_begin, tile_count;
-  int32_t hist_begin, pad;
+  int32_t hist_begin;
+  int32_t tile;  // the queries' segments: queries per stabbing tile
 };
 
 constexpr int kSortThreads = 1024;
@@ -165,6 +173,14 @@ constexpr int kRowSortMax = 2048;
 constexpr int kTileQ = 64;
 constexpr int kStage = 128;
 constexpr int kChunk = 512;
+
+// Queries with equal upper kRadixBits bits of their codes form a group of the
+// one-pass query sort.  What the window pass does with a segment's groups:
+// sort around the boundaries of neighbouring tiles, where groups are small;
+// sort its workgroups' queries, where tiles hold fewer than kTileQ of them;
+// and bring groups of more than two tiles into the order of their keys.
+constexpr uint32_t kGroupsSmall = 0, kGroupsLocal = 1, kGroupsLarge = 2;
+static_assert(kCentreBits >= kRadixBits, "a group's queries differ in the bits below");
 
 // Per-tile record windows found by the window pass: up to two ranges of
 // sorted positions per width class (the second one when the window wraps

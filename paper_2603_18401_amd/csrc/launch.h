@@ -70,8 +70,12 @@ hipError_t launch_query_keys(const PairDev* pairs, const SortCall& c, bool two_p
 // afterwards.
 hipError_t sort_records(const SortCall& c, const RecordSort& r, hipStream_t s);
 // perm: the queries of every pair by the upper kRadixBits bits of their
-// position codes, or by all of them (two_passes; perm may then be c.k0).
-hipError_t sort_queries(const SortCall& c, bool two_passes, uint32_t* perm, hipStream_t s);
+// position codes, or by all of them (two_passes; perm may then be c.k0).  One
+// pass also sets groups[segment] to kGroups..; with kGroupsLarge, and in
+// segments of several sort tiles, their first two rows of c.hist1 hold the
+// places where the groups start.
+hipError_t sort_queries(const PairDev* pairs, const SortCall& c, bool two_passes, uint32_t* perm,
+                        uint32_t* groups, hipStream_t s);
 
 hipError_t launch_class_bounds(const int64_t* kstart, int num_pairs, const uint32_t* skey,
                                int64_t* class_begin, hipStream_t s);
@@ -84,7 +88,13 @@ struct StabArgs {
   const float* kp1;
   const uint32_t* qkey;
   const uint32_t* qflag;
-  uint32_t* qperm;  // the queries by angle; the window pass orders it within its workgroups
+  const uint32_t* qperm;  // the queries by angle (the sort's order for the window pass)
+  // the window pass: its order of the queries, and of the sort the segments,
+  // group starts and kGroups.. (groups NULL: all kGroupsSmall)
+  uint32_t* qperm_out;
+  const SortSeg* qsegs;
+  const uint32_t* group_starts;
+  const uint32_t* groups;
   const int64_t* class_begin;
   const uint32_t* skey;
   const uint32_t* rC;

@@ -278,18 +278,158 @@ static_assert(kTileQ == 64, "pair indexing uses a 6-bit query field");
 // queries (class_ranges), one wavefront per tile, so every tile's searches are
 // in flight at once.
 constexpr int kWindowTiles = 4;  // tiles (one wavefront each) per workgroup
-__global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs A) {
-  const int lane = lane_id();
+constexpr int kWindowThreads = kWave * kWindowTiles;
+constexpr int kWindowQ = kTileQ * kWindowTiles;
+static_assert(kWindowQ == kWindowThreads, "a thread per query slot");
+
+// A large group of the query sort in the order of its keys, by every workgroup
+// that holds a part of it for itself: the group's keys are counted in
+// kRefineBins bins over their span, and the queries of the bins that this
+// workgroup's places fall into are collected and ranked.  A bin of more than
+// kRefineBin queries (nearly equal keys) leaves the group as the sort wrote it,
+// in all of its workgroups.  What bounds it: three walks over the group by a
+// workgroup, a few loads per thread for groups of a thousand.  (Without it
+// 60000 queries and 240000 records in 8 of the 2048 groups took 1665 us to
+// count instead of 270.)
+constexpr int kRefineBins = 1024, kRefineBin = 384;
+constexpr int kRefineMax = kWindowQ + 2 * kRefineBin;
+struct Refine {
+  uint64_t v[kRefineMax];  // key and place in the group, by bin
+  uint32_t start[kRefineBins + 1], cursor[kRefineBins];
+  uint32_t wsum[kWindowTiles], wmax[kWindowTiles], lo, hi, base, end;
+};
+
+// Group: places [gs, ge) of the segment that starts at query seg; the workgroup
+// holds places [pa, pb), tq per tile from its tile w0 on.  Called by the whole
+// workgroup.
+__device__ void refine_group(const StabArgs& A, int64_t seg, uint32_t gs, uint32_t ge, uint32_t pa,
+                             uint32_t pb, int w0, uint32_t tq, uint32_t* s_i, uint32_t* s_k,
+                             Refine& S) {
+  static_assert(kRefineBins == 4 * kWindowThreads, "four bins per thread");
+  const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+  const uint32_t n = ge - gs;  // at most 2^17 (one-pass segments)
+  const uint32_t* perm = A.qperm + seg + gs;
+  #pragma unroll
+  for (int u = 0; u < 4; ++u) S.start[4 * tid + u] = S.cursor[4 * tid + u] = 0u;
+  if (tid == 0) {
+    S.lo = 0xFFFFFFFFu;
+    S.hi = 0u;
+  }
+  __syncthreads();
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  #pragma unroll 4
+  for (uint32_t e = tid; e < n; e += kWindowThreads) {
+    const uint32_t k = A.qkey[perm[e]];
+    lo = min(lo, k);
+    hi = max(hi, k);
+  }
+  lo = wave_min_u32(lo);
+  hi = wave_max_u32(hi);
+  if (lane == 0) {
+    atomicMin(&S.lo, lo);
+    atomicMax(&S.hi, hi);
+  }
+  __syncthreads();
+  lo = S.lo;
+  const uint32_t span = S.hi - lo;
+  const int shift = span < (uint32_t)kRefineBins ? 0 : 22 - (int)__builtin_clz(span);
+  static_assert(kRefineBins == 1 << 10, "span >> shift has ten bits");
+  #pragma unroll 4
+  for (uint32_t e = tid; e < n; e += kWindowThreads)
+    atomicAdd(&S.start[(A.qkey[perm[e]] - lo) >> shift], 1u);
+  __syncthreads();
+  uint32_t c[4];
+  #pragma unroll
+  for (int u = 0; u < 4; ++u) c[u] = S.start[4 * tid + u];
+  const uint32_t own = c[0] + c[1] + c[2] + c[3];
+  const uint32_t most = wave_max_u32(max(max(c[0], c[1]), max(c[2], c[3])));
+  const uint32_t incl = wave_scan_u32(own);
+  if (lane == kWave - 1) S.wsum[wave] = incl;
+  if (lane == 0) S.wmax[wave] = most;
+  __syncthreads();
+  uint32_t at = incl - own, biggest = 0u;
+  #pragma unroll
+  for (int w = 0; w < kWindowTiles; ++w) {
+    at += w < wave ? S.wsum[w] : 0u;
+    biggest = max(biggest, S.wmax[w]);
+  }
+  if (biggest > (uint32_t)kRefineBin) {  // uniform
+    __syncthreads();
+    return;
+  }
+  // this workgroup's ranks in the group, and the bins that hold them
+  const uint32_t r0 = max(pa, gs) - gs, r1 = min(pb, ge) - gs;
+  #pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    S.start[4 * tid + u] = at;
+    if (at <= r0 && r0 < at + c[u]) S.base = at;
+    if (at < r1 && r1 <= at + c[u]) S.end = at + c[u];
+    at += c[u];
+  }
+  if (tid == kWindowThreads - 1) S.start[kRefineBins] = at;
+  __syncthreads();
+  const uint32_t base = S.base, end = S.end;
+  #pragma unroll 4
+  for (uint32_t e = tid; e < n; e += kWindowThreads) {
+    const uint32_t k = A.qkey[perm[e]], bin = (k - lo) >> shift, b = S.start[bin];
+    if (b >= base && b < end) S.v[b - base + atomicAdd(&S.cursor[bin], 1u)] = ((uint64_t)k << 17) | e;
+  }
+  __syncthreads();
+  for (uint32_t p = tid; p < end - base; p += kWindowThreads) {
+    const uint64_t v = S.v[p];
+    const uint32_t k = (uint32_t)(v >> 17), bin = (k - lo) >> shift;
+    const uint32_t b = S.start[bin] - base, e = S.start[bin + 1] - base;
+    uint32_t r = base + b;
+    for (uint32_t u = b; u < e; ++u) r += S.v[u] < v ? 1u : 0u;
+    if (r >= r0 && r < r1) {
+      const uint32_t x = gs + r - pa;
+      const uint32_t slot = (uint32_t)w0 * kTileQ + x / tq * kTileQ + x % tq;
+      s_i[slot] = perm[v & 0x1FFFFull];
+      s_k[slot] = k;
+    }
+  }
+  __syncthreads();
+}
+
+// Bitonic sort of a value per thread of the workgroup, ascending (a
+// wavefront's in registers, others' through buf, in turn in its two halves).
+__device__ __forceinline__ uint64_t window_sort(uint64_t v, uint64_t* buf) {
+  const int tid = threadIdx.x;
+  // blocks of k are brought into ascending and descending order in turn
+  bool down = (tid & kWave) != 0;
+  v = wave_sort64(down ? ~v : v);
+  v = down ? ~v : v;
+  uint64_t* at = buf;
+  #pragma unroll 1
+  for (int k = 2 * kWave; k <= kWindowThreads; k *= 2) {
+    down = (tid & k) != 0;
+    v = down ? ~v : v;
+    #pragma unroll 1
+    for (int j = k / 2; j >= kWave; j /= 2) {
+      at[tid] = v;
+      __syncthreads();
+      const uint64_t o = at[tid ^ j];
+      v = (o < v) == ((tid & j) == 0) ? o : v;
+      at = at == buf ? buf + kWindowThreads : buf;
+    }
+    sort_step<kWave, kWave / 2>(v, lane_id());
+    v = down ? ~v : v;
+  }
+  return v;
+}
+
+__global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
+  const int lane = lane_id(), wave = wave_id();
   // each XCD takes one run of consecutive tiles: the queries of a pair are
   // gathered in their sorted order, and a line of them holds several tiles'
   // (12.5 us with the workgroups dealt in turn, 10.8 so, at 1878 tiles)
   const int run = (int)gridDim.x / kNumXcd;
   const int t =
-      (((int)blockIdx.x % kNumXcd) * run + (int)blockIdx.x / kNumXcd) * kWindowTiles + wave_id();
+      (((int)blockIdx.x % kNumXcd) * run + (int)blockIdx.x / kNumXcd) * kWindowTiles + wave;
   // the look-back words of the pass over the rows (one per 256 queries, a
   // tile holds at most 64) start from zero
-  for (int64_t k = (int64_t)blockIdx.x * (kWave * kWindowTiles) + threadIdx.x;
-       k < (A.n1 + kFinishRows - 1) / kFinishRows; k += (int64_t)gridDim.x * (kWave * kWindowTiles))
+  for (int64_t k = (int64_t)blockIdx.x * kWindowThreads + threadIdx.x;
+       k < (A.n1 + kFinishRows - 1) / kFinishRows; k += (int64_t)gridDim.x * kWindowThreads)
     A.row_sums[k] = 0ull;
   // The sort grouped the queries by the upper bits of their codes.  Sorting
   // the 64 queries around each boundary between two of the workgroup's tiles
@@ -297,8 +437,14 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
   // as long as a group holds no more than half a tile.  (Without it the
   // windows are longer: the tile pass 90.6 instead of 86.1 us at six pairs of
   // 20000 keypoints, 149 instead of 139 at one of 60000; this costs 2.)
-  __shared__ uint32_t s_i[kWindowTiles * kTileQ];
-  __shared__ uint32_t s_k[kWindowTiles * kTileQ];
+  // Where queries crowd into groups of more than two tiles, those that leave
+  // the workgroup are put in order across their workgroups, and the
+  // workgroup's queries are sorted by their whole keys; the latter also where
+  // its tiles hold few of them.
+  __shared__ uint32_t s_i[kWindowQ], s_k[kWindowQ];
+  __shared__ int32_t s_pair[kWindowTiles], s_count[kWindowTiles];
+  __shared__ uint32_t s_place[kWindowTiles];  // the tile's first place in its segment
+  __shared__ Refine refine;
   const bool live = t < A.num_tiles;
   StabTile T;
   T.begin = 0;
@@ -306,40 +452,96 @@ __global__ __launch_bounds__(kWave * kWindowTiles) void k_tile_windows(StabArgs 
   T.pair = -1;
   if (live) T = A.tiles[t];
   const int slot = (int)threadIdx.x;
-  uint32_t qi = 0u;
-  s_k[slot] = 0xFFFFFFFFu;  // behind every query, by its place
+  uint32_t qi = 0u, key = 0xFFFFFFFFu;  // behind every query, by its place
   if (lane < T.count) {
     qi = A.qperm[T.begin + lane];
-    s_i[slot] = qi;
-    s_k[slot] = A.qkey[qi];
+    key = A.qkey[qi];
   }
-  const bool joined = wave_id() + 1 < kWindowTiles && t + 1 < A.num_tiles && T.count == kTileQ &&
-                      A.tiles[t + 1].pair == T.pair;
-  __syncthreads();
-  uint32_t moved = 0u;
-  if (joined) {
-    uint64_t v = ((uint64_t)s_k[slot + kTileQ / 2] << 6) | (uint64_t)lane;
-    v = wave_sort64(v);
-    moved = s_i[slot - lane + kTileQ / 2 + (int)(v & 63ull)];
+  const bool sorts = live && A.groups && A.groups[T.pair] != kGroupsSmall;
+  s_i[slot] = qi;
+  s_k[slot] = key;
+  if (!__syncthreads_or(sorts)) {
+    const bool joined = wave + 1 < kWindowTiles && t + 1 < A.num_tiles && T.count == kTileQ &&
+                        A.tiles[t + 1].pair == T.pair;
+    uint32_t moved_i = 0u, moved_k = 0u;
+    if (joined) {
+      const uint64_t v =
+          wave_sort64(((uint64_t)s_k[slot + kTileQ / 2] << 6) | (uint64_t)lane);
+      moved_i = s_i[slot - lane + kTileQ / 2 + (int)(v & 63ull)];
+      moved_k = (uint32_t)(v >> 6);
+    }
+    __syncthreads();
+    if (joined) {
+      s_i[slot + kTileQ / 2] = moved_i;
+      s_k[slot + kTileQ / 2] = moved_k;
+    }
+    __syncthreads();
+    qi = s_i[slot];
+    key = s_k[slot];
+  } else {
+    if (lane == 0) {
+      s_pair[wave] = T.pair;
+      s_count[wave] = T.count;
+      s_place[wave] = live ? (uint32_t)(T.begin - A.qstart[T.pair]) : 0u;
+    }
+    __syncthreads();
+    int first = 0;  // of this wavefront's run of tiles of one pair
+    for (int w0 = 0; w0 < kWindowTiles;) {  // uniform
+      const int p = s_pair[w0];
+      int w1 = w0 + 1;
+      while (w1 < kWindowTiles && s_pair[w1] == p) ++w1;
+      if (w0 <= wave) first = w0;
+      if (p >= 0 && A.groups[p] == kGroupsLarge) {
+        const SortSeg sg = A.qsegs[p];
+        const uint32_t pa = s_place[w0], pb = s_place[w1 - 1] + (uint32_t)s_count[w1 - 1];
+        const uint32_t tq = (uint32_t)s_count[w0];
+        if (sg.tile_count < 2) {  // a segment of one sort tile: all of it as one group
+          refine_group(A, sg.begin, 0u, (uint32_t)sg.count, pa, pb, w0, tq, s_i, s_k, refine);
+        } else {
+          const uint32_t* starts = A.group_starts + (int64_t)sg.hist_begin * kHistWords;
+          constexpr int kLow = kCentreBits - kRadixBits;
+          const uint32_t d0 = position_code(A.pairs[p], s_k[w0 * kTileQ]) >> kLow;
+          const uint32_t d1 =
+              position_code(A.pairs[p], s_k[(w1 - 1) * kTileQ + s_count[w1 - 1] - 1]) >> kLow;
+          for (uint32_t d = d0;; d = d1) {
+            const uint32_t gs = starts[d] - (uint32_t)sg.begin;
+            const uint32_t ge = d + 1 < (uint32_t)kRadix ? starts[d + 1] - (uint32_t)sg.begin
+                                                         : (uint32_t)sg.count;
+            if (ge - gs > 2u * (uint32_t)sg.tile && digit_counts(A.pairs[p], d))
+              refine_group(A, sg.begin, gs, ge, pa, pb, w0, tq, s_i, s_k, refine);
+            if (d == d1) break;
+          }
+        }
+      }
+      w0 = w1;
+    }
+    // all queries of every run by (key, slot); empty slots follow them
+    const bool full = lane < T.count;
+    const uint64_t v = window_sort(((uint64_t)first << 41) | ((uint64_t)(full ? 0 : 1) << 40) |
+                                       ((uint64_t)s_k[slot] << 8) | (uint64_t)slot,
+                                   refine.v);
+    __syncthreads();
+    refine.v[slot] = v;
+    __syncthreads();
+    if (full) {  // the run's k-th query goes to its k-th filled slot
+      const uint64_t mine = refine.v[first * kTileQ + (wave - first) * s_count[first] + lane];
+      qi = s_i[(int)(mine & 255ull)];
+      key = (uint32_t)(mine >> 8);
+    }
   }
-  __syncthreads();
-  if (joined) s_i[slot + kTileQ / 2] = moved;
-  __syncthreads();
   if (!live) return;  // whole wavefronts
   bool normal = false, brute = false;
-  uint32_t key = 0;
   TileQuery tq;
   tq.a = tq.b = tq.c = 0.0;
   tq.i = 0;
   tq.flag = kQueryEmpty;
   tq.key = tq.pad = 0;
   if (lane < T.count) {
-    const int64_t i = s_i[slot];
-    if ((uint32_t)i != qi) A.qperm[T.begin + lane] = (uint32_t)i;
+    const int64_t i = qi;
+    A.qperm_out[T.begin + lane] = qi;
     const uint32_t flag = A.qflag[i];
     normal = flag == kQueryNormal;
     brute = flag == kQueryBrute;
-    key = A.qkey[i];
     tq.i = (uint32_t)i;
     tq.flag = flag;
     tq.key = key;
@@ -2151,7 +2353,7 @@ hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s) {
   if (a.num_tiles == 0) return hipSuccess;
   const int blocks = (a.num_tiles + kWindowTiles - 1) / kWindowTiles;
   hipLaunchKernelGGL(k_tile_windows, dim3((blocks + kNumXcd - 1) / kNumXcd * kNumXcd),
-                     dim3(kWave * kWindowTiles), 0, s, a);
+                     dim3(kWindowThreads), 0, s, a);
   return hipGetLastError();
 }
 
