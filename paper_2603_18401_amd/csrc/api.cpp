@@ -545,7 +545,7 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   EPM_HIP(launch_query_keys(A.pairs, c, two, A.kp1, idx->at<uint32_t>(L.qkey),
                             idx->at<uint32_t>(L.qflag), A.qline, A.stats,
                             idx->at<uint32_t>(L.sched), A.match_stats, stream));
-  EPM_HIP(sort_queries(A.pairs, c, two, sorted, groups, stream));
+  EPM_HIP(sort_queries(c, two, sorted, groups, stream));
   A.qperm = sorted;
   A.group_starts = c.hist1;
   A.groups = two ? nullptr : groups;

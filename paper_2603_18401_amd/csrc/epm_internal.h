@@ -22,10 +22,14 @@ constexpr uint32_t kFullHalf = 0x80000000u;
 // Keys of a pair are angles minus the pair's cut, the middle of the gap that
 // the lines through the epipole leave beside image 2 (a far epipole sees the
 // image under a small angle); differences of keys do not notice.  The
-// position code of a key places it in the arc between (arc_off, arc_len) with
-// kCentreBits bits; keys outside the arc take the code of its nearer end.
-// The code never decreases with the key, so windows of keys are windows of
-// codes, whatever the arc is.
+// position code of a key has kCentreBits bits: the arc of the lines that meet
+// image 2 takes all of them but kSideCodes on either side, for the rest of the
+// circle, since keypoints may lie outside their image.  Most of those resolve
+// what borders on the arc, up to twice its length away.  (With the keys beyond
+// the arc all at its ends' codes, a pair of 60000 whose keypoints reach twice
+// as far as the stated image took 3450 us instead of 160.)  The code never
+// decreases with the key, so windows of keys are windows of codes, whatever the
+// arc is.
 //
 // Records are sorted by (width class, position code of the centre).  Class c
 // holds half-widths H with 2^(c-1) <= H < 2^c, so a query at key P only has
@@ -34,6 +38,8 @@ constexpr uint32_t kFullHalf = 0x80000000u;
 constexpr int kClassBits = 5;
 constexpr int kNumClasses = 32;
 constexpr int kCentreBits = 17;
+constexpr uint32_t kSideCodes = 1u << (kCentreBits - 4);
+constexpr uint32_t kNearCodes = kSideCodes / 8 * 7;
 constexpr int kRadixBits = 11;  // bits per pass of the sort
 constexpr int kSortBits = kClassBits + kCentreBits;  // two passes
 constexpr int kWideClass = 31;
@@ -53,6 +59,13 @@ constexpr double kEpsRelSlack = 1.0 / (1 << 30);
 constexpr double kEpsAbsSlackPx = 1e-7;
 
 // ------------------------------------------------------------ pair records
+// Position codes of a pair's keys: codes per key, times 2^32, of the arc (for
+// keys shifted up by arc_shift), near it and beyond; keys minus `cut` have the
+// arc in their middle (arc_len 0: no arc).
+struct KeyArc {
+  uint32_t arc_mul, arc_shift, near_mul, far_mul, cut, arc_len;
+};
+
 struct PairDev {
   double F[9];          // row-major, pixel space, exactly as given
   double u[3], v[3], e[3];  // orthonormal pencil basis in normalised line space
@@ -60,8 +73,7 @@ struct PairDev {
   double G11, G12, G22; // Gram matrix of (u_12, v_12)
   double e12;           // |e_12|
   double kappa;         // miss bound absorbed by the record intervals
-  uint64_t arc_mul;     // position code of a key: (key - arc_off) * arc_mul >> 32
-  uint32_t cut, arc_off, arc_len, arc_pad;
+  KeyArc arc;
   int64_t q_begin, m, k_begin, n;
 };
 
@@ -72,14 +84,21 @@ __host__ __device__ inline uint32_t angle_key(double phi) {
   return (uint32_t)(uint64_t)(int64_t)nearbyint(phi * kKeyPerRad);
 }
 
+// Keys below an arc of len keys in the middle of the circle (one more may lie
+// above it), and how far the finer codes beside it reach.
+__host__ __device__ inline uint32_t arc_side(uint32_t len) { return (0u - len) >> 1; }
+__host__ __device__ inline uint32_t arc_near(uint32_t len) {
+  const uint32_t side = arc_side(len);
+  return len < side / 4u ? 2u * len : side / 2u;
+}
+
 // The pair's arc of keys: those of the pencil lines that meet image 2, a
 // little wider on both sides; the whole circle when the epipole lies in the
 // image or close to it, or the pair has no pencil.  (Only the resolution of
 // the position codes depends on it.)
 __host__ __device__ inline void set_key_arc(PairDev& pd) {
-  pd.cut = pd.arc_off = pd.arc_pad = 0u;
-  pd.arc_len = 0xFFFFFFFFu;
-  pd.arc_mul = 1ull << kCentreBits;
+  KeyArc& arc = pd.arc;
+  arc.cut = arc.arc_len = arc.arc_mul = arc.arc_shift = arc.near_mul = arc.far_mul = 0u;
   if (pd.kappa < 0.0) return;
   // d = e_w p - (e_x, e_y) is the direction from the epipole to the point p
   // (normalised coordinates, centre 0; up to a common sign).  While the four
@@ -117,24 +136,33 @@ __host__ __device__ inline void set_key_arc(PairDev& pd) {
   const uint64_t wide = (uint64_t)len + 2u * margin;
   if (wide >= 0xF0000000ull) return;
   lo -= (uint32_t)margin;
-  pd.arc_len = (uint32_t)wide;
-  pd.arc_off = (uint32_t)((0x100000000ull - wide) / 2u);
-  pd.cut = lo - pd.arc_off;
-  pd.arc_mul = ((1ull << (32 + kCentreBits)) - 1ull) / wide;
+  arc.arc_len = (uint32_t)wide;
+  const uint32_t off = arc_side(arc.arc_len), near = arc_near(arc.arc_len);
+  arc.cut = lo - off;
+  while (!((arc.arc_len << arc.arc_shift) & 0x80000000u)) ++arc.arc_shift;
+  // (a key beyond the arc is at most `off` keys away, which is at least 2^27;
+  // all rounded down, whatever the divisions' last bits)
+  arc.arc_mul = (uint32_t)(((1u << kCentreBits) - 2u * kSideCodes) * 0x1p32 /
+                          (arc.arc_len << arc.arc_shift)) - 1u;
+  arc.near_mul = (uint32_t)(kNearCodes * 0x1p32 / near) - 1u;
+  arc.far_mul = (uint32_t)((kSideCodes - kNearCodes) * 0x1p32 / (off - near + 2u)) - 1u;
 }
 
 // Position code of a key (an angle minus the pair's cut); never decreases
 // with the key.
-__host__ __device__ inline uint32_t position_code(const PairDev& pd, uint32_t key) {
-  const uint32_t y = key < pd.arc_off ? 0u : key - pd.arc_off;
-  return y >= pd.arc_len ? (1u << kCentreBits) - 1u : (uint32_t)(((uint64_t)y * pd.arc_mul) >> 32);
-}
-
-// Whether the digit of the one-pass query sort can crowd: with an arc, its two
-// ends hold the keys beyond it, of lines that miss image 2, and their order is
-// of no account.
-__host__ __device__ inline bool digit_counts(const PairDev& pd, uint32_t digit) {
-  return pd.arc_len == 0xFFFFFFFFu || (digit != 0u && digit != (1u << kRadixBits) - 1u);
+__host__ __device__ inline uint32_t position_code(const KeyArc& arc, uint32_t key) {
+  const uint32_t off = arc_side(arc.arc_len), near = arc_near(arc.arc_len);
+  const uint32_t y = key - off;  // (past the arc's end below the arc)
+  const bool below = key < off, inside = !below && y < arc.arc_len;
+  const uint32_t d = below ? off - 1u - key : y - arc.arc_len;  // keys to the arc
+  const bool far = d >= near;
+  const uint32_t mul = inside ? arc.arc_mul : far ? arc.far_mul : arc.near_mul;
+  const uint32_t x = inside ? y << arc.arc_shift : far ? d - near : d;
+  const uint32_t c = (uint32_t)(((uint64_t)x * mul) >> 32), s = far ? kNearCodes + c : c;
+  const uint32_t code = inside  ? kSideCodes + c
+                        : below ? kSideCodes - 1u - s
+                                : (1u << kCentreBits) - kSideCodes + s;
+  return arc.arc_len == 0u ? key >> (32 - kCentreBits) : code;
 }
 
 struct SortTile {

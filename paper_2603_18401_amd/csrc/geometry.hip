@@ -75,7 +75,7 @@ __device__ void circle_interval(const PairDev& pd, float xf, float yf, float ef,
     H = kFullHalf;
     return;
   }
-  C = angle_key(psi) - pd.cut;
+  C = angle_key(psi) - pd.arc.cut;
   H = (uint32_t)hk;
 }
 
@@ -199,6 +199,7 @@ __global__ __launch_bounds__(kSortThreads) void k_intervals(
   __syncthreads();
   const SortTile t = tiles[blockIdx.x];
   const PairDev& pd = pairs[t.seg];
+  const KeyArc arc = pd.arc;  // (loaded before the geometry)
   for (int k = threadIdx.x; k < t.count; k += kSortThreads) {
     const int64_t r = t.begin + k;
     const float xf = kp2[2 * r], yf = kp2[2 * r + 1];
@@ -209,7 +210,7 @@ __global__ __launch_bounds__(kSortThreads) void k_intervals(
     if (ef > 0.0f && isfinite(ef) && isfinite(xf) && isfinite(yf))
       circle_interval(pd, xf, yf, ef, C, H);
     const uint32_t cls = (uint32_t)width_class(H);
-    const uint32_t key = (cls << kCentreBits) | position_code(pd, C);
+    const uint32_t key = (cls << kCentreBits) | position_code(arc, C);
     sort_key[r] = key;
     recC[r] = C;
     recH[r] = H;
@@ -238,6 +239,7 @@ __global__ __launch_bounds__(kSortThreads) void k_query_keys(
   __syncthreads();
   const SortTile t = tiles[blockIdx.x];
   const PairDev& pd = pairs[t.seg];
+  const KeyArc arc = pd.arc;  // (loaded before the geometry)
   for (int kk = threadIdx.x; kk < t.count; kk += kSortThreads) {
     const int64_t i = t.begin + kk;
     double a, b, c;
@@ -259,12 +261,12 @@ __global__ __launch_bounds__(kSortThreads) void k_query_keys(
       if (pd.kappa < 0.0 || !(fabs(nu) <= pd.kappa * nrm)) {
         flag = kQueryBrute;  // the line misses the epipole by more than absorbed
       } else {
-        key = angle_key(atan2(mu, lam)) - pd.cut;
+        key = angle_key(atan2(mu, lam)) - arc.cut;
       }
     }
     qkey[i] = key;
     qflag[i] = flag;
-    const uint32_t sk = position_code(pd, key) << kClassBits;
+    const uint32_t sk = position_code(arc, key) << kClassBits;
     sort_key[i] = sk;
     // the line and its norm for the tile passes (the denominator of Eq. 3)
     qline[i] = flag == kQueryEmpty ? make_double4(0.0, 0.0, 0.0, 0.0)

@@ -74,8 +74,8 @@ hipError_t sort_records(const SortCall& c, const RecordSort& r, hipStream_t s);
 // pass also sets groups[segment] to kGroups..; with kGroupsLarge, and in
 // segments of several sort tiles, their first two rows of c.hist1 hold the
 // places where the groups start.
-hipError_t sort_queries(const PairDev* pairs, const SortCall& c, bool two_passes, uint32_t* perm,
-                        uint32_t* groups, hipStream_t s);
+hipError_t sort_queries(const SortCall& c, bool two_passes, uint32_t* perm, uint32_t* groups,
+                        hipStream_t s);
 
 hipError_t launch_class_bounds(const int64_t* kstart, int num_pairs, const uint32_t* skey,
                                int64_t* class_begin, hipStream_t s);

@@ -135,8 +135,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
     const uint32_t* __restrict__ kin, const uint32_t* __restrict__ vin,
     uint32_t* __restrict__ kout, uint32_t* __restrict__ vout, const SortTile* __restrict__ tiles,
     const SortSeg* __restrict__ segs, int num_segs, int shift, const uint32_t* __restrict__ hist,
-    RecordSort R, const PairDev* __restrict__ pairs, uint32_t* __restrict__ group_starts,
-    uint32_t* __restrict__ groups) {
+    RecordSort R, uint32_t* __restrict__ group_starts, uint32_t* __restrict__ groups) {
   constexpr bool REC = OUT == kOutRecords;
   __shared__ uint32_t run[kRadix];  // the digits' next places
   __shared__ uint32_t wsum[kSortWaves];
@@ -193,9 +192,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
     // (the first tile's workgroup tells the window pass about large groups)
     if (groups && mine == 0) {
       const uint32_t most = 2u * (uint32_t)sg.tile;
-      const PairDev& pd = pairs[t.seg];
-      const int large = __syncthreads_or((total[0] > most && digit_counts(pd, 2 * tid)) ||
-                                         (total[1] > most && digit_counts(pd, 2 * tid + 1)));
+      const int large = __syncthreads_or(total[0] > most || total[1] > most);
       if (tid == 0)
         groups[t.seg] = large ? kGroupsLarge : sg.tile < kTileQ ? kGroupsLocal : kGroupsSmall;
       if (large && sg.tile_count >= 2) {
@@ -300,8 +297,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
 void first_pass(const SortCall& c, hipStream_t s) {
   const dim3 g((unsigned)c.num_tiles), b(kSortThreads);
   hipLaunchKernelGGL((k_sort_pass<kOutPairs>), g, b, 0, s, c.k0, (const uint32_t*)nullptr, c.k1,
-                     c.v1, c.tiles, c.segs, c.num_segs, 0, c.hist0, RecordSort{}, (const PairDev*)nullptr,
-                     (uint32_t*)nullptr, (uint32_t*)nullptr);
+                     c.v1, c.tiles, c.segs, c.num_segs, 0, c.hist0, RecordSort{}, (uint32_t*)nullptr,
+                     (uint32_t*)nullptr);
   if (c.rows > 0)
     hipLaunchKernelGGL(k_sort_hist, g, b, 0, s, c.k1, c.tiles, c.segs, kRadixBits, c.hist1);
 }
@@ -332,19 +329,18 @@ hipError_t sort_records(const SortCall& c, const RecordSort& r, hipStream_t s) {
   first_pass(c, s);
   hipLaunchKernelGGL((k_sort_pass<kOutRecords>), dim3((unsigned)c.num_tiles), dim3(kSortThreads),
                      0, s, c.k1, c.v1, c.k0, (uint32_t*)nullptr, c.tiles, c.segs, c.num_segs,
-                     kRadixBits, c.hist1, r, (const PairDev*)nullptr, (uint32_t*)nullptr,
-                     (uint32_t*)nullptr);
+                     kRadixBits, c.hist1, r, (uint32_t*)nullptr, (uint32_t*)nullptr);
   return hipGetLastError();
 }
 
-hipError_t sort_queries(const PairDev* pairs, const SortCall& c, bool two_passes, uint32_t* perm,
-                        uint32_t* groups, hipStream_t s) {
+hipError_t sort_queries(const SortCall& c, bool two_passes, uint32_t* perm, uint32_t* groups,
+                        hipStream_t s) {
   if (c.num_tiles == 0) return hipSuccess;
   if (two_passes) first_pass(c, s);
   hipLaunchKernelGGL((k_sort_pass<kOutIndex>), dim3((unsigned)c.num_tiles), dim3(kSortThreads), 0,
                      s, two_passes ? c.k1 : c.k0, two_passes ? c.v1 : (uint32_t*)nullptr,
                      (uint32_t*)nullptr, perm, c.tiles, c.segs, c.num_segs, kRadixBits,
-                     two_passes ? c.hist1 : c.hist0, RecordSort{}, pairs,
+                     two_passes ? c.hist1 : c.hist0, RecordSort{},
                      two_passes ? nullptr : c.hist1, two_passes ? nullptr : groups);
   return hipGetLastError();
 }

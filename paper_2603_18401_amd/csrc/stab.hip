@@ -126,7 +126,7 @@ __device__ __forceinline__ uint32_t class_ranges(const StabArgs& A, const PairDe
       if (!full) {
         const uint32_t lo = kmin - span, hi = kmax + span;
         const uint32_t cls = (uint32_t)c << kCentreBits;
-        const uint32_t blo = cls | position_code(pd, lo), bhi = cls | position_code(pd, hi);
+        const uint32_t blo = cls | position_code(pd.arc, lo), bhi = cls | position_code(pd.arc, hi);
         // bhi + 1 > blo without a wrap; through the cut the two ranges may
         // meet in one code (and then take the whole class once)
         wrap = lo > hi;
@@ -500,14 +500,14 @@ __global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
         } else {
           const uint32_t* starts = A.group_starts + (int64_t)sg.hist_begin * kHistWords;
           constexpr int kLow = kCentreBits - kRadixBits;
-          const uint32_t d0 = position_code(A.pairs[p], s_k[w0 * kTileQ]) >> kLow;
+          const uint32_t d0 = position_code(A.pairs[p].arc, s_k[w0 * kTileQ]) >> kLow;
           const uint32_t d1 =
-              position_code(A.pairs[p], s_k[(w1 - 1) * kTileQ + s_count[w1 - 1] - 1]) >> kLow;
+              position_code(A.pairs[p].arc, s_k[(w1 - 1) * kTileQ + s_count[w1 - 1] - 1]) >> kLow;
           for (uint32_t d = d0;; d = d1) {
             const uint32_t gs = starts[d] - (uint32_t)sg.begin;
             const uint32_t ge = d + 1 < (uint32_t)kRadix ? starts[d + 1] - (uint32_t)sg.begin
                                                          : (uint32_t)sg.count;
-            if (ge - gs > 2u * (uint32_t)sg.tile && digit_counts(A.pairs[p], d))
+            if (ge - gs > 2u * (uint32_t)sg.tile)
               refine_group(A, sg.begin, gs, ge, pa, pb, w0, tq, s_i, s_k, refine);
             if (d == d1) break;
           }
