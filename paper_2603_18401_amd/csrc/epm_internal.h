@@ -24,12 +24,12 @@ constexpr uint32_t kFullHalf = 0x80000000u;
 // image under a small angle); differences of keys do not notice.  The
 // position code of a key has kCentreBits bits: the arc of the lines that meet
 // image 2 takes all of them but kSideCodes on either side, for the rest of the
-// circle, since keypoints may lie outside their image.  Most of those resolve
+// circle, since keypoints may lie outside their image.  Half of those resolve
 // what borders on the arc, up to twice its length away.  (With the keys beyond
 // the arc all at its ends' codes, a pair of 60000 whose keypoints reach twice
-// as far as the stated image took 3450 us instead of 160.)  The code never
-// decreases with the key, so windows of keys are windows of codes, whatever the
-// arc is.
+// as far as the stated image took 3450 us fused, now 165; twenty times as far
+// 187, and 269 with seven in eight beside the arc.)  The code never decreases
+// with the key, so windows of keys are windows of codes, whatever the arc is.
 //
 // Records are sorted by (width class, position code of the centre).  Class c
 // holds half-widths H with 2^(c-1) <= H < 2^c, so a query at key P only has
@@ -39,7 +39,7 @@ constexpr int kClassBits = 5;
 constexpr int kNumClasses = 32;
 constexpr int kCentreBits = 17;
 constexpr uint32_t kSideCodes = 1u << (kCentreBits - 4);
-constexpr uint32_t kNearCodes = kSideCodes / 8 * 7;
+constexpr uint32_t kNearCodes = kSideCodes / 2;
 constexpr int kRadixBits = 11;  // bits per pass of the sort
 constexpr int kSortBits = kClassBits + kCentreBits;  // two passes
 constexpr int kWideClass = 31;
