@@ -205,8 +205,9 @@ constexpr int kChunk = 512;
 // Queries with equal upper kRadixBits bits of their codes form a group of the
 // one-pass query sort.  What the window pass does with a segment's groups:
 // sort around the boundaries of neighbouring tiles, where groups are small;
-// sort its workgroups' queries, where tiles hold fewer than kTileQ of them;
-// and bring groups of more than two tiles into the order of their keys.
+// sort its workgroups' queries, where groups exceed a tile or tiles hold fewer
+// than kTileQ of them; and bring groups of more than two tiles into the order
+// of their keys.
 constexpr uint32_t kGroupsSmall = 0, kGroupsLocal = 1, kGroupsLarge = 2;
 static_assert(kCentreBits >= kRadixBits, "a group's queries differ in the bits below");
 

@@ -191,10 +191,10 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
   if constexpr (OUT == kOutIndex) {
     // (the first tile's workgroup tells the window pass about large groups)
     if (groups && mine == 0) {
-      const uint32_t most = 2u * (uint32_t)sg.tile;
-      const int large = __syncthreads_or(total[0] > most || total[1] > most);
-      if (tid == 0)
-        groups[t.seg] = large ? kGroupsLarge : sg.tile < kTileQ ? kGroupsLocal : kGroupsSmall;
+      const uint32_t most = max(total[0], total[1]), tile = (uint32_t)sg.tile;
+      const int large = __syncthreads_or(most > 2u * tile);
+      const int local = __syncthreads_or(most > tile) || tile < (uint32_t)kTileQ;
+      if (tid == 0) groups[t.seg] = large ? kGroupsLarge : local ? kGroupsLocal : kGroupsSmall;
       if (large && sg.tile_count >= 2) {
         static_assert(2 * kHistWords == kRadix, "two rows of counts hold the starts");
         uint32_t* g = group_starts + (int64_t)sg.hist_begin * kHistWords;

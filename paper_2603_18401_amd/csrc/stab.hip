@@ -440,7 +440,9 @@ __global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
   // Where queries crowd into groups of more than two tiles, those that leave
   // the workgroup are put in order across their workgroups, and the
   // workgroup's queries are sorted by their whole keys; the latter also where
-  // its tiles hold few of them.
+  // a group exceeds a tile, or the tiles hold few of them.  (Groups of one to
+  // two tiles, 60000 queries with 60 candidates: match and count 189 us without,
+  // 187 with it.)
   __shared__ uint32_t s_i[kWindowQ], s_k[kWindowQ];
   __shared__ int32_t s_pair[kWindowTiles], s_count[kWindowTiles];
   __shared__ uint32_t s_place[kWindowTiles];  // the tile's first place in its segment
