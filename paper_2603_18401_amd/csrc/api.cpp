@@ -38,6 +38,8 @@ struct Layout {
 struct Tiles {
   int rsize = kSortTileMin, qsize = kSortTileMin;
   int64_t r = 0, q = 0, rrows = 0, qrows = 0, stab = 0;
+  int64_t even = 0;  // tiles of the pairs that take kTileQ queries per tile: the first ones
+  int64_t full = 0;  // tiles of kTileQ queries everywhere
   // queries by all bits of their codes: tiles of larger segments
   bool q_two_passes() const { return qsize > kSortTileMin; }
 };
@@ -127,6 +129,10 @@ int64_t stab_tiles_of(const epm_pair& e) {
   return (e.m + tq - 1) / tq;
 }
 
+int64_t even_tiles_of(const epm_pair& e) {
+  return tile_queries(e.m, e.n) == kTileQ ? stab_tiles_of(e) : 0;
+}
+
 // The tiles of a validated batch.
 Tiles tiles_of(const epm_pair* pairs, int P) {
   Tiles T;
@@ -144,6 +150,8 @@ Tiles tiles_of(const epm_pair* pairs, int P) {
     T.rrows += r > 1 ? r : 0;
     T.qrows += q > 1 ? q : 0;
     T.stab += stab_tiles_of(pairs[p]);
+    T.even += even_tiles_of(pairs[p]);
+    T.full += (pairs[p].m + kTileQ - 1) / kTileQ;
   }
   return T;
 }
@@ -281,7 +289,7 @@ struct epm_index {
   int P = 0;
   int64_t N1 = 0, N2 = 0;
   std::vector<PairDev> pairs;
-  std::vector<int32_t> stile_begin;  // first stabbing tile of every pair, and the total
+  std::vector<int32_t> stile_begin;  // first even stabbing tile of every pair, and their total
   std::vector<int64_t> qstart, kstart;
   std::vector<SortSeg> rsegs, qsegs;
   Tiles tiles;
@@ -353,7 +361,7 @@ epm_status index_prepare(const epm_pair* pairs, int32_t num_pairs, void* workspa
   idx->stile_begin.resize(num_pairs + 1);
   idx->stile_begin[0] = 0;
   for (int p = 0; p < num_pairs; ++p)
-    idx->stile_begin[p + 1] = idx->stile_begin[p] + (int32_t)stab_tiles_of(pairs[p]);
+    idx->stile_begin[p + 1] = idx->stile_begin[p] + (int32_t)even_tiles_of(pairs[p]);
   idx->L = make_layout(num_pairs, n1, n2, idx->tiles);
   if (workspace_bytes < idx->L.total) {
     delete idx;
@@ -385,7 +393,7 @@ hipError_t expand_tiles(const epm_index* idx, hipStream_t stream) {
                              idx->at<int64_t>(L.qstart), idx->at<int32_t>(L.stile_begin), idx->P,
                              idx->at<SortTile>(L.rtiles), T.r, T.rsize,
                              idx->at<SortTile>(L.qtiles), T.q, T.qsize,
-                             idx->at<StabTile>(L.stiles), T.stab, stream);
+                             idx->at<StabTile>(L.stiles), T.even, stream);
 }
 
 epm_status index_upload(epm_index* idx, hipStream_t stream) {
@@ -474,6 +482,8 @@ StabArgs stab_args(epm_index* idx, const float* kp1_xy, int64_t* row_offsets,
   A.capacity = capacity;
   A.tiles = idx->at<StabTile>(L.stiles);
   A.num_tiles = (int)idx->tiles.stab;
+  A.even_tiles = (int)idx->tiles.even;
+  A.split_tiles = nullptr;
   A.staging = idx->at<int32_t>(L.staging);
   A.stats = idx->at<unsigned long long>(L.stats);
   A.long_rows = idx->at<uint32_t>(L.long_rows);
@@ -561,6 +571,11 @@ epm_status enqueue_count(epm_index* idx, StabArgs& A, int64_t* row_offsets,
   const bool xcd_lpt = S.stab_workgroups == 0 && A.num_tiles > kResidentTiles;
   uint32_t* sched = idx->at<uint32_t>(L.sched);  // cleared by the key pass
   A.tile_cost = lpt || xcd_lpt ? idx->at<uint32_t>(L.tile_cost) : nullptr;
+  if (idx->tiles.even < idx->tiles.stab) {
+    A.split_tiles = sched + kSchedSplit;
+    const double fill = (double)idx->tiles.full / kResidentTiles;
+    EPM_HIP(launch_tile_split(A, fill < 1.0 ? (float)fill : 1.0f, stream));
+  }
   EPM_HIP(launch_tile_windows(A, stream));
   A.qperm = idx->qperm;
   if (lpt) {

@@ -227,7 +227,7 @@ constexpr int kTileCounts = 8;
 
 struct StabTile {
   int64_t begin;  // first angle-sorted query position of the tile
-  int32_t count;  // queries in the tile (<= kTileQ)
+  int32_t count;  // queries in the tile (<= kTileQ; 0: not needed)
   int32_t pair;
 };
 
@@ -239,15 +239,13 @@ struct TileQuery {
   uint32_t i, flag, key, pad;
 };
 
-// Queries per tile of a pair with m queries and n records.  A tile's window
-// holds the records between its first and last query, n / m per query, beside
-// those within the tolerance, and windows of more than 1024 records are left
-// to slower passes; so a pair with many records per query takes fewer queries
-// per tile, such that they hold up to 512.  (512 uneven pairs, of whose
-// queries 2 % have more than 8 records each: 3265 us with 64 everywhere --
-// 267 us of it rebuilding and matching the rows of such windows, 280 us a few
-// very long tiles of the wide-row pass -- and 3025 us with this rule; 3060
-// with up to 384.)
+// The fewest queries per tile of a pair with m queries and n records, which
+// say how many tiles it gets; how many queries they take is decided when the
+// pair is queried (launch_tile_split).  A tile's window holds the records
+// between its first and last query, n / m per query, beside those within the
+// tolerance, and windows of more than 1024 records are left to slower passes;
+// so a pair with many records per query may take fewer queries per tile, such
+// that they hold up to 512.
 __host__ __device__ inline int tile_queries(int64_t m, int64_t n) {
   return n <= 8 * m ? kTileQ : n <= 16 * m ? kTileQ / 2 : n <= 32 * m ? kTileQ / 4 : kTileQ / 8;
 }

@@ -44,9 +44,9 @@ struct RecordSort {
 int sort_tile_size(int64_t largest_segment);
 
 // The sort tiles of the records (tr, rsize elements each) and the queries
-// (tq, qsize) and the stabbing tiles (ts), filled from the per-pair segments,
-// the query slice starts and each pair's first stabbing tile (num_pairs + 1
-// entries).
+// (tq, qsize) and the even stabbing tiles (ts), filled from the per-pair
+// segments, the query slice starts and each pair's first even stabbing tile
+// (num_pairs + 1 entries).
 hipError_t launch_expand_tiles(const SortSeg* rsegs, const SortSeg* qsegs, const int64_t* qstart,
                                const int32_t* stile_begin, int num_pairs, SortTile* rtiles,
                                int64_t tr, int rsize, SortTile* qtiles, int64_t tq, int qsize,
@@ -118,8 +118,12 @@ struct StabArgs {
   const int64_t* row_offsets;
   int32_t* cols;
   int64_t capacity;
-  const StabTile* tiles;
-  int num_tiles;
+  // the tiles of the pairs with kTileQ queries each, then as many as
+  // launch_tile_split counts in *split_tiles (NULL: none) for the other pairs;
+  // those past them hold no queries
+  StabTile* tiles;
+  int num_tiles, even_tiles;
+  uint32_t* split_tiles;
   int32_t* staging;  // [n1][kStage], indexed by the original query index
   unsigned long long* stats;  // kNumStats counters, cleared by launch_clear_stats
   // [num_tiles][kTileCounts] per-tile counters of the tile pass (records
@@ -166,8 +170,8 @@ struct StabArgs {
 constexpr int kCostBuckets = 65;  // cost 0, then two buckets per power of two
 constexpr int kLptXcd = 8;        // XCDs the workgroups of a launch are dealt to in turn
 constexpr int kSchedHist = 0, kSchedCursor = kCostBuckets, kSchedStabQueue = 2 * kCostBuckets,
-              kSchedMatchQueue = 2 * kCostBuckets + 1;
-constexpr int kSchedWords = 2 * kCostBuckets + 2;
+              kSchedMatchQueue = 2 * kCostBuckets + 1, kSchedSplit = 2 * kCostBuckets + 2;
+constexpr int kSchedWords = 2 * kCostBuckets + 3;
 
 hipError_t launch_fill_u32(uint32_t* p, int64_t n, uint32_t v, hipStream_t s);
 // Longest-first order of the tiles from their costs; the histogram and cursor
@@ -181,6 +185,10 @@ hipError_t launch_lpt_order(const uint32_t* cost, int num_tiles, uint32_t* sched
 hipError_t launch_xcd_lpt_order(const uint32_t* cost, int num_tiles, uint32_t* block_tile,
                                 hipStream_t s);
 
+// The tiles of the pairs with many records per query, with as many queries as
+// their records' widths suggest (*a.split_tiles zero before).  fill: the part
+// of the chip that tiles of kTileQ queries everywhere would fill (at most 1).
+hipError_t launch_tile_split(const StabArgs& a, float fill, hipStream_t s);
 // One wavefront per tile finds the tile's window in every width class.
 hipError_t launch_tile_windows(const StabArgs& a, hipStream_t s);
 

@@ -96,11 +96,10 @@ __global__ __launch_bounds__(256) void k_expand_tiles(
       else hi = mid - 1;
     }
     const int64_t m = qstart[lo + 1] - qstart[lo];
-    const int tq_size = tile_queries(m, rsegs[lo].count);
-    const int64_t o = (t - stile_begin[lo]) * tq_size;
+    const int64_t o = (t - stile_begin[lo]) * kTileQ;
     StabTile st;
     st.begin = qstart[lo] + o;
-    st.count = (int32_t)(m - o < tq_size ? m - o : tq_size);
+    st.count = (int32_t)(m - o < kTileQ ? m - o : kTileQ);
     st.pair = lo;
     stiles[t] = st;
   }

@@ -71,6 +71,25 @@ __device__ void wave_sort_lds(int32_t* buf, int len) {
   }
 }
 
+// Position of the k-th set bit (k from 0) of w, which has more than k bits set.
+__device__ __forceinline__ int nth_bit(uint64_t w, uint32_t k) {
+  const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
+  const uint32_t below = (uint32_t)__popc(lo);
+  const bool up = k >= below;
+  uint32_t x = up ? hi : lo;
+  k = up ? k - below : k;
+  int pos = up ? 32 : 0;
+  #pragma unroll
+  for (int half = 16; half > 0; half >>= 1) {
+    const uint32_t c = (uint32_t)__popc(x & ((1u << half) - 1u));
+    const bool u = k >= c;
+    k = u ? k - c : k;
+    x = u ? x >> half : x;
+    pos += u ? half : 0;
+  }
+  return pos;
+}
+
 struct QueryCtx {
   double a, b, c;
   uint32_t key;
@@ -273,6 +292,88 @@ constexpr int kQPerWave = kTileQ / kWaves;
 static_assert(kQPerWave == 16, "the pair test packs four records of 16 queries per wavefront");
 static_assert(kTileQ == 64, "pair indexing uses a 6-bit query field");
 
+// Queries per tile of the pairs with many records per query: a workgroup per
+// pair, which looks at kSplitSamples places and takes as many queries as the
+// cheapest of 64, 32, 16 and 8 for the windows that they would have there.  With
+// w records that the middle of 64 queries can meet and v more between the
+// first and the last, T of them have about w + v T / 64 records in their
+// window; a tile's time is taken as that and kTileCost, times the tiles that run
+// one after another, and kLongCost times that for rows that a fused pass leaves
+// because of the window's length.  (Rows of more than kStage candidates go to
+// the wide-row pass, whose time is the windows' too: there small tiles only
+// multiply it.)
+// What bounds it: a binary search per place and the atomic of a pair's base,
+// about 10 us beside the other passes.  What it gives, counted / matched in BF16
+// in one call: 48 pairs of 1000 queries and 40000 records take 198 / 455 us at
+// 22 candidates per query and 518 / 929 at 1083 with 64 queries in all tiles,
+// 236 / 375 and 1106 / 2021 with tile_queries' numbers, 213 / 379 and 509 / 882
+// with this; one pair of 2000 and 100000 at 21: 188 / 174, 76 / 124, 87 / 127;
+// 512 uneven pairs in BF16: 3327 us, 2960, 2990 (with kLongWindow 600: 3262;
+// with kTileCost 64: 3014).
+constexpr int kSplitSamples = 8;
+constexpr int kSplitThreads = 2 * kWave * kSplitSamples;  // two wavefronts per place
+constexpr float kTileCost = 256.0f, kLongCost = 4.0f, kLongWindow = 900.0f;
+__global__ __launch_bounds__(kSplitThreads) void k_tile_split(StabArgs A, float fill) {
+  __shared__ float s_cost[kSplitSamples][4], s_one[kSplitSamples];
+  __shared__ uint32_t s_base;
+  const int lane = lane_id(), place = wave_id() >> 1, pair = (int)blockIdx.x;
+  const bool middle = (wave_id() & 1) != 0;  // this wavefront searches for the middle query
+  const PairDev& pd = A.pairs[pair];
+  const int least = tile_queries(pd.m, pd.n);
+  if (least == kTileQ || pd.m == 0) return;  // uniform
+  // 64 queries around the middle of the place's part of the pair
+  const int64_t mid = pd.m * (2 * place + 1) / (2 * kSplitSamples);
+  const int64_t from = mid < kTileQ / 2 ? 0 : mid - kTileQ / 2;
+  const int64_t first = pd.m < kTileQ ? 0 : from + kTileQ <= pd.m ? from : pd.m - kTileQ;
+  const int64_t at = first + lane;
+  const uint32_t qi = at < pd.m ? A.qperm[pd.q_begin + at] : 0u;
+  const bool normal = at < pd.m && A.qflag[qi] == kQueryNormal;
+  const uint32_t key = normal ? A.qkey[qi] : 0u;
+  const uint32_t kmin = wave_min_u32(normal ? key : 0xFFFFFFFFu);
+  const uint32_t kmax = wave_max_u32(key);
+  const uint64_t have = ballot(normal);
+  const uint32_t kmid = (uint32_t)__builtin_amdgcn_readlane(
+      (int)key, have != 0ull ? nth_bit(have, (uint32_t)__popcll(have) / 2u) : 0);
+  uint32_t begin;
+  const float found = (float)wave_sum_u32(class_ranges(
+      A, pd, pair, middle ? kmid : kmin, middle ? kmid : kmax, have != 0ull, begin));
+  if (middle && lane == 0) s_one[place] = found;
+  __syncthreads();
+  const float one = s_one[place], between = fmaxf(found - one, 0.0f);
+  const bool kept_rows = A.qrec != nullptr && one <= 2.0f * kStage;  // rows that a fused pass keeps
+  if (!middle && lane < 4) {
+    const float part = 1.0f / (float)(1 << lane);  // of kTileQ queries
+    const float window = one + between * part;
+    float cost = fmaxf(1.0f, fill / part) * (window + kTileCost);
+    if (kept_rows && window > kLongWindow) cost *= kLongCost;
+    s_cost[place][lane] = cost;
+  }
+  __syncthreads();
+  int best = kTileQ;
+  float best_cost = __builtin_inff();
+  for (int k = 0; k < 4 && kTileQ >> k >= least; ++k) {
+    float cost = 0.0f;
+    #pragma unroll
+    for (int w = 0; w < kSplitSamples; ++w) cost += s_cost[w][k];
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = kTileQ >> k;
+    }
+  }
+  // the pair's tiles, behind those of the pairs that were faster
+  const int64_t tiles = (pd.m + best - 1) / best;
+  if (threadIdx.x == 0) s_base = atomicAdd(A.split_tiles, (uint32_t)tiles);
+  __syncthreads();
+  StabTile* to = A.tiles + A.even_tiles + s_base;
+  for (int64_t t = threadIdx.x; t < tiles; t += kSplitThreads) {
+    StabTile T;
+    T.begin = pd.q_begin + t * best;
+    T.count = (int32_t)(pd.m - t * best < best ? pd.m - t * best : best);
+    T.pair = pair;
+    to[t] = T;
+  }
+}
+
 // Window pass: for tile t, the record ranges of every width class whose
 // centres lie within [min key - 2^c + 1, max key + 2^c - 1] of the tile's
 // queries (class_ranges), one wavefront per tile, so every tile's searches are
@@ -300,11 +401,11 @@ struct Refine {
 };
 
 // Group: places [gs, ge) of the segment that starts at query seg; the workgroup
-// holds places [pa, pb), tq per tile from its tile w0 on.  Called by the whole
-// workgroup.
+// holds places [pa, pb) of it in its tiles w0 to w1 - 1 (place, count: of its
+// tiles).  Called by the whole workgroup.
 __device__ void refine_group(const StabArgs& A, int64_t seg, uint32_t gs, uint32_t ge, uint32_t pa,
-                             uint32_t pb, int w0, uint32_t tq, uint32_t* s_i, uint32_t* s_k,
-                             Refine& S) {
+                             uint32_t pb, int w0, int w1, const uint32_t* place,
+                             const int32_t* count, uint32_t* s_i, uint32_t* s_k, Refine& S) {
   static_assert(kRefineBins == 4 * kWindowThreads, "four bins per thread");
   const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
   const uint32_t n = ge - gs;  // at most 2^17 (one-pass segments)
@@ -382,10 +483,13 @@ __device__ void refine_group(const StabArgs& A, int64_t seg, uint32_t gs, uint32
     uint32_t r = base + b;
     for (uint32_t u = b; u < e; ++u) r += S.v[u] < v ? 1u : 0u;
     if (r >= r0 && r < r1) {
-      const uint32_t x = gs + r - pa;
-      const uint32_t slot = (uint32_t)w0 * kTileQ + x / tq * kTileQ + x % tq;
-      s_i[slot] = perm[v & 0x1FFFFull];
-      s_k[slot] = k;
+      const uint32_t x = gs + r;
+      for (int w = w0; w < w1; ++w) {
+        if (x - place[w] < (uint32_t)count[w]) {
+          s_i[w * kTileQ + (int)(x - place[w])] = perm[v & 0x1FFFFull];
+          s_k[w * kTileQ + (int)(x - place[w])] = k;
+        }
+      }
     }
   }
   __syncthreads();
@@ -448,23 +552,25 @@ __global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
   __shared__ uint32_t s_place[kWindowTiles];  // the tile's first place in its segment
   __shared__ Refine refine;
   const bool live = t < A.num_tiles;
+  const bool used = live && (t < A.even_tiles || t < A.even_tiles + (int)*A.split_tiles);
   StabTile T;
   T.begin = 0;
   T.count = 0;
   T.pair = -1;
-  if (live) T = A.tiles[t];
+  if (used) T = A.tiles[t];
   const int slot = (int)threadIdx.x;
   uint32_t qi = 0u, key = 0xFFFFFFFFu;  // behind every query, by its place
   if (lane < T.count) {
     qi = A.qperm[T.begin + lane];
     key = A.qkey[qi];
   }
-  const bool sorts = live && A.groups && A.groups[T.pair] != kGroupsSmall;
+  const bool sorts = used && A.groups && A.groups[T.pair] != kGroupsSmall;
   s_i[slot] = qi;
   s_k[slot] = key;
+  if (lane == 0) s_pair[wave] = T.pair;
   if (!__syncthreads_or(sorts)) {
     const bool joined = wave + 1 < kWindowTiles && t + 1 < A.num_tiles && T.count == kTileQ &&
-                        A.tiles[t + 1].pair == T.pair;
+                        s_pair[wave + 1] == T.pair;
     uint32_t moved_i = 0u, moved_k = 0u;
     if (joined) {
       const uint64_t v =
@@ -482,35 +588,42 @@ __global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
     key = s_k[slot];
   } else {
     if (lane == 0) {
-      s_pair[wave] = T.pair;
       s_count[wave] = T.count;
-      s_place[wave] = live ? (uint32_t)(T.begin - A.qstart[T.pair]) : 0u;
+      s_place[wave] = used ? (uint32_t)(T.begin - A.qstart[T.pair]) : 0u;
     }
     __syncthreads();
-    int first = 0;  // of this wavefront's run of tiles of one pair
+    int first = 0;             // of this wavefront's run of tiles of one pair
+    uint32_t first_place = 0;  // the run's first place in the segment
     for (int w0 = 0; w0 < kWindowTiles;) {  // uniform
       const int p = s_pair[w0];
-      int w1 = w0 + 1;
-      while (w1 < kWindowTiles && s_pair[w1] == p) ++w1;
-      if (w0 <= wave) first = w0;
-      if (p >= 0 && A.groups[p] == kGroupsLarge) {
+      int w1 = w0, from = w0, last = w0;  // the first and the last tile that holds queries
+      for (; w1 < kWindowTiles && s_pair[w1] == p; ++w1) {
+        if (s_count[from] == 0) from = w1;
+        if (s_count[w1] > 0) last = w1;
+      }
+      if (w0 <= wave) {
+        first = w0;
+        first_place = s_place[from];
+      }
+      if (p >= 0 && s_count[from] > 0 && A.groups[p] == kGroupsLarge) {
         const SortSeg sg = A.qsegs[p];
-        const uint32_t pa = s_place[w0], pb = s_place[w1 - 1] + (uint32_t)s_count[w1 - 1];
-        const uint32_t tq = (uint32_t)s_count[w0];
+        const uint32_t pa = s_place[from], pb = s_place[last] + (uint32_t)s_count[last];
+        const auto put = [&](uint32_t gs, uint32_t ge) {
+          refine_group(A, sg.begin, gs, ge, pa, pb, w0, w1, s_place, s_count, s_i, s_k, refine);
+        };
         if (sg.tile_count < 2) {  // a segment of one sort tile: all of it as one group
-          refine_group(A, sg.begin, 0u, (uint32_t)sg.count, pa, pb, w0, tq, s_i, s_k, refine);
+          put(0u, (uint32_t)sg.count);
         } else {
           const uint32_t* starts = A.group_starts + (int64_t)sg.hist_begin * kHistWords;
           constexpr int kLow = kCentreBits - kRadixBits;
-          const uint32_t d0 = position_code(A.pairs[p].arc, s_k[w0 * kTileQ]) >> kLow;
-          const uint32_t d1 =
-              position_code(A.pairs[p].arc, s_k[(w1 - 1) * kTileQ + s_count[w1 - 1] - 1]) >> kLow;
+          const KeyArc arc = A.pairs[p].arc;
+          const uint32_t d0 = position_code(arc, s_k[from * kTileQ]) >> kLow;
+          const uint32_t d1 = position_code(arc, s_k[last * kTileQ + s_count[last] - 1]) >> kLow;
           for (uint32_t d = d0;; d = d1) {
             const uint32_t gs = starts[d] - (uint32_t)sg.begin;
             const uint32_t ge = d + 1 < (uint32_t)kRadix ? starts[d + 1] - (uint32_t)sg.begin
                                                          : (uint32_t)sg.count;
-            if (ge - gs > 2u * (uint32_t)sg.tile)
-              refine_group(A, sg.begin, gs, ge, pa, pb, w0, tq, s_i, s_k, refine);
+            if (ge - gs > 2u * (uint32_t)sg.tile) put(gs, ge);
             if (d == d1) break;
           }
         }
@@ -526,12 +639,21 @@ __global__ __launch_bounds__(kWindowThreads) void k_tile_windows(StabArgs A) {
     refine.v[slot] = v;
     __syncthreads();
     if (full) {  // the run's k-th query goes to its k-th filled slot
-      const uint64_t mine = refine.v[first * kTileQ + (wave - first) * s_count[first] + lane];
+      const uint64_t mine = refine.v[first * kTileQ + (int)(s_place[wave] - first_place) + lane];
       qi = s_i[(int)(mine & 255ull)];
       key = (uint32_t)(mine >> 8);
     }
   }
   if (!live) return;  // whole wavefronts
+  if (!used) {  // no kernel looks further
+    T.pair = 0;
+    if (lane == 0) A.tiles[t] = T;
+    if (lane == 0) A.tile_wide[t] = 0u;
+    if (lane == 0 && A.tile_cost) A.tile_cost[t] = 0u;
+    if (lane < kTileCounts && A.tile_counts)
+      A.tile_counts[(int64_t)t * kTileCounts + lane] = 0ull;
+    return;
+  }
   bool normal = false, brute = false;
   TileQuery tq;
   tq.a = tq.b = tq.c = 0.0;
@@ -876,25 +998,6 @@ __device__ __forceinline__ void bf_bounds(float at, float nb, float q_nb, float 
               dlo, dhi);
 }
 
-// Position of the k-th set bit (k from 0) of w, which has more than k bits set.
-__device__ __forceinline__ int nth_bit(uint64_t w, uint32_t k) {
-  const uint32_t lo = (uint32_t)w, hi = (uint32_t)(w >> 32);
-  const uint32_t below = (uint32_t)__popc(lo);
-  const bool up = k >= below;
-  uint32_t x = up ? hi : lo;
-  k = up ? k - below : k;
-  int pos = up ? 32 : 0;
-  #pragma unroll
-  for (int half = 16; half > 0; half >>= 1) {
-    const uint32_t c = (uint32_t)__popc(x & ((1u << half) - 1u));
-    const bool u = k >= c;
-    k = u ? k - c : k;
-    x = u ? x >> half : x;
-    pos += u ? half : 0;
-  }
-  return pos;
-}
-
 // f(value of lane S of each row of 16 lanes) for S = 0 .. n - 1 (n <= 16).
 template <int S, class F>
 __device__ __forceinline__ void for_steps(int v, int n, const F& f) {
@@ -1106,6 +1209,11 @@ __global__ __launch_bounds__(kThreads, MODE == kStabBF16 || MODE == kCsrBF16 ? 4
       continue;
     }
     const StabTile T = A.tiles[tile];
+    if (T.count == 0) {
+      if (!PERSIST) return;
+      __syncthreads();
+      continue;
+    }
     const PairDev& pd = A.pairs[T.pair];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
 
@@ -2348,6 +2456,12 @@ __global__ __launch_bounds__(256) void k_clear_stats(unsigned long long* stats, 
 hipError_t launch_clear_stats(unsigned long long* stats, hipStream_t s, uint32_t* sched,
                               unsigned long long* match_stats) {
   hipLaunchKernelGGL(k_clear_stats, dim3(1), dim3(256), 0, s, stats, sched, match_stats);
+  return hipGetLastError();
+}
+
+hipError_t launch_tile_split(const StabArgs& a, float fill, hipStream_t s) {
+  if (a.num_tiles == 0) return hipSuccess;
+  hipLaunchKernelGGL(k_tile_split, dim3((unsigned)a.num_pairs), dim3(kSplitThreads), 0, s, a, fill);
   return hipGetLastError();
 }
 
