@@ -306,7 +306,8 @@ struct MatchArgs {
 constexpr int kNumMatchStats = 4;
 constexpr int kMatchStatRest = 4;  // internal: rest-list length of the wide-row match
 constexpr int kMatchStatWords = kMatchStatRest + 1;
-// fmt 0: BF16, 1: FP8-E4M3 with row scales.
+// fmt 0: BF16 with qerr1 and qerr2 (without them launch_stab_tiles' kCsrBF16),
+// 1: FP8-E4M3 with row scales.
 // grid as for launch_stab_tiles.
 hipError_t launch_match_window_mfma(const MatchArgs& a, int fmt, int grid, hipStream_t s);
 

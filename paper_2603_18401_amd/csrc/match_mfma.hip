@@ -163,7 +163,10 @@ __global__ __launch_bounds__(kThreads) void k_match_window_mfma(MatchArgs A) {
       q_norm[tid] = n * s * s;  // squared norm of the dequantised row
       const double nb = sqrt((double)q_norm[tid]) * (1.0 + 1e-5);
       q_nb[tid] = nb;
-      q_db[tid] = A.qerr1 && tid < T.count ? (double)A.qerr1[q_i[tid]] : row_delta<FMT>(nb, s);
+      if (FMT == 0)
+        q_db[tid] = tid < T.count ? (double)A.qerr1[q_i[tid]] : 0.0;
+      else
+        q_db[tid] = A.qerr1 && tid < T.count ? (double)A.qerr1[q_i[tid]] : row_delta<FMT>(nb, s);
     }
 
     const uint32_t wlen = slot_pref[kSlots];
@@ -197,8 +200,11 @@ __global__ __launch_bounds__(kThreads) void k_match_window_mfma(MatchArgs A) {
         w_norm[tid] = n * s * s;
         const double nb = sqrt((double)w_norm[tid]) * (1.0 + 1e-5);
         w_nb[tid] = nb;
-        w_db[tid] = A.qerr2 && row_j[tid] >= 0 ? (double)A.qerr2[kb + row_j[tid]]
-                                               : row_delta<FMT>(nb, s);
+        if (FMT == 0)
+          w_db[tid] = row_j[tid] >= 0 ? (double)A.qerr2[kb + row_j[tid]] : 0.0;
+        else
+          w_db[tid] = A.qerr2 && row_j[tid] >= 0 ? (double)A.qerr2[kb + row_j[tid]]
+                                                 : row_delta<FMT>(nb, s);
       }
       // S = Q W^T: wavefront w owns queries 16w..16w+15 against all 64 rows
       f32x4 acc[4];
@@ -359,6 +365,7 @@ __global__ __launch_bounds__(kThreads) void k_match_window_mfma(MatchArgs A) {
 hipError_t launch_match_window_mfma(const MatchArgs& a, int fmt, int grid, hipStream_t s) {
   if (a.num_tiles == 0) return hipSuccess;
   if (grid > 0 && !a.queue) return hipErrorInvalidValue;
+  if (fmt == 0 && !(a.qerr1 && a.qerr2)) return hipErrorInvalidValue;
   const dim3 g(grid > 0 ? (grid < a.num_tiles ? grid : a.num_tiles) : a.num_tiles);
   if (fmt == 0) {
     if (grid > 0)
