@@ -634,7 +634,10 @@ typedef struct {
   int64_t queries;        /* image-1 queries                                         */
   int64_t reranked_rows;  /* rows ranked on MFMA bounds with a few candidates re-ranked */
   int64_t fallback_rows;  /* of those, not certified: every candidate evaluated exactly */
-  int64_t long_rows;      /* rows beyond a tile's 8192-entry list: evaluated exactly  */
+  int64_t long_rows;      /* rows evaluated exactly without bounds: beyond a tile's
+                             8192-entry list; for BF16 without measured errors, rows
+                             over 128 entries, with repeated or foreign entries, or
+                             in tiles with windows over 1024 records               */
   int64_t exact_distances; /* epm_query_match_bf16 / _fp8: exact FP32 distances of the re-rank */
 } epm_match_stats;
 
@@ -642,10 +645,10 @@ typedef struct {
  * Reads the counters of the last BF16/FP8 (or FP32 on angle tiles) epm_match
  * on idx, or of the rows with more than 128 candidates of the last
  * epm_query_match on idx (ranked on MFMA with BF16 copies of the FP32 rows;
- * long_rows is then 0), and waits for the stream that call used.  fallback_rows / reranked_rows is the rate at which
- * the four re-ranked candidates could not be certified to contain the exact
- * best and second; those rows are then evaluated exactly, so results never
- * depend on it.
+ * long_rows is then 0), and waits for the stream that call used.
+ * fallback_rows / reranked_rows is the rate at which the re-ranked candidates
+ * could not be certified to contain the exact best and second; those rows are
+ * then evaluated exactly, so results never depend on it.
  */
 epm_status epm_get_match_stats(const epm_index* idx, epm_match_stats* out);
 

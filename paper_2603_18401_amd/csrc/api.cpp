@@ -1360,7 +1360,7 @@ epm_status epm_batch_create(const epm_pair* pairs, int32_t num_pairs, const epm_
       r = EPM_ERR_HIP;
     if (r == EPM_OK) r = enqueue_build(idx, d->kp2_xy, d->eps2, d->eps_scalar, cs2);
     if (r == EPM_OK && hipEventRecord(join, cs2) != hipSuccess) r = EPM_ERR_HIP;
-    // after the build: the stab arguments name the sorted key buffer it chose
+    // (the stab arguments name the buffers of the query sort and of this index)
     StabArgs A = stab_args(idx, d->kp1_xy, d->row_offsets, d->col_indices, d->capacity);
     // FP32, BF16 and FP8 with error bounds on the tiled path: selection fused
     // into the stabbing pass

@@ -27,8 +27,9 @@ constexpr uint32_t kFullHalf = 0x80000000u;
 // circle, since keypoints may lie outside their image.  Half of those resolve
 // what borders on the arc, up to twice its length away.  (With the keys beyond
 // the arc all at its ends' codes, a pair of 60000 whose keypoints reach twice
-// as far as the stated image took 3450 us fused, now 165; twenty times as far
-// 187, and 269 with seven in eight beside the arc.)  The code never decreases
+// as far as the stated image took 3450 us fused, now 167; twenty times as far
+// 187, and 269 with seven in eight beside the arc.  The three pieces add 5 us
+// to 65 for four million keys.)  The code never decreases
 // with the key, so windows of keys are windows of codes, whatever the arc is.
 //
 // Records are sorted by (width class, position code of the centre).  Class c

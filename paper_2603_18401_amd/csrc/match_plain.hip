@@ -81,11 +81,21 @@ __global__ __launch_bounds__(kThreads) void k_match_plain_bin256(MatchArgs A) {
 // what bounds a wavefront is the latency of its dependent loads and of the
 // merge, which here goes by DPP.  Two lanes read a candidate's two halves (one
 // line, one address slot; 19.4 us with both read by one lane).  A candidate is
-// kept as (distance, j) in one 64-bit key.  60000 queries with 66 candidates each: 30.0 us with a wavefront
-// per query, 15.9 this way.
+// kept as (distance, j) in one 64-bit key.  60000 queries with 66 candidates
+// each: 30.0 us with a wavefront per query, 15.9 this way.
+//
+// Where the line lies, in us per call with a wavefront per query / 16 lanes,
+// for rows of 9, 70, 320, 1070 and 4250 candidates:
+//    8192 queries  11.0/11.4  11.3/11.6  14.3/12.8  41.3/33.9  139/114
+//   16384          11.1/12.0  11.8/11.5  25.9/16.6  74.0/43.0  330/181
+//   24576          11.6/12.1  14.8/11.7  36.7/21.1   108/56.0  544/268
+//   32768          13.7/11.1  19.0/11.4  47.5/26.8   143/72.4  726/367
+//   65536          27.5/11.3  34.2/17.4  89.9/45.1   365/174  1461/700
+// From 32768 on the groups win everywhere; below, rows of a few candidates are
+// as fast with a wavefront each (the line could lie lower for longer rows).
 constexpr int kBinLanes = 16;
 constexpr int kBinQueries = kThreads / kBinLanes;
-constexpr int64_t kBinGroupMin = 32768;  // queries that fill the chip at four per wavefront
+constexpr int64_t kBinGroupMin = 32768;
 __global__ __launch_bounds__(kThreads) void k_match_groups_bin256(MatchArgs A) {
   if (csr_overflow(A)) return;
   const int sub = (int)threadIdx.x & (kBinLanes - 1);

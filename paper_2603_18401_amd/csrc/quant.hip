@@ -11,8 +11,11 @@
 // instructions; other widths, and arrays that are not aligned, one wavefront
 // per row and a value per lane.  500003 rows of 128, before -> now: to BF16
 // 98 -> 57 us, to FP8 171 -> 57 us, rounding error of BF16 rows
-// 120 -> 84 us, of FP8 rows 185 -> 64 us (the bytes alone, at the 4.9 TB/s
-// of a large copy from and to HBM: 78, 66, 79, 66 us).
+// 120 -> 84 us, of FP8 rows 185 -> 64 us.  (These follow one another on the
+// same rows, part of which is still in the memory-side cache then: the bytes
+// alone, at the 4.9 TB/s of a large copy from and to HBM, are 78, 66, 79 and
+// 66 us.  After 1 GiB of other writes, some of which are still to be written
+// back, the four take 102, 98, 117 and 108 us, and a 256 MB copy 132.)
 #include "device_common.h"
 #include "launch.h"
 

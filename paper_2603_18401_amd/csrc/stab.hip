@@ -303,7 +303,7 @@ static_assert(kTileQ == 64, "pair indexing uses a 6-bit query field");
 // the wide-row pass, whose time is the windows' too: there small tiles only
 // multiply it.)
 // What bounds it: a binary search per place and the atomic of a pair's base,
-// about 10 us beside the other passes.  What it gives, counted / matched in BF16
+// 10 us for a pair, 14 for 512.  What it gives, counted / matched in BF16
 // in one call: 48 pairs of 1000 queries and 40000 records take 198 / 455 us at
 // 22 candidates per query and 518 / 929 at 1083 with 64 queries in all tiles,
 // 236 / 375 and 1106 / 2021 with tile_queries' numbers, 213 / 379 and 509 / 882
@@ -391,7 +391,7 @@ static_assert(kWindowQ == kWindowThreads, "a thread per query slot");
 // in all of its workgroups.  What bounds it: three walks over the group by a
 // workgroup, a few loads per thread for groups of a thousand.  (Without it
 // 60000 queries and 240000 records in 8 of the 2048 groups took 1665 us to
-// count instead of 270.)
+// count, 167 with it.)
 constexpr int kRefineBins = 1024, kRefineBin = 384;
 constexpr int kRefineMax = kWindowQ + 2 * kRefineBin;
 struct Refine {

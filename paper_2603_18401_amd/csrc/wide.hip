@@ -309,9 +309,9 @@ __device__ __forceinline__ void stage_pre(const Rows& R, uint8_t* dst, float* nr
   }
 }
 
-// One window entry in ascending j: its image-2 index and record.
 typedef __attribute__((address_space(1))) int32_t* GlobalInt;
 
+// One window entry in ascending j: its image-2 index and record.
 struct Entry {
   int32_t j;
   uint32_t C, H;
@@ -476,8 +476,8 @@ __global__ __launch_bounds__(kThreads, MODE == kWideFill ? 1 : 3) void k_wide_ti
   __syncthreads();
   const uint64_t wide_mask = wide_mask_s;
   const int q0 = wave * kQPerWave;  // this wavefront's queries
-  // lane l < 16 holds query q0 + l's row start, its CSR write position and
-  // (match) the largest kept key of its list -- read through readlane
+  // lane l holds the row position and the entries left of query q0 + (l & 15);
+  // lanes 0 to 15 are read through readlane, one query at a time
   const int ql = q0 + (lane & (kQPerWave - 1));
   GlobalInt row_at = (GlobalInt)(A.cols + q_o0[ql]);  // where the row of query q0 + (lane & 15) goes on
   uint32_t row_left = q_len[ql];        // its entries from there on (past its end: wraps)
