@@ -16,7 +16,7 @@
 // 8-bit passes of 512-element tiles and a gather for the records and two for
 // the queries took 52 us for six pairs of 20000 keypoints, 65 us for one of
 // 60000 and 322 us for 3.7 M records and 3.6 M queries; the passes here take
-// 34, 37 and 223 us.
+// 33, 37 and 222 us.
 // Workgroups take their tiles through xcd_tile: groups of consecutive tiles
 // run on one XCD, so what neighbouring tiles of a segment write side by side
 // in every bucket meets in one L2 before it is written back.
@@ -137,7 +137,7 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
     RecordSort R, uint32_t* __restrict__ group_starts, uint32_t* __restrict__ groups) {
   constexpr bool REC = OUT == kOutRecords;
   __shared__ uint32_t run[kRadix];  // the digits' next places
-  __shared__ uint32_t wsum[kSortWaves];
+  __shared__ uint32_t wsum[kSortWaves], wmost[OUT == kOutIndex ? kSortWaves : 1];
   __shared__ __attribute__((aligned(16))) uint8_t wcnt[kSortWaves][kRadix];
   // the round in the order of its digits: starts of the digits, elements
   __shared__ uint16_t local[REC ? kRadix : 1];
@@ -188,19 +188,8 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
   run[2 * tid] = start + before[0];
   run[2 * tid + 1] = start + total[0] + before[1];
   if constexpr (OUT == kOutIndex) {
-    // (the first tile's workgroup tells the window pass about large groups)
-    if (groups && mine == 0) {
-      const uint32_t most = max(total[0], total[1]), tile = (uint32_t)sg.tile;
-      const int large = __syncthreads_or(most > 2u * tile);
-      const int local = __syncthreads_or(most > tile) || tile < (uint32_t)kTileQ;
-      if (tid == 0) groups[t.seg] = large ? kGroupsLarge : local ? kGroupsLocal : kGroupsSmall;
-      if (large && sg.tile_count >= 2) {
-        static_assert(2 * kHistWords == kRadix, "two rows of counts hold the starts");
-        uint32_t* g = group_starts + (int64_t)sg.hist_begin * kHistWords;
-        g[2 * tid] = start;
-        g[2 * tid + 1] = start + total[0];
-      }
-    }
+    const uint32_t most = wave_max_u32(max(total[0], total[1]));
+    if (lane_id() == 0) wmost[wave] = most;  // read at the end
   }
   if constexpr (REC) {
     // the start of width class c: of digit c << (kRadixBits - kClassBits)
@@ -288,6 +277,25 @@ __global__ __launch_bounds__(kSortThreads) void k_sort_pass(
       run[2 * tid] += own[0];
       run[2 * tid + 1] += own[1];
       __syncthreads();
+    }
+  }
+  if constexpr (OUT == kOutIndex) {
+    // The first tile's workgroup tells the window pass about large groups.
+    // (Here, behind a round's barriers: with reductions of its own before the
+    // rounds the pass took 1 us more.)
+    if (groups && mine == 0) {
+      uint32_t most = 0u;
+      #pragma unroll
+      for (int w = 0; w < kSortWaves; ++w) most = max(most, wmost[w]);
+      const uint32_t tile = (uint32_t)sg.tile;
+      const bool large = most > 2u * tile, some = most > tile || tile < (uint32_t)kTileQ;
+      if (tid == 0) groups[t.seg] = large ? kGroupsLarge : some ? kGroupsLocal : kGroupsSmall;
+      if (large && sg.tile_count >= 2) {
+        static_assert(2 * kHistWords == kRadix, "two rows of counts hold the starts");
+        uint32_t* g = group_starts + (int64_t)sg.hist_begin * kHistWords;
+        g[2 * tid] = start;
+        g[2 * tid + 1] = start + total[0];
+      }
     }
   }
 }
